@@ -180,10 +180,12 @@ template <typename T>
 hipError_t launch_trace_sum(double* trace_nodes, const float* trace_e, int m, int W, const T* U, const int* deg, int n,
                             int L, int iters, double* out,
                             hipStream_t st);
+// (ticket: one int of scratch; node_e [n], edge_e [m]: the energy's terms;
+// err, spin_limit: bound of the waits for labels, as in the engines)
 template <typename T>
 hipError_t launch_decode(const T* unaries, const T* tables, const T* phi, const SlotInfo* slots, const int* node_ptr,
-                         const int* inc, int n, int L, int m, int* labels, double* energy, hipStream_t st,
-                         int potts = 0);
+                         const int* inc, int n, int L, int m, int* labels, int* ticket, double* node_e, double* edge_e,
+                         double* energy, int* err, long long spin_limit, hipStream_t st, int potts = 0);
 template <typename T>
 hipError_t launch_check_finite(const T* p, size_t count, int* flag, hipStream_t st);
 template <typename T>

@@ -470,6 +470,29 @@ template <typename T> HsArgs<T> hs_args(mplpxx_solver* h, double* trace) {
   return a;
 }
 
+// Eq. (3) of the current state into the device double `out`
+hipError_t queue_dual(mplpxx_solver* h, double* out) {
+  if (h->dtype == MPLPXX_F32)
+    return launch_dual<float>((const float*)h->d_unaries, (const float*)h->d_tables, (const float*)h->d_phi, h->d_node_ptr,
+                              h->d_inc, h->n, h->L, h->m, h->d_node_min, h->d_edge_min, out, h->stream(), h->potts);
+  return launch_dual<double>((const double*)h->d_unaries, (const double*)h->d_tables, (const double*)h->d_phi,
+                             h->d_node_ptr, h->d_inc, h->n, h->L, h->m, h->d_node_min, h->d_edge_min, out, h->stream());
+}
+
+// the rounding of Eq. (5) into the device array `labels`, its energy into
+// the device double `energy` (d_node_min, d_edge_min and the third scalar
+// are scratch)
+hipError_t queue_decode(mplpxx_solver* h, int* labels, double* energy) {
+  int* ticket = reinterpret_cast<int*>(h->d_scalar + 2);
+  if (h->dtype == MPLPXX_F32)
+    return launch_decode<float>((const float*)h->d_unaries, (const float*)h->d_tables, (const float*)h->d_phi, h->d_slots,
+                                h->d_node_ptr, h->d_inc, h->n, h->L, h->m, labels, ticket, h->d_node_min, h->d_edge_min,
+                                energy, h->d_err, h->spin_limit, h->stream(), h->potts);
+  return launch_decode<double>((const double*)h->d_unaries, (const double*)h->d_tables, (const double*)h->d_phi,
+                               h->d_slots, h->d_node_ptr, h->d_inc, h->n, h->L, h->m, labels, ticket, h->d_node_min,
+                               h->d_edge_min, energy, h->d_err, h->spin_limit, h->stream());
+}
+
 // messages of a workgroup's slots kept in LDS up to this size
 constexpr size_t kPhiLdsBudget = 96 * 1024;
 
@@ -940,14 +963,7 @@ int mplpxx_adjoint_backward(mplpxx_solver* h, void* grad_unaries, void* grad_pai
 
 int mplpxx_dual_bound(mplpxx_solver* h, double* out) {
   if (!h || !out) return fail(MPLPXX_EINVAL, "NULL argument");
-  hipStream_t st = h->stream();
-  if (h->dtype == MPLPXX_F32)
-    HIP_TRY(launch_dual<float>((const float*)h->d_unaries, (const float*)h->d_tables, (const float*)h->d_phi,
-                               h->d_node_ptr, h->d_inc, h->n, h->L, h->m, h->d_node_min, h->d_edge_min, h->d_scalar, st,
-                               h->potts));
-  else
-    HIP_TRY(launch_dual<double>((const double*)h->d_unaries, (const double*)h->d_tables, (const double*)h->d_phi,
-                                h->d_node_ptr, h->d_inc, h->n, h->L, h->m, h->d_node_min, h->d_edge_min, h->d_scalar, st));
+  HIP_TRY(queue_dual(h, h->d_scalar));
   int rc = sync_and_check(h);
   if (rc != MPLPXX_OK) return rc;
   HIP_TRY(hipMemcpy(out, h->d_scalar, sizeof(double), hipMemcpyDeviceToHost));
@@ -956,14 +972,7 @@ int mplpxx_dual_bound(mplpxx_solver* h, double* out) {
 
 int mplpxx_decode(mplpxx_solver* h, int32_t* labels, double* energy) {
   if (!h || !labels) return fail(MPLPXX_EINVAL, "NULL argument");
-  hipStream_t st = h->stream();
-  if (h->dtype == MPLPXX_F32)
-    HIP_TRY(launch_decode<float>((const float*)h->d_unaries, (const float*)h->d_tables, (const float*)h->d_phi,
-                                 h->d_slots, h->d_node_ptr, h->d_inc, h->n, h->L, h->m, h->d_labels, h->d_scalar + 1, st,
-                                 h->potts));
-  else
-    HIP_TRY(launch_decode<double>((const double*)h->d_unaries, (const double*)h->d_tables, (const double*)h->d_phi,
-                                  h->d_slots, h->d_node_ptr, h->d_inc, h->n, h->L, h->m, h->d_labels, h->d_scalar + 1, st));
+  HIP_TRY(queue_decode(h, h->d_labels, h->d_scalar + 1));
   int rc = sync_and_check(h);
   if (rc != MPLPXX_OK) return rc;
   HIP_TRY(hipMemcpy(labels, h->d_labels, (size_t)h->n * sizeof(int), hipMemcpyDeviceToHost));
@@ -994,23 +1003,8 @@ int mplpxx_iterate_gap(mplpxx_solver* h, int32_t k, double* dual, double* energy
       release();
       return rc;
     }
-    hipError_t e;
-    if (h->dtype == MPLPXX_F32) {
-      e = launch_dual<float>((const float*)h->d_unaries, (const float*)h->d_tables, (const float*)h->d_phi,
-                             h->d_node_ptr, h->d_inc, h->n, h->L, h->m, h->d_node_min, h->d_edge_min, d_gap + it, st,
-                             h->potts);
-      if (e == hipSuccess)
-        e = launch_decode<float>((const float*)h->d_unaries, (const float*)h->d_tables, (const float*)h->d_phi,
-                                 h->d_slots, h->d_node_ptr, h->d_inc, h->n, h->L, h->m, d_lab + (size_t)it * h->n,
-                                 d_gap + k + it, st, h->potts);
-    } else {
-      e = launch_dual<double>((const double*)h->d_unaries, (const double*)h->d_tables, (const double*)h->d_phi,
-                              h->d_node_ptr, h->d_inc, h->n, h->L, h->m, h->d_node_min, h->d_edge_min, d_gap + it, st);
-      if (e == hipSuccess)
-        e = launch_decode<double>((const double*)h->d_unaries, (const double*)h->d_tables, (const double*)h->d_phi,
-                                  h->d_slots, h->d_node_ptr, h->d_inc, h->n, h->L, h->m, d_lab + (size_t)it * h->n,
-                                  d_gap + k + it, st);
-    }
+    hipError_t e = queue_dual(h, d_gap + it);
+    if (e == hipSuccess) e = queue_decode(h, d_lab + (size_t)it * h->n, d_gap + k + it);
     if (e != hipSuccess) {
       release();
       return fail(MPLPXX_EDEVICE, "gap trace: %s", hipGetErrorString(e));
