@@ -52,7 +52,7 @@ struct mplpxx_batch {
   int count = 0;
   std::vector<ModelHost> mh;
   std::vector<BatchModel> md;
-  long long total_tables = 0, total_phi = 0, total_u = 0;
+  long long total_tables = 0, total_phi = 0, total_u = 0, total_mb = 0;
   int total_slots = 0, total_nodes = 0, total_csr = 0, total_inc = 0;
   int max_lt = 16;
   // device
@@ -365,12 +365,12 @@ hipError_t enqueue(mplpxx_batch* b, int k) {
   a.qlen = b->qlen;
   hipError_t e = launch_fill_int(b->d_ticket, 0, 2, b->stream);
   if (e != hipSuccess) return e;
-  e = launch_u_to_mb(b->d_U, b->d_Ulo, b->d_mb, (size_t)b->total_u, b->stream);
+  e = launch_u_to_mb(b->d_U, b->d_Ulo, b->d_mb, b->d_models, b->d_node_model, b->total_nodes, b->stream);
   if (e != hipSuccess) return e;
   e = b->wave ? launch_wbatch(a, b->grid, k, b->lds_bytes, b->potts, b->stream)
               : launch_batch(a, b->max_lt, b->grid, k, b->lds_bytes, b->stream);
   if (e != hipSuccess) return e;
-  return launch_mb_to_u(b->d_U, b->d_Ulo, b->d_mb, (size_t)b->total_u, b->stream);
+  return launch_mb_to_u(b->d_U, b->d_Ulo, b->d_mb, b->d_models, b->d_node_model, b->total_nodes, b->stream);
 }
 
 }  // namespace
@@ -436,6 +436,7 @@ static int create_batch(int32_t count, const int32_t* n, const int32_t* L, const
     d.table_off = b->total_tables;
     d.phi_off = b->total_phi;
     d.u_off = b->total_u;
+    d.mb_off = b->total_mb;
     d.slot_off = b->total_slots;
     d.node_off = b->total_nodes;
     d.n = h.n;
@@ -448,6 +449,7 @@ static int create_batch(int32_t count, const int32_t* n, const int32_t* L, const
     b->total_tables += (long long)h.m * (potts ? (long long)cost_params(potts) : (long long)h.L * h.L);
     b->total_phi += (long long)h.m * 2 * h.L;
     b->total_u += (long long)h.n * h.L;
+    b->total_mb += (long long)h.n * mb_row_words(h.L);
     b->total_slots += h.m;
     b->total_nodes += h.n;
     b->total_csr += h.n + 1;
@@ -476,7 +478,7 @@ static int create_batch(int32_t count, const int32_t* n, const int32_t* L, const
   TRY(alloc((void**)&b->d_U, (size_t)b->total_u * sizeof(float)));
   TRY(alloc((void**)&b->d_Ulo, (size_t)b->total_u * sizeof(float)));
   TRY(alloc((void**)&b->d_unaries, (size_t)b->total_u * sizeof(float)));
-  TRY(alloc((void**)&b->d_mb, (size_t)b->total_u * sizeof(unsigned long long)));
+  TRY(alloc((void**)&b->d_mb, (size_t)b->total_mb * sizeof(unsigned long long)));
   TRY(alloc((void**)&b->d_slots, (size_t)b->total_slots * sizeof(SlotInfo)));
   TRY(alloc((void**)&b->d_deg, (size_t)b->total_nodes * sizeof(int)));
   TRY(alloc((void**)&b->d_models, (size_t)count * sizeof(BatchModel)));

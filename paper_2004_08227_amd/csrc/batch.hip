@@ -19,6 +19,12 @@
 
 namespace mplpxx {
 
+// mailbox word of entry i of a model's n x L unaries
+__device__ __forceinline__ size_t mb_word(int i, int L) {
+  const int u = i / L;
+  return (size_t)u * mb_row_words(L) + (i - u * L);
+}
+
 template <int NT, int MAXLT> union BatchSmem {
   SmemMB<16, NT> s16;
   SmemMB<32, NT> s32;
@@ -30,9 +36,9 @@ template <int LT, int NT>
 __device__ __forceinline__ bool run_task(const BatchArgs& b, const BatchModel& md, const BatchTask& task,
                                          SmemMB<LT, NT>& sm, int iters, unsigned char* dyn) {
   if (threadIdx.x == 0) sm.abort_flag = 0;
-  MbView v{b.tables + uni(md.table_off), b.phi + uni(md.phi_off), b.mb + uni(md.u_off), b.slots + uni(md.slot_off),
+  MbView v{b.tables + uni(md.table_off), b.phi + uni(md.phi_off), b.mb + uni(md.mb_off), b.slots + uni(md.slot_off),
            b.deg + uni(md.node_off), nullptr, nullptr, nullptr, uni(md.L), uni(md.m), uni(md.n), nullptr, nullptr,
-           b.sink + (size_t)blockIdx.x * (NT + 128)};
+           b.sink + (size_t)blockIdx.x * (NT + 128), mb_row_words(uni(md.L))};
   // messages prefetched with the tables when the task owns at least
   // DEPTH + 2 slots
   constexpr int kDepth = LT <= 64 ? 2 : 1;
@@ -50,7 +56,7 @@ __device__ __forceinline__ bool run_task(const BatchArgs& b, const BatchModel& m
   v.lds_hi = reinterpret_cast<float*>(dyn);
   v.lds_lo = reinterpret_cast<unsigned short*>(dyn + lds_lo_offset(md.n, md.L));
   for (int i = threadIdx.x; i < nl; i += blockDim.x) {
-    const unsigned long long w = v.mb[i];
+    const unsigned long long w = v.mb[mb_word(i, md.L)];
     v.lds_hi[i] = mb_hi(w);
     v.lds_lo[i] = (unsigned short)(__float_as_uint(mb_lo(w)) >> 16);
   }
@@ -60,7 +66,7 @@ __device__ __forceinline__ bool run_task(const BatchArgs& b, const BatchModel& m
                                                                        b.err);
   __syncthreads();
   for (int i = threadIdx.x; i < nl; i += blockDim.x)
-    v.mb[i] = mb_pack(v.lds_hi[i], __uint_as_float((unsigned)v.lds_lo[i] << 16), 0u);
+    v.mb[mb_word(i, md.L)] = mb_pack(v.lds_hi[i], __uint_as_float((unsigned)v.lds_lo[i] << 16), 0u);
   return ok;
 }
 
@@ -177,9 +183,9 @@ template <int LT, int KIND = kCostDense>
 __device__ __forceinline__ void wv_task(const BatchArgs& b, const BatchModel& md, const BatchTask& task,
                                         WvScratch& scr, int iters, unsigned char* dyn, int* abort) {
   const int wave = threadIdx.x >> 6;
-  WvView v{b.tables + uni(md.table_off), b.phi + uni(md.phi_off), b.mb + uni(md.u_off), b.slots + uni(md.slot_off),
+  WvView v{b.tables + uni(md.table_off), b.phi + uni(md.phi_off), b.mb + uni(md.mb_off), b.slots + uni(md.slot_off),
            uni(md.L), uni(md.m), uni(md.n), nullptr, nullptr, nullptr,
-           b.sink + ((size_t)blockIdx.x * kWvWaves + wave) * kWvSink};
+           b.sink + ((size_t)blockIdx.x * kWvWaves + wave) * kWvSink, mb_row_words(uni(md.L))};
   const int first = uni(task.first + wave * task.stride);
   const int stride = uni(task.stride * kWvWaves);
   const int owned = first < md.m ? (md.m - first + stride - 1) / stride : 0;
@@ -195,7 +201,7 @@ __device__ __forceinline__ void wv_task(const BatchArgs& b, const BatchModel& md
   v.lds_lo = reinterpret_cast<unsigned short*>(dyn + lds_lo_offset(md.n, md.L));
   v.lds_ver = reinterpret_cast<int*>(dyn + wv_ver_offset(md.n, md.L));
   for (int i = threadIdx.x; i < nl; i += blockDim.x) {
-    const unsigned long long w = v.mb[i];
+    const unsigned long long w = v.mb[mb_word(i, md.L)];
     v.lds_hi[i] = mb_hi(w);
     v.lds_lo[i] = (unsigned short)(__float_as_uint(mb_lo(w)) >> 16);
   }
@@ -205,7 +211,7 @@ __device__ __forceinline__ void wv_task(const BatchArgs& b, const BatchModel& md
   else (void)wv_run<LT, true, false, KIND>(v, first, stride, iters, scr, b.spin_limit, b.err, abort);
   __syncthreads();
   for (int i = threadIdx.x; i < nl; i += blockDim.x)
-    v.mb[i] = mb_pack(v.lds_hi[i], __uint_as_float((unsigned)v.lds_lo[i] << 16), 0u);
+    v.mb[mb_word(i, md.L)] = mb_pack(v.lds_hi[i], __uint_as_float((unsigned)v.lds_lo[i] << 16), 0u);
 }
 
 // KIND: a batch of models with structured costs (mplpxx_batch_create_potts,
@@ -292,30 +298,39 @@ size_t wbatch_lds_limit(size_t* static_bytes, int kind) {
   return limit;
 }
 
-// mailbox <- (U, Ulo, version 0) and back
-__global__ void k_u_to_mb(const float* __restrict__ U, const float* __restrict__ Ulo,
-                          unsigned long long* __restrict__ mb, size_t count) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < count; i += (size_t)gridDim.x * blockDim.x)
-    mb[i] = mb_pack(U[i], Ulo[i], 0u);
+// mailbox <- (U, Ulo, version 0) and back: one wave per node of the batch
+__global__ void __launch_bounds__(64) k_u_to_mb(const float* __restrict__ U, const float* __restrict__ Ulo,
+                                                unsigned long long* __restrict__ mb,
+                                                const BatchModel* __restrict__ models,
+                                                const int* __restrict__ node_model) {
+  const BatchModel& md = models[node_model[blockIdx.x]];
+  const int u = blockIdx.x - md.node_off;
+  for (int s = threadIdx.x; s < md.L; s += 64) {
+    const size_t i = md.u_off + (size_t)u * md.L + s;
+    mb[md.mb_off + (size_t)u * mb_row_words(md.L) + s] = mb_pack(U[i], Ulo[i], 0u);
+  }
 }
-__global__ void k_mb_to_u(float* __restrict__ U, float* __restrict__ Ulo, const unsigned long long* __restrict__ mb,
-                          size_t count) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < count; i += (size_t)gridDim.x * blockDim.x) {
-    const unsigned long long w = mb[i];
+__global__ void __launch_bounds__(64) k_mb_to_u(float* __restrict__ U, float* __restrict__ Ulo,
+                                                const unsigned long long* __restrict__ mb,
+                                                const BatchModel* __restrict__ models,
+                                                const int* __restrict__ node_model) {
+  const BatchModel& md = models[node_model[blockIdx.x]];
+  const int u = blockIdx.x - md.node_off;
+  for (int s = threadIdx.x; s < md.L; s += 64) {
+    const size_t i = md.u_off + (size_t)u * md.L + s;
+    const unsigned long long w = mb[md.mb_off + (size_t)u * mb_row_words(md.L) + s];
     U[i] = mb_hi(w);
     Ulo[i] = mb_lo(w);
   }
 }
-static unsigned blocks_for(size_t count) {
-  size_t b = (count + 255) / 256;
-  return (unsigned)(b > 2048 ? 2048 : (b == 0 ? 1 : b));
-}
-hipError_t launch_u_to_mb(const float* U, const float* Ulo, unsigned long long* mb, size_t count, hipStream_t st) {
-  hipLaunchKernelGGL(k_u_to_mb, dim3(blocks_for(count)), dim3(256), 0, st, U, Ulo, mb, count);
+hipError_t launch_u_to_mb(const float* U, const float* Ulo, unsigned long long* mb, const BatchModel* models,
+                          const int* node_model, int total_nodes, hipStream_t st) {
+  hipLaunchKernelGGL(k_u_to_mb, dim3(total_nodes), dim3(64), 0, st, U, Ulo, mb, models, node_model);
   return hipGetLastError();
 }
-hipError_t launch_mb_to_u(float* U, float* Ulo, const unsigned long long* mb, size_t count, hipStream_t st) {
-  hipLaunchKernelGGL(k_mb_to_u, dim3(blocks_for(count)), dim3(256), 0, st, U, Ulo, mb, count);
+hipError_t launch_mb_to_u(float* U, float* Ulo, const unsigned long long* mb, const BatchModel* models,
+                          const int* node_model, int total_nodes, hipStream_t st) {
+  hipLaunchKernelGGL(k_mb_to_u, dim3(total_nodes), dim3(64), 0, st, U, Ulo, mb, models, node_model);
   return hipGetLastError();
 }
 

@@ -54,6 +54,14 @@ struct SlotInfo {
   int step;    // index of its matching in the schedule
 };
 
+// Words of one node's row of mailboxes: whole 128-byte lines.  Rows of L words
+// share lines wherever L is no multiple of 16, and the polls of one node's
+// waiters then delay the stores of another node's producer.  Microseconds a
+// matching with rows of L words and of whole lines (complete graphs): n = 33,
+// L = 11 1.27 -> 1.15; n = 61, L = 21 1.31 -> 1.21; n = 200, L = 60 1.55 ->
+// 1.43; multiples of 16 the same.
+__host__ __device__ constexpr int mb_row_words(int L) { return (L + 15) / 16 * 16; }
+
 template <typename T> struct HsArgs {
   const T* tables;        // [m][L][L] slot order, read-only (Potts models: [m] weights)
   T* phi;                 // [m][2][L] slot order
@@ -68,6 +76,7 @@ template <typename T> struct HsArgs {
   long long* stamps;      // [m][4] wall-clock stamps of the last iteration, or null
   unsigned long long* sink;  // FP32 mailbox engine: [grid][NT + 128] scratch words
   int L, m, n;
+  int mbs;                // FP32 mailbox engine: words from one node's mailbox row to the next
   long long spin_limit;
 };
 
@@ -77,7 +86,8 @@ template <typename T> struct HsArgs {
 struct BatchModel {
   long long table_off;  // floats into the concatenated tables
   long long phi_off;    // floats into the concatenated messages
-  long long u_off;      // entries into U / mailboxes / unaries (n*L per model)
+  long long u_off;      // entries into U / unaries (n*L per model)
+  long long mb_off;     // words into the mailboxes (n * mb_row_words(L) per model)
   int slot_off;         // first slot of the model in the concatenated SlotInfo
   int node_off;         // first node of the model (degrees, node maps)
   int n, L, m, lt;      // sizes and register tile (16, 32, 64 or 128)
@@ -114,8 +124,10 @@ size_t batch_lds_limit(int max_lt);
 // (FP32), then, from this byte offset, n*L bf16 corrections
 __host__ __device__ inline size_t lds_lo_offset(int n, int L) { return ((size_t)n * L * 4 + 15) / 16 * 16; }
 __host__ __device__ inline size_t lds_model_bytes(int n, int L) { return lds_lo_offset(n, L) + (size_t)n * L * 2; }
-hipError_t launch_u_to_mb(const float* U, const float* Ulo, unsigned long long* mb, size_t count, hipStream_t st);
-hipError_t launch_mb_to_u(float* U, float* Ulo, const unsigned long long* mb, size_t count, hipStream_t st);
+hipError_t launch_u_to_mb(const float* U, const float* Ulo, unsigned long long* mb, const BatchModel* models,
+                          const int* node_model, int total_nodes, hipStream_t st);
+hipError_t launch_mb_to_u(float* U, float* Ulo, const unsigned long long* mb, const BatchModel* models,
+                          const int* node_model, int total_nodes, hipStream_t st);
 hipError_t launch_batch_dual(const float* unaries, const float* tables, const float* phi, const BatchModel* models,
                              const int* node_model, const int* slot_model, const int* node_ptr, const int* inc,
                              int total_nodes, int total_slots, int count, double* node_min, double* edge_min,
@@ -164,8 +176,10 @@ hipError_t launch_persistent_mb(const HsArgs<float>& a, unsigned long long* mb, 
 int max_blocks_per_cu_mb_potts();
 hipError_t launch_persistent_mb_potts(const HsArgs<float>& a, unsigned long long* mb, int grid, int iters,
                                       int phi_in_lds, size_t dyn_lds, hipStream_t st, int kind = MPLPXX_COST_POTTS);
-hipError_t launch_mb_init(const float* U, const float* Ulo, unsigned long long* mb, size_t count, hipStream_t st);
-hipError_t launch_mb_fini(float* U, float* Ulo, const unsigned long long* mb, int n, int L, double* trace_row,
+// (mbs: words of a node's mailbox row)
+hipError_t launch_mb_init(const float* U, const float* Ulo, unsigned long long* mb, int n, int L, int mbs,
+                          hipStream_t st);
+hipError_t launch_mb_fini(float* U, float* Ulo, const unsigned long long* mb, int n, int L, int mbs, double* trace_row,
                           hipStream_t st);
 
 // dual bound, traces, decode (dual.hip)

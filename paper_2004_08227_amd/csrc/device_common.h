@@ -274,14 +274,19 @@ template <typename T, int LT, int NT> struct TileShape {
   static_assert(BR >= 1 && BC >= 1 && RB * BR == LT, "tile shape");
 };
 
-// Table pad of the mailbox engine.  With pads = BIG = 2^126 and every real
-// value below 2^100 in magnitude, the three passes need no masks: a padded
-// column never wins a row minimum (BIG + a_v rounds to BIG); a padded row
-// gets p = BIG, b = -BIG/2 exactly, so it never wins a column minimum of a
-// real column (BIG - BIG/2 = BIG/2) and makes q = BIG/2 in every padded
-// column, which in turn never wins pass 3 (BIG - BIG/2).  All values stay
-// finite and every real minimum is the one over the real entries, so the
-// results are bitwise those of the unpadded tile.
+// Padded labels of the mailbox engine.  The tile is loaded without pads
+// (its entries outside L x L are whatever follows in memory, finite and below
+// 2^100 in magnitude); the pads sit on the per-label vectors instead, O(L)
+// selects where pads on the tile took one per entry, on the step's critical
+// path.  With BIG = 2^126: a padded column has a_v = BIG in pass 1 (any entry
+// plus BIG rounds to BIG, never a row minimum) and -q = BIG in pass 3; a
+// padded row has a_u = 2 BIG, so b = (a_u - p)/2 rounds to BIG and never wins
+// a column minimum in pass 2.  All values stay finite and every real minimum
+// is the one over the real entries, so the results are bitwise those of the
+// unpadded tile.  Microseconds a matching with pads on the tile and on the
+// vectors (complete graphs of 40 nodes): 3.05 -> 2.57 at 100 labels, 2.94 ->
+// 2.61 at 65; within the spread of runs at tiles of 64 and less, whose
+// selects hide behind the handoff.
 constexpr float kPadBig = 0x1p126f;
 
 // Loads the table of one slot into the register tile; pads take `pad`.
@@ -436,7 +441,7 @@ __device__ __forceinline__ bool sync_gather(const unsigned long long* __restrict
 struct MbView {
   const float* tables;          // [m][L][L] slot order
   float* phi;                   // [m][2][L] slot order
-  unsigned long long* mb;       // [n][L] mailboxes
+  unsigned long long* mb;       // [n][mbs] mailboxes
   const SlotInfo* slots;        // [m]
   const int* deg;               // [n]
   double* trace;                // [iters][n] or null
@@ -446,6 +451,7 @@ struct MbView {
   float* lds_hi;                // LDS-resident unaries (hi [n][L], lo as bf16 bits), or null
   unsigned short* lds_lo;
   unsigned long long* sink;     // this workgroup's scratch words [NT + 128] (see the output stores)
+  int mbs;                      // words of a node's mailbox row
 };
 
 // The gather of the LDS-resident mode: hi, lo, centred values and reference
@@ -479,11 +485,10 @@ __device__ __forceinline__ void lds_gather(const float* hi_row, const unsigned s
   if (lane == 0) *dst_c = c;
 }
 
-// Raw tile load for the mailbox engine: every lane loads, at clamped indices
-// (always inside the table), so no load is predicated and no destination
-// register is written twice; the pads are applied when the tile is used
-// (pad_tile).  A predicated load into a register that the pad value was
-// written to makes the compiler wait for every load in flight.
+// Raw tile load for the mailbox engine: every lane loads, so no load is
+// predicated and no destination register is written twice.  (A predicated load
+// into a register that a pad value was written to makes the compiler wait for
+// every load in flight.)
 template <int LT, int NT, bool FULL>
 __device__ __forceinline__ void load_tile_raw(const float* __restrict__ tab, int L,
                                               float (&x)[TileShape<float, LT, NT>::BR][TileShape<float, LT, NT>::BC]) {
@@ -505,8 +510,8 @@ __device__ __forceinline__ void load_tile_raw(const float* __restrict__ tab, int
   } else {
     // rows clamped, columns not: a row segment runs on into the next row
     // (or past the table, into the allocation's zeroed tail); those entries
-    // are replaced by the pad in pad_tile.  One address per row, immediate
-    // offsets for the columns.
+    // never win a minimum (kPadBig).  One address per row, immediate offsets
+    // for the columns.
 #pragma unroll
     for (int i = 0; i < S::BR; ++i) {
       const int s = rb * S::BR + i;
@@ -516,22 +521,6 @@ __device__ __forceinline__ void load_tile_raw(const float* __restrict__ tab, int
     }
   }
 }
-template <int LT, int NT, bool FULL>
-__device__ __forceinline__ void pad_tile(int L, float (&x)[TileShape<float, LT, NT>::BR][TileShape<float, LT, NT>::BC]) {
-  using S = TileShape<float, LT, NT>;
-  if (FULL) return;
-  const int rb = threadIdx.x >> 4, cb = threadIdx.x & 15;
-#pragma unroll
-  for (int i = 0; i < S::BR; ++i) {
-    const int s = rb * S::BR + i;
-#pragma unroll
-    for (int j = 0; j < S::BC; ++j) {
-      const int t = cb * S::BC + j;
-      x[i][j] = (s < L && t < L) ? x[i][j] : kPadBig;
-    }
-  }
-}
-
 // A +0 the compiler cannot see (a visible constant would let it rewrite
 // fl(0 - q) under a minimum as -q, which is -0 for q = +0).
 __device__ __forceinline__ float opaque_zero() {
@@ -549,7 +538,7 @@ __device__ __forceinline__ float ld_const_f(const float* p) {
 // table's value (Potts: +0 on the diagonal, w off it; truncated linear:
 // fl(w min(|s - t|, tau)); truncated quadratic: fl(w min((s - t)^2, tau))),
 // so the passes give the dense engine's bits.
-// Entries outside L x L are replaced by the pad at use (pad_tile).
+// Entries outside L x L are finite and never win a minimum (kPadBig).
 template <int LT, int NT, int KIND>
 __device__ __forceinline__ void gen_tile(const float* prm, float (&x)[TileShape<float, LT, NT>::BR][TileShape<float, LT, NT>::BC]) {
   using S = TileShape<float, LT, NT>;
@@ -638,6 +627,7 @@ __device__ __forceinline__ bool mb_run(const MbView& v_in, int first_in, int str
   v.L = uni(v.L);
   v.m = uni(v.m);
   v.n = uni(v.n);
+  v.mbs = uni(v.mbs);
   const int first = uni(first_in), stride = uni(stride_in), iters = uni(iters_in);
   const int tid = threadIdx.x;
   const int L = FULL ? LT : v.L;
@@ -677,7 +667,7 @@ __device__ __forceinline__ bool mb_run(const MbView& v_in, int first_in, int str
       if (LDSU) {
         lds_gather<LT>(v.lds_hi + (size_t)node * L, v.lds_lo + (size_t)node * L, L, dst, dst_hi, dst_lo,
                        &sm.cc[parity][is_sync_u ? 0 : 1]);
-      } else if (!sync_gather<LT>(v.mb + (size_t)node * L, L, want, dst, dst_hi, dst_lo,
+      } else if (!sync_gather<LT>(v.mb + (size_t)node * v.mbs, L, want, dst, dst_hi, dst_lo,
                                   &sm.cc[parity][is_sync_u ? 0 : 1], spin_limit, err, &seen)) {
         if (lane == 0) {
           // a wait may also end because another workgroup reported first
@@ -798,7 +788,7 @@ __device__ __forceinline__ bool mb_run(const MbView& v_in, int first_in, int str
     unsigned long long* mb_dst = nullptr;
     unsigned ver = 0;
     if (!LDSU) {
-      mb_dst = outk ? v.mb + (size_t)node * L + out_i : v.sink + (tid & ~63);
+      mb_dst = outk ? v.mb + (size_t)node * v.mbs + out_i : v.sink + (tid & ~63);
       ver = (out_u ? want_u : want_v) + 1;
       asm volatile("" ::"v"(mb_dst), "v"(ver));
     }
@@ -810,21 +800,22 @@ __device__ __forceinline__ bool mb_run(const MbView& v_in, int first_in, int str
 #endif
     __syncthreads();
     if (!PHI_FAR) load_phiset(fc, j);
-    pad_tile<LT, NT, FULL>(L, xc);
 #if MPLPXX_FINE_STAMPS
     if (v.stamps && last_iter && tid == 0) v.stamps[(size_t)slot * kStampStride + 5] = wall_clock64();
 #endif
-    // a' = centred U - phi (padded labels read label L-1: any finite value works)
+    // a' = centred U - phi; padded labels take the pads of kPadBig's comment
     float av[S::BC], au[S::BR];
 #pragma unroll
     for (int jj = 0; jj < S::BC; ++jj) {
       const int t = cb * S::BC + jj;
-      av[jj] = sm.uv[parity][(FULL || t < L) ? t : L - 1] - pv[jj];
+      const float x = sm.uv[parity][(FULL || t < L) ? t : L - 1] - pv[jj];
+      av[jj] = (FULL || t < L) ? x : kPadBig;
     }
 #pragma unroll
     for (int i = 0; i < S::BR; ++i) {
       const int s = rb * S::BR + i;
-      au[i] = sm.uu[parity][(FULL || s < L) ? s : L - 1] - pu[i];
+      const float x = sm.uu[parity][(FULL || s < L) ? s : L - 1] - pu[i];
+      au[i] = (FULL || s < L) ? x : 2.0f * kPadBig;
     }
     // the old value (hi, lo) and message of this lane's output; the shift
     // between the centred passes and the messages
@@ -907,7 +898,7 @@ __device__ __forceinline__ bool mb_run(const MbView& v_in, int first_in, int str
       float mn = part[0][jj];
 #pragma unroll
       for (int w = 1; w < S::W; ++w) mn = vmin(mn, part[w][jj]);
-      qv[jj] = mn;
+      qv[jj] = (FULL || cb * S::BC + jj < L) ? mn : -kPadBig;
     }
     // the output column's message q' + delta, q' reduced the same way
     // ((M): (p' - a'_v)/2 + delta; (U): (G/2 - a'_v) + delta)

@@ -282,7 +282,7 @@ __global__ void __launch_bounds__(NT + 128) k_persistent_mb(HsArgs<float> a, uns
   }
   __syncthreads();
   MbView v{a.tables, a.phi, mb, a.slots, a.deg, a.trace, a.trace_e, a.stamps, L, a.m, a.n, nullptr, nullptr,
-           a.sink + (size_t)blockIdx.x * (NT + 128)};
+           a.sink + (size_t)blockIdx.x * (NT + 128), a.mbs};
   if (!mb_run<LT, NT, PHI_LDS, FULL, TRACE, false, PHI_FAR, DEPTH, KIND, RULE>(v, blockIdx.x, G, iters, sm, phi_lds,
                                                                          a.spin_limit, a.err))
     return;
@@ -311,7 +311,7 @@ __global__ void __launch_bounds__(kPottsNT + 128) k_persistent_mb_potts(HsArgs<f
   }
   __syncthreads();
   MbView v{a.tables, a.phi, mb, a.slots, a.deg, nullptr, nullptr, a.stamps, L, a.m, a.n, nullptr, nullptr,
-           a.sink + (size_t)blockIdx.x * (kPottsNT + 128)};
+           a.sink + (size_t)blockIdx.x * (kPottsNT + 128), a.mbs};
   if (!mb_run_potts<PHI_LDS, KIND>(v, blockIdx.x, G, iters, sm, phi_lds, a.spin_limit, a.err)) return;
   __syncthreads();
   if (PHI_LDS) {
@@ -320,20 +320,20 @@ __global__ void __launch_bounds__(kPottsNT + 128) k_persistent_mb_potts(HsArgs<f
   }
 }
 
-// mailbox <- (U, Ulo, version 0)
-__global__ void k_mb_init(const float* __restrict__ U, const float* __restrict__ Ulo,
-                          unsigned long long* __restrict__ mb, size_t count) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < count; i += (size_t)gridDim.x * blockDim.x)
-    mb[i] = mb_pack(U[i], Ulo[i], 0u);
+// mailbox <- (U, Ulo, version 0): one wave per node
+__global__ void __launch_bounds__(64) k_mb_init(const float* __restrict__ U, const float* __restrict__ Ulo,
+                                                unsigned long long* __restrict__ mb, int L, int mbs) {
+  const size_t u = blockIdx.x;
+  for (int s = threadIdx.x; s < L; s += 64) mb[u * mbs + s] = mb_pack(U[u * L + s], Ulo[u * L + s], 0u);
 }
 
 // U, Ulo <- mailbox values; trace row of the last iteration from the final values
 __global__ void k_mb_fini(float* __restrict__ U, float* __restrict__ Ulo, const unsigned long long* __restrict__ mb,
-                          int n, int L, double* __restrict__ trace_row) {
+                          int n, int L, int mbs, double* __restrict__ trace_row) {
   const int u = blockIdx.x;
   double mn = __builtin_inf();
   for (int s = threadIdx.x; s < L; s += 64) {
-    const unsigned long long w = mb[(size_t)u * L + s];
+    const unsigned long long w = mb[(size_t)u * mbs + s];
     U[(size_t)u * L + s] = mb_hi(w);
     Ulo[(size_t)u * L + s] = mb_lo(w);
     mn = __builtin_fmin(mn, (double)mb_hi(w) + (double)mb_lo(w));
@@ -520,17 +520,15 @@ hipError_t launch_persistent_mb_potts(const HsArgs<float>& a, unsigned long long
   return e;
 }
 
-hipError_t launch_mb_init(const float* U, const float* Ulo, unsigned long long* mb, size_t count, hipStream_t st) {
-  size_t blocks = (count + 255) / 256;
-  if (blocks > 1024) blocks = 1024;
-  if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_mb_init, dim3((unsigned)blocks), dim3(256), 0, st, U, Ulo, mb, count);
+hipError_t launch_mb_init(const float* U, const float* Ulo, unsigned long long* mb, int n, int L, int mbs,
+                          hipStream_t st) {
+  hipLaunchKernelGGL(k_mb_init, dim3(n), dim3(64), 0, st, U, Ulo, mb, L, mbs);
   return hipGetLastError();
 }
 
-hipError_t launch_mb_fini(float* U, float* Ulo, const unsigned long long* mb, int n, int L, double* trace_row,
+hipError_t launch_mb_fini(float* U, float* Ulo, const unsigned long long* mb, int n, int L, int mbs, double* trace_row,
                           hipStream_t st) {
-  hipLaunchKernelGGL(k_mb_fini, dim3(n), dim3(64), 0, st, U, Ulo, mb, n, L, trace_row);
+  hipLaunchKernelGGL(k_mb_fini, dim3(n), dim3(64), 0, st, U, Ulo, mb, n, L, mbs, trace_row);
   return hipGetLastError();
 }
 

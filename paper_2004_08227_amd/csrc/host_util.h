@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -73,6 +74,34 @@ inline int check_structured_params(int kind, const float* prm, int64_t m) {
 }
 inline bool known_cost_kind(int kind) {
   return kind == MPLPXX_COST_POTTS || kind == MPLPXX_COST_TRUNC_LINEAR || kind == MPLPXX_COST_TRUNC_QUAD;
+}
+
+// FP32 mailbox engine: messages of a workgroup's slots kept in LDS up to this
+// size
+constexpr size_t kPhiLdsBudget = 96 * 1024;
+
+// Workgroups of the FP32 mailbox engine.
+//  * A matching with more edges than there are compute units: one workgroup
+//    per edge of it as far as they fit (`per_cu` on each compute unit), so a
+//    workgroup runs about one update per matching instead of several one
+//    after another.
+//  * Otherwise two per edge of the largest matching, at most one per compute
+//    unit: while one workgroup updates its edge, the one that owns the edge of
+//    the next matching has its table and waits.  Workgroups beyond that only
+//    poll the same mailboxes and delay the stores into them; with one per edge
+//    a workgroup's own preparation of its next step joins the chain.
+//    Microseconds a matching with one, two and 256 / (edges of a matching)
+//    workgroups per edge: n = 33, L = 11 1.22 / 1.27 / 1.52; n = 61, L = 21
+//    1.32 / 1.31 / 1.45; n = 200, L = 64 1.60 / 1.36 / 1.37; n = 40, L = 100
+//    2.89 / 2.36 / 2.57.
+//    More where the messages of a workgroup's slots would not fit in LDS
+//    otherwise.
+template <typename F>
+inline int mb_default_grid(int max_step, int num_cus, long long m, int L, const F& per_cu) {
+  if (max_step > num_cus) return std::max(num_cus, std::min(max_step, per_cu() * num_cus));
+  const long long slots_in_lds = (long long)(kPhiLdsBudget / (2 * sizeof(float) * L));
+  const long long fit = (m + slots_in_lds - 1) / slots_in_lds;
+  return (int)std::min<long long>(num_cus, std::max<long long>(2ll * max_step, fit));
 }
 
 // smallest register tile (16, 32, 64, 128) holding L labels

@@ -108,19 +108,18 @@ extern "C" int mplpxx_solve_noalloc(int32_t n, int32_t L, int64_t m, const int32
   int cus = 0;
   HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   const int LT = next_tile(L), NT = 256;
-  int G = cus;
-  if (max_step > cus) G = std::max(cus, std::min(max_step, max_blocks_per_cu_mb(LT, NT) * cus));
-  G = std::max(1, std::min<int>(G, (int)std::max<int64_t>(m, 1)));
+  const int G = std::max(
+      1, std::min<int>(mb_default_grid(max_step, cus, m, L, [&] { return max_blocks_per_cu_mb(LT, NT); }),
+                       (int)std::max<int64_t>(m, 1)));
   const size_t nL = (size_t)n * L, mLL = (size_t)m * L * L;
   const size_t owned = ((size_t)m + G - 1) / G;
   const size_t phi_lds = owned * 2 * L * sizeof(float);
-  const int in_lds = phi_lds <= 96 * 1024 && G <= cus ? 1 : 0;
+  const int in_lds = phi_lds <= kPhiLdsBudget && G <= cus ? 1 : 0;
 
   Carver c;
   const size_t o_tab = c.take((mLL + kTailPad) * sizeof(float));
   const size_t o_phi = c.take(((size_t)m * 2 * L + kTailPad) * sizeof(float));
   const size_t o_ulo = c.take(nL * sizeof(float));
-  const size_t o_mb = c.take(nL * sizeof(unsigned long long));
   const size_t o_slots = c.take((size_t)std::max<int64_t>(m, 1) * sizeof(SlotInfo));
   const size_t o_deg = c.take((size_t)n * sizeof(int));
   const size_t o_err = c.take(8 * sizeof(int));
@@ -133,6 +132,10 @@ extern "C" int mplpxx_solve_noalloc(int32_t n, int32_t L, int64_t m, const int32
   const size_t o_se = c.take((size_t)std::max<int64_t>(m, 1) * sizeof(int));
   const size_t o_sf = c.take((size_t)std::max<int64_t>(m, 1) * sizeof(int));
   const size_t o_soe = c.take((size_t)std::max<int64_t>(m, 1) * sizeof(int));
+  // mailbox rows of whole cache lines, or of L words where only those fit
+  int mbs = mb_row_words(L);
+  if (c.used + (size_t)n * mbs * sizeof(unsigned long long) > kScratchBytes) mbs = L;
+  const size_t o_mb = c.take((size_t)n * mbs * sizeof(unsigned long long));
   if (c.used > kScratchBytes)
     return fail(MPLPXX_EINVAL, "the model needs %zu bytes of working memory; mplpxx_solve_noalloc holds at most %zu",
                 c.used, kScratchBytes);
@@ -210,10 +213,11 @@ extern "C" int mplpxx_solve_noalloc(int32_t n, int32_t L, int64_t m, const int32
     a.L = L;
     a.m = (int)m;
     a.n = n;
+    a.mbs = mbs;
     a.spin_limit = 1ll << 22;
-    HIP_TRY(launch_mb_init(U_dev, d_ulo, d_mb, nL, st));
+    HIP_TRY(launch_mb_init(U_dev, d_ulo, d_mb, n, L, mbs, st));
     HIP_TRY(launch_persistent_mb(a, d_mb, LT, NT, G, iters, in_lds, in_lds ? phi_lds : 0, st));
-    HIP_TRY(launch_mb_fini(U_dev, d_ulo, d_mb, n, L, nullptr, st));
+    HIP_TRY(launch_mb_fini(U_dev, d_ulo, d_mb, n, L, mbs, nullptr, st));
   }
   HIP_TRY(launch_dual<float>(unaries_dev, d_tab, d_phi, d_nptr, d_inc, n, L, (int)m, d_nmin, d_emin, d_dual, st));
   if (m > 0) hipLaunchKernelGGL(k_phi_by_edge, dim3((unsigned)m), dim3(256), 0, st, d_phi, d_soe, 2 * L, phi_dev);

@@ -31,6 +31,7 @@ __device__ __forceinline__ bool mb_run_potts(const MbView& v_in, int first_in, i
   v.L = uni(v.L);
   v.m = uni(v.m);
   v.n = uni(v.n);
+  v.mbs = uni(v.mbs);
   const int first = uni(first_in), stride = uni(stride_in), iters = uni(iters_in);
   const int tid = threadIdx.x;
   const int L = v.L;
@@ -59,7 +60,7 @@ __device__ __forceinline__ bool mb_run_potts(const MbView& v_in, int first_in, i
       float* dst_hi = is_sync_u ? sm.uh[parity] : sm.vh[parity];
       float* dst_lo = is_sync_u ? sm.ul[parity] : sm.vl[parity];
       unsigned seen = 0;
-      if (!sync_gather<64>(v.mb + (size_t)node * L, L, want, dst, dst_hi, dst_lo, &sm.cc[parity][is_sync_u ? 0 : 1],
+      if (!sync_gather<64>(v.mb + (size_t)node * v.mbs, L, want, dst, dst_hi, dst_lo, &sm.cc[parity][is_sync_u ? 0 : 1],
                            spin_limit, err, &seen)) {
         if (lane == 0) {
           if (ld_dev(err) == 0 || seen != (want & 0xFFFFu)) report_timeout(err, slot, node, want & 0xFFFFu, seen);
@@ -110,8 +111,8 @@ __device__ __forceinline__ bool mb_run_potts(const MbView& v_in, int first_in, i
     comp_update(hu, lu, fu, phu, nhu, nlu);
     comp_update(hv, lv, fv, phv, nhv, nlv);
     // push back (every lane issues the same stores)
-    mb_store(lout ? v.mb + (size_t)si.u * L + lane : v.sink, mb_pack(nhu, nlu, want_u + 1));
-    mb_store(lout ? v.mb + (size_t)si.v * L + lane : v.sink + 1, mb_pack(nhv, nlv, want_v + 1));
+    mb_store(lout ? v.mb + (size_t)si.u * v.mbs + lane : v.sink, mb_pack(nhu, nlu, want_u + 1));
+    mb_store(lout ? v.mb + (size_t)si.v * v.mbs + lane : v.sink + 1, mb_pack(nhv, nlv, want_v + 1));
     if (PHI_LDS) {
       if (lout) {
         ph[lane] = phu;

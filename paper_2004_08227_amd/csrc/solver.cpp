@@ -167,17 +167,13 @@ struct mplpxx_solver {
     return rule != MPLPXX_RULE_H && dtype == MPLPXX_F32 && !potts && max_deg < 65536 && engine_opt != ENGINE_STEP &&
            (threads_opt == 0 || threads_opt == 256);
   }
-  // FP32 mailbox engine: one workgroup per compute unit, or, when a matching
-  // has more edges than there are compute units, one workgroup per edge of
-  // the largest matching as far as they fit (each workgroup then runs about
-  // one update per matching instead of several one after another)
   bool mb_engine() const { return dtype == MPLPXX_F32 && engine() == ENGINE_PERSISTENT; }
   int grid() const {
     int g = grid_opt > 0 ? grid_opt : num_cus;
-    if (grid_opt == 0 && (mb_engine() || rule_mailbox()) && max_step > num_cus)
-      g = std::max(num_cus, std::min(max_step, (potts && !gen_tiles() ? max_blocks_per_cu_mb_potts()
-                                                                       : max_blocks_per_cu_mb(LT(), NT())) *
-                                                     num_cus));
+    if (grid_opt == 0 && (mb_engine() || rule_mailbox()))
+      g = mb_default_grid(max_step, num_cus, m, L, [&] {
+        return potts && !gen_tiles() ? max_blocks_per_cu_mb_potts() : max_blocks_per_cu_mb(LT(), NT());
+      });
     if (g > m) g = m;
     if (g < 1) g = 1;
     return g;
@@ -326,7 +322,7 @@ int create_impl(int32_t n, int32_t L, int64_t m, const int32_t* edges, const voi
   h->d_scalar = dalloc<double>(4, &ae); TRY(ae);
   h->d_labels = dalloc<int>(n, &ae); TRY(ae);
   if (dtype == MPLPXX_F32) {
-    h->d_mb = dalloc<unsigned long long>(nL, &ae);
+    h->d_mb = dalloc<unsigned long long>((size_t)n * mb_row_words(L), &ae);
     TRY(ae);
     h->d_Ulo = dalloc<float>(nL, &ae);
     TRY(ae);
@@ -493,9 +489,6 @@ hipError_t queue_decode(mplpxx_solver* h, int* labels, double* energy) {
                                h->d_edge_min, energy, h->d_err, h->spin_limit, h->stream());
 }
 
-// messages of a workgroup's slots kept in LDS up to this size
-constexpr size_t kPhiLdsBudget = 96 * 1024;
-
 template <typename T> int iterate_t(mplpxx_solver* h, int k, double* trace_host) {
   hipStream_t st = h->stream();
   if (h->profile && !h->d_stamps && h->m > 0) {
@@ -554,18 +547,19 @@ template <typename T> int iterate_t(mplpxx_solver* h, int k, double* trace_host)
         h->sink_words = words;
       }
       a.sink = h->d_sink;
+      a.mbs = mb_row_words(h->L);
       const size_t owned = ((size_t)h->m + G - 1) / G;
       const size_t phi_bytes = owned * 2 * h->L * sizeof(float);
       // (more than one workgroup per compute unit: messages in HBM, so that
       // the workgroups' LDS never limits how many fit)
       const int in_lds = phi_bytes <= kPhiLdsBudget && G <= h->num_cus && h->phi_opt != 2 ? 1 : 0;
-      HIP_TRY(launch_mb_init(static_cast<const float*>(h->d_U), h->d_Ulo, h->d_mb, (size_t)h->n * h->L, st));
+      HIP_TRY(launch_mb_init(static_cast<const float*>(h->d_U), h->d_Ulo, h->d_mb, h->n, h->L, a.mbs, st));
       if (h->potts && !h->gen_tiles())
         HIP_TRY(launch_persistent_mb_potts(a, h->d_mb, G, k, in_lds, in_lds ? phi_bytes : 0, st, h->potts));
       else
         HIP_TRY(launch_persistent_mb(a, h->d_mb, LT, NT, G, k, in_lds, in_lds ? phi_bytes : 0, st, h->prefetch_opt,
                                      h->gen_tiles() ? h->potts : 0, rule_mb ? h->rule : MPLPXX_RULE_H));
-      HIP_TRY(launch_mb_fini(static_cast<float*>(h->d_U), h->d_Ulo, h->d_mb, h->n, h->L,
+      HIP_TRY(launch_mb_fini(static_cast<float*>(h->d_U), h->d_Ulo, h->d_mb, h->n, h->L, a.mbs,
                              trace_host ? h->d_trace_nodes + (size_t)(k - 1) * h->n : nullptr, st));
     } else if (!trace_host && h->L <= 64) {
       // FP64 without a trace: the mailbox forward (two tagged words per

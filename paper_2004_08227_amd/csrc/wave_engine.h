@@ -86,13 +86,14 @@ template <int LT> struct WvShape {
 struct WvView {
   const float* tables;          // [m][L][L] slot order
   float* phi;                   // [m][2][L] slot order
-  unsigned long long* mb;       // [n][L] mailboxes (mailbox mode)
+  unsigned long long* mb;       // [n][mbs] mailboxes (mailbox mode)
   const SlotInfo* slots;        // [m]
   int L, m, n;
   float* lds_hi;                // LDS mode: [n][L] hi of the unaries
   unsigned short* lds_lo;       //           [n][L] bf16 bits of lo
   int* lds_ver;                 //           [n] updates of each node so far
   unsigned long long* sink;     // this wave's 192 scratch words (stores of lanes without an output)
+  int mbs;                      // words of a node's mailbox row
 };
 
 // Table of one slot into the grid layout: offb[i] is the byte offset of
@@ -150,6 +151,7 @@ __device__ __forceinline__ bool wv_run(const WvView& v_in, int first_in, int str
   v.L = uni(v.L);
   v.m = uni(v.m);
   v.n = uni(v.n);
+  v.mbs = uni(v.mbs);
   const int first = uni(first_in), stride = uni(stride_in), iters = uni(iters_in);
   if (first >= v.m) return true;
   const int L = v.L;
@@ -228,8 +230,8 @@ __device__ __forceinline__ bool wv_run(const WvView& v_in, int first_in, int str
         hv = v.lds_hi[(size_t)si.v * L + li];
         lv = __uint_as_float((unsigned)v.lds_lo[(size_t)si.v * L + li] << 16);
       } else {
-        const unsigned long long* pu = v.mb + (size_t)si.u * L + li;
-        const unsigned long long* pv = v.mb + (size_t)si.v * L + li;
+        const unsigned long long* pu = v.mb + (size_t)si.u * v.mbs + li;
+        const unsigned long long* pv = v.mb + (size_t)si.v * v.mbs + li;
         unsigned long long wu, wv;
         for (;;) {
           wu = mb_load(pu);
@@ -356,8 +358,8 @@ __device__ __forceinline__ bool wv_run(const WvView& v_in, int first_in, int str
         __hip_atomic_store(v.lds_ver + si.v, (int)(want_v + 1), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     } else {
-      mb_store(lout ? v.mb + (size_t)si.u * L + lane : v.sink + lane, mb_pack(nhu, nlu, want_u + 1));
-      mb_store(lout ? v.mb + (size_t)si.v * L + lane : v.sink + 64 + lane, mb_pack(nhv, nlv, want_v + 1));
+      mb_store(lout ? v.mb + (size_t)si.u * v.mbs + lane : v.sink + lane, mb_pack(nhu, nlu, want_u + 1));
+      mb_store(lout ? v.mb + (size_t)si.v * v.mbs + lane : v.sink + 64 + lane, mb_pack(nhv, nlv, want_v + 1));
     }
     si = si_next;
     j = jn;
