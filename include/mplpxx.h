@@ -311,7 +311,9 @@ int mplpxx_iterate_trace(mplpxx_solver* h, int32_t k, double* trace);
 /* Tuning options (never change results: every option gives bitwise the same
  * state, because each entry of a pass is one IEEE add followed by an exact,
  * order-free minimum). */
-#define MPLPXX_OPT_ENGINE 1      /* 0 auto, 1 one launch per matching, 2 persistent
+#define MPLPXX_OPT_ENGINE 1      /* 0 auto (persistent; small dense models with every other option of this
+                                    list at its default on one workgroup), 1 one launch per matching,
+                                    2 persistent
                                     (FP32 handles with a node of degree >= 65536
                                     always run one launch per matching) */
 #define MPLPXX_OPT_THREADS 2     /* threads per workgroup: 0 auto, 256, 512, 1024; 64 (one compute

@@ -17,6 +17,7 @@
 #include "common.h"
 #include "host_util.h"
 #include "schedule.h"
+#include "solo.h"
 
 using namespace mplpxx;
 
@@ -215,9 +216,14 @@ extern "C" int mplpxx_solve_noalloc(int32_t n, int32_t L, int64_t m, const int32
     a.n = n;
     a.mbs = mbs;
     a.spin_limit = 1ll << 22;
-    HIP_TRY(launch_mb_init(U_dev, d_ulo, d_mb, n, L, mbs, st));
-    HIP_TRY(launch_persistent_mb(a, d_mb, LT, NT, G, iters, in_lds, in_lds ? phi_lds : 0, st));
-    HIP_TRY(launch_mb_fini(U_dev, d_ulo, d_mb, n, L, mbs, nullptr, st));
+    if (solo_fits(n, L, (int)m, g.S, max_step, sizeof(float), false)) {
+      const SoloArgs<float> s{d_tab, d_phi, U_dev, d_ulo, d_slots, nullptr, nullptr, L, (int)m, n, g.S};
+      HIP_TRY(launch_solo<float>(s, max_step, iters, st));
+    } else {
+      HIP_TRY(launch_mb_init(U_dev, d_ulo, d_mb, n, L, mbs, st));
+      HIP_TRY(launch_persistent_mb(a, d_mb, LT, NT, G, iters, in_lds, in_lds ? phi_lds : 0, st));
+      HIP_TRY(launch_mb_fini(U_dev, d_ulo, d_mb, n, L, mbs, nullptr, st));
+    }
   }
   HIP_TRY(launch_dual<float>(unaries_dev, d_tab, d_phi, d_nptr, d_inc, n, L, (int)m, d_nmin, d_emin, d_dual, st));
   if (m > 0) hipLaunchKernelGGL(k_phi_by_edge, dim3((unsigned)m), dim3(256), 0, st, d_phi, d_soe, 2 * L, phi_dev);

@@ -1,0 +1,51 @@
+// Host interface of the one-workgroup engine for small models (solo.hip).
+#pragma once
+#include "common.h"
+
+namespace mplpxx {
+
+template <typename T> struct SoloArgs {
+  const T* tables;        // [m][L][L] slot order
+  T* phi;                 // [m][2][L] slot order
+  T* U;                   // [n][L]
+  T* Ulo;                 // [n][L] (FP32)
+  const SlotInfo* slots;  // [m]
+  double* trace;          // [iters][n] node minima after each iteration, or null
+  float* trace_e;         // [iters][m] edge terms (FP32 traces)
+  int L, m, n, S;
+};
+
+// LDS of the launch: unaries, messages, node pairs, matching offsets
+inline size_t solo_lds_bytes(int n, int L, int m, int S, size_t esz) {
+  return ((size_t)n * L * (esz == 4 ? 2 : 1) + (size_t)m * 2 * L) * esz + ((size_t)m + S + 1) * sizeof(int);
+}
+constexpr size_t kSoloLds = 144 * 1024;
+// waves a workgroup can have (registers: the 32-label tile needs 168)
+constexpr int solo_max_waves(int LT) { return LT == 32 ? 12 : 16; }
+
+// Whether the model runs on one workgroup: its state fits in LDS, and one wave
+// per edge of its largest matching gives a shorter step than the mailbox
+// engines.  The step grows with the waves a SIMD has to issue for, the mailbox
+// step does not (microseconds a matching, one workgroup / mailboxes, at 2, 8
+// and 16 edges a matching):
+//   FP32, L = 8   0.43 / 1.18   0.54 / 1.11   0.72 / 1.07
+//   FP32, L = 16  0.51 / 1.07   0.66 / 1.12   0.99 / 1.08
+//   FP32, L = 32  0.87 / 1.16   1.73 / 1.14
+//   FP32 traces, L = 8   0.67 / 1.29   0.82 / 1.27   1.07 / 1.21
+//   FP32 traces, L = 16  0.86 / 1.23   1.20 / 1.37   1.65 / 1.34
+//   FP64, L = 8   0.42 / 1.75   0.55 / 1.78   0.75 / 1.72
+//   FP64, L = 16  0.60 / 1.85   0.83 / 1.88   1.27 / 1.97 (14 edges)
+//   FP64, L = 32  1.15 / 3.12   1.92 / 3.36   2.45 / 3.27 (12 edges)
+// (FP64 traces a little above the FP64 lines, against 2.4 to 4.2).
+inline bool solo_fits(int n, int L, int m, int S, int max_step, size_t esz, bool trace) {
+  if (m < 1 || n > 32767 || L > 32 || solo_lds_bytes(n, L, m, S, esz) > kSoloLds) return false;
+  if (esz == 8) return max_step <= solo_max_waves(L <= 8 ? 8 : L <= 16 ? 16 : 32);
+  if (L <= 8) return max_step <= 16;
+  if (L <= 16) return max_step <= (trace ? 8 : 16);
+  return !trace && max_step <= 2;
+}
+
+// one workgroup of max_step waves (solo_fits holds)
+template <typename T> hipError_t launch_solo(const SoloArgs<T>& a, int max_step, int iters, hipStream_t st);
+
+}  // namespace mplpxx

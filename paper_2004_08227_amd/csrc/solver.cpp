@@ -24,6 +24,7 @@
 
 #include "common.h"
 #include "schedule.h"
+#include "solo.h"
 
 using namespace mplpxx;
 
@@ -114,7 +115,8 @@ struct mplpxx_solver {
   int grid_opt = 0;
   int phi_opt = 0;       // FP32 persistent engine: 0 auto, 1 messages in LDS when they fit, 2 in global memory
   int prefetch_opt = 0;  // FP32 persistent engine: tables loaded 1 or 2 steps ahead (0 auto)
-  long long spin_limit = 1ll << 22;
+  static constexpr long long kSpinDefault = 1ll << 22;
+  long long spin_limit = kSpinDefault;
   int num_cus = 0;
   long long iterations = 0;
   double last_ms = 0.0;
@@ -168,6 +170,13 @@ struct mplpxx_solver {
            (threads_opt == 0 || threads_opt == 256);
   }
   bool mb_engine() const { return dtype == MPLPXX_F32 && engine() == ENGINE_PERSISTENT; }
+  // small models on one workgroup (solo.h), where no option asks for one of
+  // the other engines' ways
+  bool solo(bool trace) const {
+    return rule == MPLPXX_RULE_H && !potts && engine_opt == ENGINE_AUTO && threads_opt == 0 && grid_opt == 0 &&
+           phi_opt == 0 && prefetch_opt == 0 && !profile && spin_limit == kSpinDefault && max_deg < 65536 &&
+           solo_fits(n, L, m, S, max_step, esz, trace);
+  }
   int grid() const {
     int g = grid_opt > 0 ? grid_opt : num_cus;
     if (grid_opt == 0 && (mb_engine() || rule_mailbox()))
@@ -489,6 +498,11 @@ hipError_t queue_decode(mplpxx_solver* h, int* labels, double* energy) {
                                h->d_edge_min, energy, h->d_err, h->spin_limit, h->stream());
 }
 
+template <typename T> SoloArgs<T> solo_args(mplpxx_solver* h, double* trace) {
+  return SoloArgs<T>{static_cast<const T*>(h->d_tables), static_cast<T*>(h->d_phi), static_cast<T*>(h->d_U),
+                     reinterpret_cast<T*>(h->d_Ulo), h->d_slots, trace, h->d_trace_e, h->L, h->m, h->n, h->S};
+}
+
 template <typename T> int iterate_t(mplpxx_solver* h, int k, double* trace_host) {
   hipStream_t st = h->stream();
   if (h->profile && !h->d_stamps && h->m > 0) {
@@ -514,7 +528,9 @@ template <typename T> int iterate_t(mplpxx_solver* h, int k, double* trace_host)
   const int LT = h->LT(), NT = rule_mb ? 256 : h->NT();
   HIP_TRY(hipEventRecord(h->ev0, st));
   if (h->m > 0 && k > 0) {
-    if (engine == ENGINE_STEP) {
+    if (h->solo(trace_host != nullptr)) {
+      HIP_TRY(launch_solo<T>(solo_args<T>(h, trace_host ? h->d_trace_nodes : nullptr), h->max_step, k, st));
+    } else if (engine == ENGINE_STEP) {
       HsArgs<T> a = hs_args<T>(h, nullptr);
       for (int it = 0; it < k; ++it) {
         for (int s = 0; s < h->S; ++s) {
@@ -624,11 +640,15 @@ int adjoint_grid(const mplpxx_solver* h, bool two_roles) {
 int fwd64_segment(mplpxx_solver* h, int seg) {
   hipStream_t st = h->stream();
   const size_t nL = (size_t)h->n * h->L;
-  HIP_TRY(launch_mb64_init(static_cast<const double*>(h->d_U), h->d_mb64, nL, st));
-  HIP_TRY(launch_adj64(static_cast<const double*>(h->d_tables), static_cast<double*>(h->d_phi), h->d_mb64, seg, nullptr,
-                       adjoint_grid(h, false), nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, h->d_slots, h->L,
-                       h->m, h->d_err, h->spin_limit, st));
-  HIP_TRY(launch_mb64_fini(static_cast<double*>(h->d_U), h->d_mb64, nL, st));
+  if (h->solo(false)) {
+    HIP_TRY(launch_solo<double>(solo_args<double>(h, nullptr), h->max_step, seg, st));
+  } else {
+    HIP_TRY(launch_mb64_init(static_cast<const double*>(h->d_U), h->d_mb64, nL, st));
+    HIP_TRY(launch_adj64(static_cast<const double*>(h->d_tables), static_cast<double*>(h->d_phi), h->d_mb64, seg, nullptr,
+                         adjoint_grid(h, false), nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, h->d_slots, h->L,
+                         h->m, h->d_err, h->spin_limit, st));
+    HIP_TRY(launch_mb64_fini(static_cast<double*>(h->d_U), h->d_mb64, nL, st));
+  }
   const int rc = sync_and_check(h);
   if (rc == MPLPXX_OK) h->iterations += seg;
   return rc;
@@ -1172,7 +1192,7 @@ int mplpxx_set_option(mplpxx_solver* h, int32_t key, int64_t value) {
     }
     case MPLPXX_OPT_SPIN_LIMIT:
       if (value < 0) return fail(MPLPXX_EINVAL, "spin limit must be >= 0");
-      h->spin_limit = value ? value : (1ll << 22);
+      h->spin_limit = value ? value : mplpxx_solver::kSpinDefault;
       return MPLPXX_OK;
     case MPLPXX_OPT_PROFILE:
       h->profile = value != 0;
