@@ -361,7 +361,8 @@ int mplpxx_set_option(mplpxx_solver* h, int32_t key, int64_t value);
 #define MPLPXX_INFO_ITERATIONS 9 /* iterations run since create / set_state */
 #define MPLPXX_INFO_WALLCLOCK_KHZ 10 /* device wall-clock rate of the timestamps */
 #define MPLPXX_INFO_ADJOINT_BYTES 11 /* device bytes held for the adjoint after mplpxx_adjoint_forward
-                                        (checkpoints, argmin records, adjoint buffers; for an FP32 handle
+                                        (checkpoints, argmin records, adjoint buffers, mailbox words without
+                                        the padding of their rows; for an FP32 handle
                                         differentiating its FP64 twin, also the twin's costs and state) */
 int mplpxx_get_info(mplpxx_solver* h, int32_t key, int64_t* value);
 
@@ -403,7 +404,8 @@ int mplpxx_adjoint_forward(mplpxx_solver* h, int32_t K, int32_t every, double* l
  * the recorded minimizers (recomputing each segment from its checkpoint).
  * FP64 runs with L <= 64 (an FP64 handle, or the FP64 run of an FP32
  * handle) use persistent kernels unless MPLPXX_OPT_ENGINE = 1: one launch
- * reverses a segment while it recomputes the previous one, the node values
+ * reverses a segment while it recomputes an earlier one (the forward keeps the
+ * records of the last two), the node values
  * and their adjoints passing between workgroups through tagged mailbox
  * words; otherwise one launch per matching.  Both give the same bits.
  * Output:

@@ -39,7 +39,7 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-Wno-unused-comman
 # reductions skip the quieting of their operands and fold into DPP forms;
 # on non-NaN operands the results are bitwise the same.
 EXTRA = {"handshake.hip": ["-fno-honor-nans"], "batch.hip": ["-fno-honor-nans"], "rules.hip": ["-fno-honor-nans"],
-         "solo.hip": ["-fno-honor-nans"]}
+         "solo.hip": ["-fno-honor-nans"], "adjoint.hip": ["-fno-honor-nans"]}
 
 
 def _compile(src: str, build_dir: str = BUILD, defines=()) -> str:

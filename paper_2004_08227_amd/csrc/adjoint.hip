@@ -32,6 +32,8 @@
 #include <type_traits>
 
 #include "device_common.h"
+#include "host_util.h"
+#include "mailbox64.h"
 
 namespace mplpxx {
 
@@ -256,338 +258,109 @@ hipError_t launch_adj_seed(const T* U, const T* Ulo, int n, int L, T* Ub, double
 
 // ---------------------------------------------------------------------------
 // Persistent FP64 adjoint (tiles up to 64 labels): one launch per segment of
-// the checkpointed run for the recomputation with records, one for its
-// reverse, instead of one launch per matching.
-//
-// Mailboxes.  A node's FP64 values (the unaries in the forward, their
-// adjoints in the reverse) travel between workgroups as two 64-bit words per
-// label, mb[node][label][h]: bits 0..31 hold the low (h = 0) or high (h = 1)
-// half of the double, bits 32..63 the number of updates the node has had in
-// this launch.  Each word is written and read with one device-scope atomic
-// access, so a consumer that sees the version it waits for in both words of
-// every label holds the values of that version: no flag, no fence.  (The
-// FP32 engines pack value and version into one word the same way.)
-//
-// Slots are owned statically as in the other persistent engines: workgroup w
-// runs slots w, w + G, ... in schedule order every iteration (the reverse in
-// the opposite order), so an edge's messages, records and adjoints never
-// leave one workgroup, and every wait is for an update earlier in the
-// (forward or reverse) order: the workgroup holding the earliest unfinished
-// one never waits.  Two sync waves poll the step's two nodes and deliver
-// them to LDS (double buffered), as in the FP32 mailbox engine.
+// the checkpointed run, whose workgroups reverse the segment and, beside it,
+// recompute an earlier one with records where the forward kept none, instead
+// of one launch per matching.  The forward role and the mailboxes are in
+// mailbox64.h; the reverse runs the same slots in the opposite order, its node
+// adjoints in a second set of mailboxes.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void mb64_put(unsigned long long* row, int s, double x, unsigned ver) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-  const unsigned long long tag = (unsigned long long)ver << 32;
-  mb_store(row + 2 * s, tag | (b & 0xffffffffull));
-  mb_store(row + 2 * s + 1, tag | (b >> 32));
-}
-
-// sync wave: poll the 2L words of one node until every one carries `want`,
-// then write their payloads to dst (2L 32-bit halves = L doubles)
-template <int LT>
-__device__ __forceinline__ bool mb64_gather(const unsigned long long* __restrict__ row, int L, unsigned want,
-                                            unsigned* dst, long long spin_limit, const int* err, unsigned* seen_out) {
-  const int lane = threadIdx.x & 63;
-  constexpr int PER = (2 * LT + 63) / 64;
-  bool have[PER];
-  unsigned long long val[PER];
-#pragma unroll
-  for (int k = 0; k < PER; ++k) have[k] = (lane + 64 * k) >= 2 * L;
-  long long spins = 0;
-  for (;;) {
-    bool all = true;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      if (!have[k]) {
-        const unsigned long long w = mb_load(row + lane + 64 * k);
-        if ((unsigned)(w >> 32) == want) {
-          have[k] = true;
-          val[k] = w;
-        } else {
-          all = false;
-        }
-      }
-    }
-    if (__all(all)) break;
-    if (++spins > spin_limit || ((spins & 255) == 0 && ld_dev(err) != 0)) {
-      unsigned seen = want;
-#pragma unroll
-      for (int k = 0; k < PER; ++k)
-        if (!have[k]) seen = (unsigned)(mb_load(row + lane + 64 * k) >> 32);
-      for (int o = 32; o >= 1; o >>= 1) seen = min(seen, (unsigned)__shfl_xor((int)seen, o, 64));
-      *seen_out = seen;
-      return false;
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < PER; ++k)
-    if (lane + 64 * k < 2 * L) dst[lane + 64 * k] = (unsigned)val[k];
-  return true;
-}
-
-__global__ void k_mb64_init(const double* __restrict__ x, unsigned long long* __restrict__ mb, size_t count) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < count; i += (size_t)gridDim.x * blockDim.x) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(x[i]);
-    mb[2 * i] = b & 0xffffffffull;
-    mb[2 * i + 1] = b >> 32;
+__global__ void __launch_bounds__(64) k_mb64_init(const double* __restrict__ x, unsigned long long* __restrict__ mb,
+                                                  int L) {
+  const size_t u = blockIdx.x;
+  for (int s = threadIdx.x; s < L; s += 64) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(x[u * L + s]);
+    unsigned long long* w = mb + u * mb64_row_words(L) + 2 * s;
+    w[0] = b & 0xffffffffull;
+    w[1] = b >> 32;
   }
 }
-__global__ void k_mb64_fini(double* __restrict__ x, const unsigned long long* __restrict__ mb, size_t count) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < count; i += (size_t)gridDim.x * blockDim.x)
-    x[i] = __longlong_as_double((long long)((mb[2 * i] & 0xffffffffull) | (mb[2 * i + 1] << 32)));
-}
-
-constexpr int kF64NT = 256;  // compute threads of the FP64 mailbox forward
-
-template <int LT> struct SmemF64 {
-  double hu[2][LT];
-  double hv[2][LT];
-  double red[kF64NT / 64][LT];
-  int redi[kF64NT / 64][LT];
-  int abort_flag;
-};
-
-// Forward of `iters` iterations (FP64): the unaries in the mailboxes, the
-// messages in phi (slot order).  REC: also the argmins of every update,
-// rec[it][slot][0..L) = t1, [L..2L) = s2, [2L..3L) = t3, lowest index on
-// ties, as the per-matching recording kernel gives them.  Every value is
-// the same IEEE result as in the other FP64 kernels (one add per entry,
-// exact minima, the same a_u, a_v), so the runs agree bit for bit.
-struct Fwd64Args {
-  const double* tables;
-  double* phi;
-  unsigned long long* mb;
-  const SlotInfo* slots;
-  int L, m, iters;
-  unsigned char* rec;   // argmin records, or null (plain forward)
-  int* err;
-  long long spin_limit;
-  int grid;             // workgroups of this role
-};
-template <int LT, bool REC>
-__device__ __forceinline__ void fwd64_role(const Fwd64Args& a, int first, int G, SmemF64<LT>& sm) {
-  const double* __restrict__ tables = a.tables;
-  double* __restrict__ phi = a.phi;
-  unsigned long long* __restrict__ mb = a.mb;
-  const SlotInfo* __restrict__ slots = a.slots;
-  unsigned char* __restrict__ rec = a.rec;
-  const int L = a.L, m = a.m, iters = a.iters;
-  int* err = a.err;
-  const long long spin_limit = a.spin_limit;
-  constexpr int NT = kF64NT;
-  using S = TileShape<double, LT, NT>;
-  const int tid = threadIdx.x;
-  const int owned = (m - first + G - 1) / G;
-  const int total = owned * iters;
-  const size_t rec_it = (size_t)m * 3 * L;
-  if (tid >= NT) {
-    // ---- sync waves: wait for the step's two nodes ----
-    const bool is_u = tid < NT + 64;
-    int parity = 0, it = 0, j = 0;
-    SlotInfo si = ld_const(slots + first);
-    for (int q = 0; q < total; ++q) {
-      const int slot = first + j * G;
-      // metadata of the next owned slot, off the dependency chain
-      const int nxt = uni(j + 1 == owned ? first : slot + G);
-      const SlotInfo si_next = ld_const(slots + nxt);
-      const int node = is_u ? si.u : si.v;
-      const unsigned want = (unsigned)it * (unsigned)(is_u ? si.deg_u : si.deg_v) + (unsigned)(is_u ? si.pos_u : si.pos_v);
-      unsigned seen = 0;
-      unsigned* dst = reinterpret_cast<unsigned*>(is_u ? sm.hu[parity] : sm.hv[parity]);
-      if (!mb64_gather<LT>(mb + (size_t)node * 2 * L, L, want, dst, spin_limit, err, &seen)) {
-        if ((tid & 63) == 0) {
-          if (ld_dev(err) == 0 || seen != want) report_timeout(err, slot, node, want, seen);
-          sm.abort_flag = q + 1;
-        }
-      }
-      __syncthreads();  // the step's nodes are in LDS
-      __syncthreads();  // the compute waves' mid-step barrier
-      if (sm.abort_flag == q + 1) return;
-      si = si_next;
-      parity ^= 1;
-      if (++j == owned) { j = 0; ++it; }
-    }
-    return;
+// values back; trace_row: their minimum per node
+__global__ void __launch_bounds__(64) k_mb64_fini(double* __restrict__ x, const unsigned long long* __restrict__ mb,
+                                                  int L, double* __restrict__ trace_row) {
+  const size_t u = blockIdx.x;
+  double mn = __builtin_inf();
+  for (int s = threadIdx.x; s < L; s += 64) {
+    const unsigned long long* w = mb + u * mb64_row_words(L) + 2 * s;
+    const double v = __longlong_as_double((long long)((w[0] & 0xffffffffull) | (w[1] << 32)));
+    x[u * L + s] = v;
+    mn = vmin(mn, v);
   }
-  // ---- compute waves ----
-  const int rb = tid >> 4, cb = tid & 15, wave = tid >> 6, lane = tid & 63;
-  double x[S::BR][S::BC];
-  double pu[S::BR], pv[S::BC];
-  auto load_phi64 = [&](int slot) __attribute__((always_inline)) {
-    const double* ph = phi + (size_t)slot * 2 * L;
-#pragma unroll
-    for (int i = 0; i < S::BR; ++i) {
-      const int s = rb * S::BR + i;
-      pu[i] = s < L ? ph[s] : 0.0;
-    }
-#pragma unroll
-    for (int jj = 0; jj < S::BC; ++jj) {
-      const int t = cb * S::BC + jj;
-      pv[jj] = t < L ? ph[L + t] : 0.0;
-    }
-  };
-  load_tile<double, LT, NT>(tables + (size_t)first * L * L, L, x);
-  // (a workgroup that owns one slot reads back the messages it wrote at the
-  // previous step: after the next step's first barrier)
-  if (owned > 1) load_phi64(first);
-  int parity = 0, it = 0, j = 0;
-  SlotInfo si = ld_const(slots + first);
-  for (int q = 0; q < total; ++q) {
-    const int slot = first + j * G;
-    const int nxt_slot = uni(j + 1 == owned ? first : slot + G);
-    const SlotInfo si_next = ld_const(slots + nxt_slot);
-    __syncthreads();  // the step's nodes are in LDS
-    if (owned == 1) load_phi64(slot);
-    double au[S::BR], av[S::BC];
-#pragma unroll
-    for (int jj = 0; jj < S::BC; ++jj) {
-      const int t = cb * S::BC + jj;
-      av[jj] = t < L ? sm.hv[parity][t] - pv[jj] : 0.0;
-    }
-#pragma unroll
-    for (int i = 0; i < S::BR; ++i) {
-      const int s = rb * S::BR + i;
-      au[i] = s < L ? sm.hu[parity][s] - pu[i] : 0.0;
-    }
-    // pass 1: p(s) = min_t [th(s,t) + a_v(t)], t1 = its lowest argmin
-    double b[S::BR];
-    int t1[S::BR];
-#pragma unroll
-    for (int i = 0; i < S::BR; ++i) {
-      double mn = x[i][0] + av[0];
-      int arg = cb * S::BC;
-#pragma unroll
-      for (int jj = 1; jj < S::BC; ++jj) argmin_next(mn, arg, x[i][jj] + av[jj], cb * S::BC + jj);
-      row16_argmin(mn, arg);
-      const int s = rb * S::BR + i;
-      b[i] = s < L ? 0.5 * (au[i] - mn) : 0.0;
-      t1[i] = arg;
-    }
-    // pass 2: q(t) = min_s [th(s,t) + b(s)], s2 = its lowest argmin
-#pragma unroll
-    for (int jj = 0; jj < S::BC; ++jj) {
-      double mn = x[0][jj] + b[0];
-      int arg = rb * S::BR;
-#pragma unroll
-      for (int i = 1; i < S::BR; ++i) argmin_next(mn, arg, x[i][jj] + b[i], rb * S::BR + i);
-      col4_argmin(mn, arg);
-      if (lane < 16) {
-        sm.red[wave][cb * S::BC + jj] = mn;
-        sm.redi[wave][cb * S::BC + jj] = arg;
-      }
-    }
-    __syncthreads();  // mid-step barrier
-    if (sm.abort_flag == q + 1) return;
-    // waves hold ascending row ranges: merging them in order keeps the
-    // lowest argmin
-    double qv[S::BC];
-    int s2[S::BC];
-#pragma unroll
-    for (int jj = 0; jj < S::BC; ++jj) {
-      const int t = cb * S::BC + jj;
-      double mn = sm.red[0][t];
-      int arg = sm.redi[0][t];
-#pragma unroll
-      for (int w = 1; w < S::W; ++w) argmin_merge(mn, arg, sm.red[w][t], sm.redi[w][t]);
-      qv[jj] = t < L ? mn : 0.0;
-      s2[jj] = arg;
-    }
-    // pass 3: r(s) = min_t [th(s,t) - q(t)], t3 = its lowest argmin
-    double r[S::BR];
-    int t3[S::BR];
-#pragma unroll
-    for (int i = 0; i < S::BR; ++i) {
-      double mn = x[i][0] - qv[0];
-      int arg = cb * S::BC;
-#pragma unroll
-      for (int jj = 1; jj < S::BC; ++jj) argmin_next(mn, arg, x[i][jj] - qv[jj], cb * S::BC + jj);
-      row16_argmin(mn, arg);
-      r[i] = mn;
-      t3[i] = arg;
-    }
-    // push back: U_u = a_u + r, phi[0] = r (column block 0), U_v = a_v + q,
-    // phi[1] = q (row block 0)
-    double* ph = phi + (size_t)slot * 2 * L;
-    unsigned char* rc = rec + (size_t)it * rec_it + (size_t)slot * 3 * L;
-    if (cb == 0) {
-      const unsigned ver = (unsigned)it * (unsigned)si.deg_u + (unsigned)si.pos_u + 1u;
-#pragma unroll
-      for (int i = 0; i < S::BR; ++i) {
-        const int s = rb * S::BR + i;
-        if (s < L) {
-          mb64_put(mb + (size_t)si.u * 2 * L, s, au[i] + r[i], ver);
-          ph[s] = r[i];
-          if (REC) {
-            rc[s] = (unsigned char)t1[i];
-            rc[2 * L + s] = (unsigned char)t3[i];
-          }
-        }
-      }
-    }
-    if (rb == 0) {
-      const unsigned ver = (unsigned)it * (unsigned)si.deg_v + (unsigned)si.pos_v + 1u;
-#pragma unroll
-      for (int jj = 0; jj < S::BC; ++jj) {
-        const int t = cb * S::BC + jj;
-        if (t < L) {
-          mb64_put(mb + (size_t)si.v * 2 * L, t, av[jj] + qv[jj], ver);
-          ph[L + t] = qv[jj];
-          if (REC) rc[L + t] = (unsigned char)s2[jj];
-        }
-      }
-    }
-    si = si_next;
-    parity ^= 1;
-    if (++j == owned) { j = 0; ++it; }
-    if (q + 1 < total && owned > 1) {
-      load_tile<double, LT, NT>(tables + (size_t)nxt_slot * L * L, L, x);
-      load_phi64(nxt_slot);
-    }
+  if (trace_row) {
+    mn = row16_min(mn);
+    mn = pair16_min(mn, mn);
+    mn = join32_min(mn, mn);
+    if (threadIdx.x == 0) trace_row[u] = mn;
   }
 }
 
 template <int LT> struct SmemR64 {
+  using Mask = typename std::conditional<LT <= 32, unsigned, unsigned long long>::type;
   double ubu[2][LT];
   double ubv[2][LT];
+  Mask mask[3][LT];  // labels whose record names this label
   int abort_flag;
 };
-// the double held by lane k, as a wave-uniform value
-__device__ __forceinline__ double lane_double(double x, int k) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-  const unsigned lo = __builtin_amdgcn_readlane((unsigned)b, k);
-  const unsigned hi = __builtin_amdgcn_readlane((unsigned)(b >> 32), k);
-  return dbl_of(lo, hi);
-}
+
+// Sums over the labels k with idx(k) = this lane's label, in ascending k: the
+// first kAhead source lanes are taken out of the mask before the step's values
+// arrive, the rest one by one.  (Records spread their indices: of 32 labels
+// three or four at most usually name the same one.)
+constexpr int kAhead = 4;
+template <typename Mask> struct ScatterSum {
+  int src[kAhead];
+  bool has[kAhead];
+  Mask rest;
+  __device__ __forceinline__ static int low(Mask m) {
+    return sizeof(Mask) == 4 ? __ffs((int)m) - 1 : __ffsll((unsigned long long)m) - 1;
+  }
+  __device__ __forceinline__ void prepare(Mask m) {
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      has[i] = m != 0;
+      src[i] = has[i] ? 4 * low(m) : 0;
+      m &= m - 1;
+    }
+    rest = m;
+  }
+  // acc +- x(k) for every k of the mask
+  template <bool MINUS> __device__ __forceinline__ double run(double acc, double x) const {
+    double y[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) y[i] = bperm(x, src[i]);
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) acc = has[i] ? (MINUS ? acc - y[i] : acc + y[i]) : acc;
+    Mask m = rest;
+    while (__any(m != 0)) {
+      const double z = bperm(x, m != 0 ? 4 * low(m) : 0);
+      acc = m != 0 ? (MINUS ? acc - z : acc + z) : acc;
+      m &= m - 1;
+    }
+    return acc;
+  }
+};
 
 // Reverse of `seg` recorded iterations (FP64, L <= 64): node adjoints in the
 // mailboxes (version = updates of the node already reversed in this
 // launch), message adjoints pb (slot order).  One compute wave, lane =
 // label; the arithmetic of every adjoint is that of the per-matching reverse
-// (same terms, same order), the sums over labels by wave-uniform values
-// read from the other lanes, with no LDS round trip.  The table adjoints are not accumulated here:
+// (same terms, same order).  A step's sums take only the labels whose records
+// name this one, found before the step's values arrive (all labels in turn,
+// with a compare each, took 2.5 us a matching at 32 labels; 1.28 us now, most
+// of it the handoff).  The table adjoints are not accumulated here:
 // each reverse step writes its three scatter vectors rb, q-bar and p-bar to
 // contrib[it][slot][3L] for k_thb_acc, which adds them in the per-matching
 // kernel's order.
-struct Rev64Args {
-  const SlotInfo* slots;
-  int L, m, seg;
-  const unsigned char* rec;
-  unsigned long long* mb;
-  double* pb;
-  double* contrib;
-  int* err;
-  long long spin_limit;
-  int grid;             // workgroups of this role (0: no reverse in the launch)
-};
 template <int LT>
-__device__ __forceinline__ void rev64_role(const Rev64Args& a, int first, int G, SmemR64<LT>& sm) {
+__device__ __forceinline__ void rev64_role(const Rev64Args& a, int first_in, int G_in, SmemR64<LT>& sm) {
+  using Mask = typename SmemR64<LT>::Mask;
   const SlotInfo* __restrict__ slots = a.slots;
   const unsigned char* __restrict__ rec = a.rec;
   unsigned long long* __restrict__ mb = a.mb;
   double* __restrict__ pb = a.pb;
   double* __restrict__ contrib = a.contrib;
-  const int L = a.L, m = a.m, seg = a.seg;
+  const int L = uni(a.L), m = uni(a.m), seg = uni(a.seg);
+  const int mbs = mb64_row_words(L);
+  const int first = uni(first_in), G = uni(G_in);
   int* err = a.err;
   const long long spin_limit = a.spin_limit;
   const int tid = threadIdx.x;
@@ -617,7 +390,7 @@ __device__ __forceinline__ void rev64_role(const Rev64Args& a, int first, int G,
       const unsigned want = (unsigned)done * (unsigned)deg + (unsigned)(deg - 1 - pos);
       unsigned seen = 0;
       unsigned* dst = reinterpret_cast<unsigned*>(is_u ? sm.ubu[parity] : sm.ubv[parity]);
-      if (!mb64_gather<LT>(mb + (size_t)node * 2 * L, L, want, dst, spin_limit, err, &seen)) {
+      if (!mb64_gather<LT>(mb + (size_t)node * mbs, L, want, dst, spin_limit, err, &seen)) {
         if ((tid & 63) == 0) {
           if (ld_dev(err) == 0 || seen != want) report_timeout(err, slot, node, want, seen);
           sm.abort_flag = q + 1;
@@ -646,52 +419,46 @@ __device__ __forceinline__ void rev64_role(const Rev64Args& a, int first, int G,
     p1 = pb[(size_t)slot * 2 * L + L + sc];
   };
   int parity = 0, done = 0, j = owned - 1;
-  if (owned > 1) load_step(first + j * G, seg - 1);
+  load_step(first + j * G, seg - 1);
   SlotInfo si = ld_const(slots + first + j * G);
   for (int q = 0; q < total; ++q) {
     const int slot = first + j * G;
     const int it = seg - 1 - done;
     const int nxt_slot = uni(j == 0 ? first + (owned - 1) * G : slot - G);
     const SlotInfo si_next = ld_const(slots + nxt_slot);
+    // before the step's values are there: who adds to this lane's label
+    // (labels past L take no part)
+    ScatterSum<Mask> sum3, sum2, sum1;
+    if (s < LT) sm.mask[0][s] = sm.mask[1][s] = sm.mask[2][s] = 0;
+    wave_sync();
+    if (real) {
+      const Mask bit = (Mask)1 << s;
+      atomicOr(&sm.mask[0][t3], bit);
+      atomicOr(&sm.mask[1][s2], bit);
+      atomicOr(&sm.mask[2][t1], bit);
+    }
+    wave_sync();
+    sum3.prepare(real ? sm.mask[0][s] : 0);
+    sum2.prepare(real ? sm.mask[1][s] : 0);
+    sum1.prepare(real ? sm.mask[2][s] : 0);
+    const double b0 = p0, b1 = p1;
     __syncthreads();  // the step's node adjoints are in LDS
     if (sm.abort_flag == q + 1) return;
-    if (owned == 1) load_step(slot, it);
     const double ubu = sm.ubu[parity][sc], ubv = sm.ubv[parity][sc];
-    // Each sum over the labels k with idx(k) = this lane's label takes the
-    // terms in ascending k, as wave-uniform values read from lane k (labels
-    // k >= L carry index -1 and never match).
-    const int t3k = real ? t3 : -1, s2k = real ? s2 : -1, t1k = real ? t1 : -1;
-    // r = th(s, t3) - q(t3): rb = pb0 + Ub_u
-    const double rb = real ? p0 + ubu : 0.0;
-    double qb = p1 + ubv;
-#pragma unroll
-    for (int k = 0; k < LT; ++k) {
-      const double y = qb - lane_double(rb, k);
-      qb = __builtin_amdgcn_readlane(t3k, k) == s ? y : qb;
-    }
+    // r = th(s, t3) - q(t3): rb = pb0 + Ub_u, q-bar(t) -= sum of rb(s), t3(s) = t
+    const double rb = b0 + ubu;
+    const double qb = sum3.template run<true>(b1 + ubv, rb);
     // q = th(s2, t) + b(s2)
-    const double qbk = real ? qb : 0.0;
-    double bb = 0.0;
-#pragma unroll
-    for (int k = 0; k < LT; ++k) {
-      const double y = bb + lane_double(qbk, k);
-      bb = __builtin_amdgcn_readlane(s2k, k) == s ? y : bb;
-    }
+    const double bb = sum2.template run<false>(0.0, qb);
     // b = (a_u - p) / 2
     const double abu = ubu + 0.5 * bb;
     const double pbv = -0.5 * bb;
     // p = th(s, t1) + a_v(t1)
-    const double pbk = real ? pbv : 0.0;
-    double abv = ubv;
-#pragma unroll
-    for (int k = 0; k < LT; ++k) {
-      const double y = abv + lane_double(pbk, k);
-      abv = __builtin_amdgcn_readlane(t1k, k) == s ? y : abv;
-    }
+    const double abv = sum1.template run<false>(ubv, pbv);
     // a_u = U_u - phi0, a_v = U_v - phi1
     if (real) {
-      mb64_put(mb + (size_t)si.u * 2 * L, s, abu, (unsigned)done * (unsigned)si.deg_u + (unsigned)(si.deg_u - si.pos_u));
-      mb64_put(mb + (size_t)si.v * 2 * L, s, abv, (unsigned)done * (unsigned)si.deg_v + (unsigned)(si.deg_v - si.pos_v));
+      mb64_put(mb + (size_t)si.u * mbs + 2 * s, abu, (unsigned)done * (unsigned)si.deg_u + (unsigned)(si.deg_u - si.pos_u));
+      mb64_put(mb + (size_t)si.v * mbs + 2 * s, abv, (unsigned)done * (unsigned)si.deg_v + (unsigned)(si.deg_v - si.pos_v));
       pb[(size_t)slot * 2 * L + s] = -abu;
       pb[(size_t)slot * 2 * L + L + s] = -abv;
       double* ct = contrib + ((size_t)it * m + slot) * 3 * L;
@@ -702,21 +469,20 @@ __device__ __forceinline__ void rev64_role(const Rev64Args& a, int first, int G,
     si = si_next;
     parity ^= 1;
     if (--j < 0) { j = owned - 1; ++done; }
-    if (q + 1 < total && owned > 1) load_step(nxt_slot, seg - 1 - done);
+    // (each lane reads back only message adjoints that it stored itself)
+    if (q + 1 < total) load_step(nxt_slot, seg - 1 - done);
   }
 }
 
-// One launch of the persistent FP64 adjoint: workgroups [0, r.grid) run the
-// reverse of one recorded segment, the others the forward of `f.iters`
-// iterations (recording or not).  In the backward the two roles work on
-// different segments (the reverse of segment c beside the recomputation of
-// segment c - 1, which needs only its checkpoint): they share no data, so
-// they run side by side on the device.  Each workgroup has kF64NT + 128
-// threads; the reverse uses wave 0 and the two sync waves.
-template <int LT, bool REC>
+// Workgroups [0, r.grid) run the reverse of one recorded segment, the others
+// the recording forward of `f.iters` iterations of another: they share no
+// data, so they run side by side on the device.  Each workgroup has kF64NT +
+// 128 threads; the reverse uses wave 0 and the two sync waves.
+template <int LT, bool PHI_LDS>
 __global__ void __launch_bounds__(kF64NT + 128) k_adj64(Fwd64Args f, Rev64Args r) {
   __shared__ SmemF64<LT> smf;
   __shared__ SmemR64<LT> smr;
+  extern __shared__ __align__(16) double phi_lds64[];
   const int b = blockIdx.x;
   if (b < r.grid) {
     if (b >= r.m || r.seg <= 0) return;
@@ -728,8 +494,17 @@ __global__ void __launch_bounds__(kF64NT + 128) k_adj64(Fwd64Args f, Rev64Args r
     if (first >= f.m || f.iters <= 0) return;
     if (threadIdx.x == 0) smf.abort_flag = 0;
     __syncthreads();
-    fwd64_role<LT, REC>(f, first, f.grid, smf);
+    fwd64_role<LT, PHI_LDS, true, false>(f, first, f.grid, smf, phi_lds64);
   }
+}
+template <int LT, bool PHI_LDS, bool TRACE>
+__global__ void __launch_bounds__(kF64NT + 128) k_fwd64(Fwd64Args f) {
+  __shared__ SmemF64<LT> smf;
+  extern __shared__ __align__(16) double phi_lds64[];
+  if ((int)blockIdx.x >= f.m) return;
+  if (threadIdx.x == 0) smf.abort_flag = 0;
+  __syncthreads();
+  fwd64_role<LT, PHI_LDS, false, TRACE>(f, blockIdx.x, f.grid, smf, phi_lds64);
 }
 
 // Table adjoints of one segment: thb[slot] += the reverse steps' scatters,
@@ -760,48 +535,60 @@ __global__ void __launch_bounds__(256) k_thb_acc(double* __restrict__ thb, const
   for (int k = tid; k < L * L; k += 256) gt[k] = g[k];
 }
 
-hipError_t launch_mb64_init(const double* x, unsigned long long* mb, size_t count, hipStream_t st) {
-  const size_t blocks = std::min<size_t>(1024, (count + 255) / 256);
-  if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_mb64_init, dim3((unsigned)blocks), dim3(256), 0, st, x, mb, count);
+hipError_t launch_mb64_init(const double* x, unsigned long long* mb, int n, int L, hipStream_t st) {
+  hipLaunchKernelGGL(k_mb64_init, dim3(n), dim3(64), 0, st, x, mb, L);
   return hipGetLastError();
 }
-hipError_t launch_mb64_fini(double* x, const unsigned long long* mb, size_t count, hipStream_t st) {
-  const size_t blocks = std::min<size_t>(1024, (count + 255) / 256);
-  if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_mb64_fini, dim3((unsigned)blocks), dim3(256), 0, st, x, mb, count);
+hipError_t launch_mb64_fini(double* x, const unsigned long long* mb, int n, int L, double* trace_row, hipStream_t st) {
+  hipLaunchKernelGGL(k_mb64_fini, dim3(n), dim3(64), 0, st, x, mb, L, trace_row);
   return hipGetLastError();
+}
+
+// dynamic LDS for the messages of a forward workgroup's slots, 0 where they
+// do not fit (they then stay in memory)
+static size_t fwd64_lds(const Fwd64Args& f) {
+  if (f.grid <= 0) return 0;
+  const size_t bytes = ((size_t)f.m + f.grid - 1) / f.grid * 2 * f.L * sizeof(double);
+  return bytes <= kPhiLdsBudget ? bytes : 0;
+}
+static hipError_t coop(const void* fn, int grid, void** args, size_t lds, hipStream_t st) {
+  const hipError_t e = hipLaunchCooperativeKernel(fn, dim3(grid), dim3(kF64NT + 128), args, lds, st);
+  if (e != hipSuccess) (void)hipGetLastError();  // (a refused launch: not left for a later launch check)
+  return e;
+}
+
+template <int LT> static hipError_t fwd64_one(const Fwd64Args& f, hipStream_t st) {
+  void* args[] = {(void*)&f};
+  const size_t lds = fwd64_lds(f);
+  const void* fn = lds ? (f.trace ? (const void*)k_fwd64<LT, true, true> : (const void*)k_fwd64<LT, true, false>)
+                       : (f.trace ? (const void*)k_fwd64<LT, false, true> : (const void*)k_fwd64<LT, false, false>);
+  return coop(fn, f.grid, args, lds, st);
+}
+hipError_t launch_fwd64(const Fwd64Args& f, hipStream_t st) {
+  if (f.m <= 0 || f.iters <= 0 || f.grid <= 0) return hipSuccess;
+  if (f.L <= 16) return fwd64_one<16>(f, st);
+  if (f.L <= 32) return fwd64_one<32>(f, st);
+  if (f.L <= 64) return fwd64_one<64>(f, st);
+  return hipErrorInvalidValue;
 }
 
 template <int LT>
 static hipError_t adj64_one(const Fwd64Args& f, const Rev64Args& r, double* thb, hipStream_t st) {
   void* args[] = {(void*)&f, (void*)&r};
-  const void* fn = f.rec ? (const void*)k_adj64<LT, true> : (const void*)k_adj64<LT, false>;
+  const size_t lds = fwd64_lds(f);
+  const void* fn = lds ? (const void*)k_adj64<LT, true> : (const void*)k_adj64<LT, false>;
   const int grid = r.grid + f.grid;
   if (grid <= 0) return hipSuccess;
-  hipError_t e = hipLaunchCooperativeKernel(fn, dim3(grid), dim3(kF64NT + 128), args, 0, st);
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    return e;
-  }
+  const hipError_t e = coop(fn, grid, args, lds, st);
+  if (e != hipSuccess) return e;
   if (r.grid > 0 && r.seg > 0 && r.m > 0) {
     hipLaunchKernelGGL(k_thb_acc<LT>, dim3(r.m), dim3(256), 0, st, thb, r.rec, r.contrib, r.L, r.m, r.seg);
     return hipGetLastError();
   }
   return hipSuccess;
 }
-
-// One launch: the reverse of `seg` recorded iterations (rev_grid
-// workgroups; 0: none) next to the forward of `iters` iterations (fwd_grid
-// workgroups; iters 0: none; fwd_rec: record the argmins there), then the
-// reverse segment's table adjoints.
-hipError_t launch_adj64(const double* tables, double* phi, unsigned long long* mb_fwd, int iters, unsigned char* fwd_rec,
-                        int fwd_grid, const unsigned char* rev_rec, unsigned long long* mb_rev, double* pb,
-                        double* contrib, double* thb, int seg, int rev_grid, const SlotInfo* slots, int L, int m,
-                        int* err, long long spin_limit, hipStream_t st) {
-  if (m <= 0) return hipSuccess;
-  Fwd64Args f{tables, phi, mb_fwd, slots, L, m, iters, fwd_rec, err, spin_limit, iters > 0 ? fwd_grid : 0};
-  Rev64Args r{slots, L, m, seg, rev_rec, mb_rev, pb, contrib, err, spin_limit, seg > 0 ? rev_grid : 0};
+hipError_t launch_adj64(const Fwd64Args& f, const Rev64Args& r, double* thb, hipStream_t st) {
+  const int L = f.grid > 0 ? f.L : r.L;
   if (L <= 16) return adj64_one<16>(f, r, thb, st);
   if (L <= 32) return adj64_one<32>(f, r, thb, st);
   if (L <= 64) return adj64_one<64>(f, r, thb, st);

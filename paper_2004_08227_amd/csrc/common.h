@@ -142,18 +142,43 @@ hipError_t launch_adj_step(const SlotInfo* slots, int L, int slot_begin, int cou
                            T* pb, T* thb, hipStream_t st);
 template <typename T>
 hipError_t launch_adj_seed(const T* U, const T* Ulo, int n, int L, T* Ub, double* node_min, hipStream_t st);
-// persistent FP64 adjoint, L <= 64 (adjoint.hip): values in mailboxes of two
-// tagged 64-bit words per label (mb[n][L][2]); rec = nullptr: plain forward
-hipError_t launch_mb64_init(const double* x, unsigned long long* mb, size_t count, hipStream_t st);
-hipError_t launch_mb64_fini(double* x, const unsigned long long* mb, size_t count, hipStream_t st);
-// one launch: the reverse of `seg` recorded iterations (rev_grid workgroups,
-// 0 for none) beside the forward of `iters` iterations (fwd_grid
-// workgroups; fwd_rec: argmin records, or null), then the reverse
-// segment's table adjoints
-hipError_t launch_adj64(const double* tables, double* phi, unsigned long long* mb_fwd, int iters, unsigned char* fwd_rec,
-                        int fwd_grid, const unsigned char* rev_rec, unsigned long long* mb_rev, double* pb,
-                        double* contrib, double* thb, int seg, int rev_grid, const SlotInfo* slots, int L, int m,
-                        int* err, long long spin_limit, hipStream_t st);
+// FP64 mailbox engine, L <= 64 (mailbox64.h, adjoint.hip): values in mailboxes
+// of two tagged 64-bit words per label, a node's row filling whole cache lines
+__host__ __device__ constexpr int mb64_row_words(int L) { return (2 * L + 15) / 16 * 16; }
+struct Fwd64Args {
+  const double* tables;
+  double* phi;
+  unsigned long long* mb;    // [n][mb64_row_words(L)]
+  const SlotInfo* slots;
+  int L, m, n, iters;
+  unsigned char* rec;        // [iters][m][3][L] argmin records, or null
+  double* trace;             // [iters][n] node minima (the last row by launch_mb64_fini), or null
+  unsigned long long* sink;  // [kF64Sink per workgroup of the launch] scratch words
+  int* err;
+  long long spin_limit;
+  int grid;                  // workgroups of this role (0: none)
+};
+// Reverse of `seg` recorded iterations
+struct Rev64Args {
+  const SlotInfo* slots;
+  int L, m, seg;
+  const unsigned char* rec;
+  unsigned long long* mb;    // node adjoints
+  double* pb;                // [m][2][L] message adjoints
+  double* contrib;           // [seg][m][3][L] scatter vectors for the table adjoints
+  int* err;
+  long long spin_limit;
+  int grid;                  // workgroups of this role (0: none)
+};
+constexpr int kF64Sink = 256;
+hipError_t launch_mb64_init(const double* x, unsigned long long* mb, int n, int L, hipStream_t st);
+hipError_t launch_mb64_fini(double* x, const unsigned long long* mb, int n, int L, double* trace_row, hipStream_t st);
+// the forward alone (no records; `trace` if given)
+hipError_t launch_fwd64(const Fwd64Args& f, hipStream_t st);
+// one launch: the reverse of a recorded segment beside the recording forward
+// of another (either may have no workgroups), then the reversed segment's
+// table adjoints
+hipError_t launch_adj64(const Fwd64Args& f, const Rev64Args& r, double* thb, hipStream_t st);
 
 int max_blocks_per_cu_mb(int LT, int NT);
 // the (M) and (U) updates on the per-matching engine (rules.hip); rule 1 = M, 2 = U

@@ -164,6 +164,27 @@ __device__ __forceinline__ void col4_argmin(double& v, int& i) {
   }
 }
 
+// the value of x in lane addr / 4
+template <typename T> __device__ __forceinline__ T bperm(T x, int addr);
+template <> __device__ __forceinline__ float bperm<float>(float x, int addr) {
+  return __int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(x)));
+}
+template <> __device__ __forceinline__ double bperm<double>(double x, int addr) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_ds_bpermute(addr, (int)(unsigned)b);
+  const unsigned hi = (unsigned)__builtin_amdgcn_ds_bpermute(addr, (int)(unsigned)(b >> 32));
+  return dbl_of(lo, hi);
+}
+
+// Stops the compiler from moving memory operations across this point (LDS
+// exchanges between the lanes of one wave need no hardware wait: a wave's
+// LDS operations execute in order).
+__device__ __forceinline__ void wave_sync() {
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_wave_barrier();
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
 // ---------------------------------------------------------------------------
 // Compensated FP32 unaries.  U_u = theta_u + (sum of the messages into u) is
 // a running sum: every update of an incident edge replaces one message,

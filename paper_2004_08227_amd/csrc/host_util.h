@@ -76,11 +76,11 @@ inline bool known_cost_kind(int kind) {
   return kind == MPLPXX_COST_POTTS || kind == MPLPXX_COST_TRUNC_LINEAR || kind == MPLPXX_COST_TRUNC_QUAD;
 }
 
-// FP32 mailbox engine: messages of a workgroup's slots kept in LDS up to this
+// Mailbox engines: messages of a workgroup's slots kept in LDS up to this
 // size
 constexpr size_t kPhiLdsBudget = 96 * 1024;
 
-// Workgroups of the FP32 mailbox engine.
+// Workgroups of the mailbox engines.
 //  * A matching with more edges than there are compute units: one workgroup
 //    per edge of it as far as they fit (`per_cu` on each compute unit), so a
 //    workgroup runs about one update per matching instead of several one
@@ -97,9 +97,9 @@ constexpr size_t kPhiLdsBudget = 96 * 1024;
 //    More where the messages of a workgroup's slots would not fit in LDS
 //    otherwise.
 template <typename F>
-inline int mb_default_grid(int max_step, int num_cus, long long m, int L, const F& per_cu) {
+inline int mb_default_grid(int max_step, int num_cus, long long m, int L, const F& per_cu, size_t esz = sizeof(float)) {
   if (max_step > num_cus) return std::max(num_cus, std::min(max_step, per_cu() * num_cus));
-  const long long slots_in_lds = (long long)(kPhiLdsBudget / (2 * sizeof(float) * L));
+  const long long slots_in_lds = (long long)(kPhiLdsBudget / (2 * esz * L));
   const long long fit = (m + slots_in_lds - 1) / slots_in_lds;
   return (int)std::min<long long>(num_cus, std::max<long long>(2ll * max_step, fit));
 }

@@ -20,8 +20,8 @@ inline size_t solo_lds_bytes(int n, int L, int m, int S, size_t esz) {
   return ((size_t)n * L * (esz == 4 ? 2 : 1) + (size_t)m * 2 * L) * esz + ((size_t)m + S + 1) * sizeof(int);
 }
 constexpr size_t kSoloLds = 144 * 1024;
-// waves a workgroup can have (registers: the 32-label tile needs 168)
-constexpr int solo_max_waves(int LT) { return LT == 32 ? 12 : 16; }
+// waves a workgroup can have (more registers for the 32-label tile)
+constexpr int solo_max_waves(int LT) { return LT == 32 ? 4 : 16; }
 
 // Whether the model runs on one workgroup: its state fits in LDS, and one wave
 // per edge of its largest matching gives a shorter step than the mailbox
@@ -33,16 +33,16 @@ constexpr int solo_max_waves(int LT) { return LT == 32 ? 12 : 16; }
 //   FP32, L = 32  0.87 / 1.16   1.73 / 1.14
 //   FP32 traces, L = 8   0.67 / 1.29   0.82 / 1.27   1.07 / 1.21
 //   FP32 traces, L = 16  0.86 / 1.23   1.20 / 1.37   1.65 / 1.34
-//   FP64, L = 8   0.42 / 1.75   0.55 / 1.78   0.75 / 1.72
-//   FP64, L = 16  0.60 / 1.85   0.83 / 1.88   1.27 / 1.97 (14 edges)
-//   FP64, L = 32  1.15 / 3.12   1.92 / 3.36   2.45 / 3.27 (12 edges)
-// (FP64 traces a little above the FP64 lines, against 2.4 to 4.2).
+//   FP64, L = 8   0.42 / 1.13   0.55 / 1.13   0.75 / 1.13
+//   FP64, L = 16  0.60 / 1.14   0.83 / 1.14   1.06 / 1.14 (12 edges)  1.27
+//   FP64, L = 32  1.15 / 1.41   1.47 / 1.41 (4 edges)   1.92 / 1.41
+//   FP64 traces, L = 16  0.73 / 1.15   0.98 / 1.15   1.47 / 1.15
+//   FP64 traces, L = 32  1.31 / 1.42   1.65 / 1.42 (4 edges)
 inline bool solo_fits(int n, int L, int m, int S, int max_step, size_t esz, bool trace) {
   if (m < 1 || n > 32767 || L > 32 || solo_lds_bytes(n, L, m, S, esz) > kSoloLds) return false;
-  if (esz == 8) return max_step <= solo_max_waves(L <= 8 ? 8 : L <= 16 ? 16 : 32);
   if (L <= 8) return max_step <= 16;
-  if (L <= 16) return max_step <= (trace ? 8 : 16);
-  return !trace && max_step <= 2;
+  if (L <= 16) return max_step <= (trace ? 8 : esz == 8 ? 12 : 16);
+  return max_step <= (esz == 8 ? (trace ? 2 : 3) : (trace ? 0 : 2));
 }
 
 // one workgroup of max_step waves (solo_fits holds)

@@ -31,16 +31,6 @@
 
 namespace mplpxx {
 
-template <typename T> __device__ __forceinline__ T bperm(T x, int addr);
-template <> __device__ __forceinline__ float bperm<float>(float x, int addr) {
-  return __int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(x)));
-}
-template <> __device__ __forceinline__ double bperm<double>(double x, int addr) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-  const unsigned lo = (unsigned)__builtin_amdgcn_ds_bpermute(addr, (int)(unsigned)b);
-  const unsigned hi = (unsigned)__builtin_amdgcn_ds_bpermute(addr, (int)(unsigned)(b >> 32));
-  return dbl_of(lo, hi);
-}
 // the lower and the upper half wave's value of x, in the lanes of both
 __device__ __forceinline__ void halves(float x, float& lo, float& hi) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);

@@ -84,6 +84,7 @@ struct mplpxx_solver {
   int wallclock_khz = 0;
   // adjoint of K unrolled iterations
   int adj_K = 0, adj_every = 0, adj_nck = 0;
+  int adj_rec_from = 0;                   // segments from this one on have their records (persistent path)
   bool adj_ready = false;
   long long adj_iter_mark = -1;           // `iterations` right after the forward
   void* d_ck_U = nullptr;                 // [nck + 1][n][L] (last = final state)
@@ -97,6 +98,7 @@ struct mplpxx_solver {
   // the forward, then their adjoints), and the reverse steps' scatter
   // vectors [every][m][3][L]; d_rec then holds two segments of records
   unsigned long long* d_mb64 = nullptr;
+  unsigned long long* d_sink64 = nullptr;  // scratch words of the FP64 mailbox engine's workgroups
   double* d_contrib = nullptr;
   size_t adj_bytes = 0;                   // device bytes of the adjoint buffers above
   int* d_slot_of_edge = nullptr;          // [m]
@@ -195,7 +197,7 @@ void free_all(mplpxx_solver* h) {
   void* ptrs[] = {h->d_tables, h->d_phi, h->d_U, h->d_Ulo, h->d_ck_Ulo, h->d_unaries, h->d_slots, h->d_deg, h->d_ver, h->d_err,
                   h->d_node_ptr, h->d_inc, h->d_node_min, h->d_edge_min, h->d_scalar, h->d_labels,
                   h->d_trace_nodes, h->d_trace_out, h->d_trace_e, h->d_mb, h->d_sink, h->d_stamps, h->d_ck_U, h->d_ck_phi,
-                  h->d_rec, h->d_Ub, h->d_pb, h->d_thb, h->d_slot_of_edge, h->d_edge_flip, h->d_mb64, h->d_contrib};
+                  h->d_rec, h->d_Ub, h->d_pb, h->d_thb, h->d_slot_of_edge, h->d_edge_flip, h->d_mb64, h->d_sink64, h->d_contrib};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (h->ev0) (void)hipEventDestroy(h->ev0);
@@ -498,9 +500,36 @@ hipError_t queue_decode(mplpxx_solver* h, int* labels, double* energy) {
                                h->d_edge_min, energy, h->d_err, h->spin_limit, h->stream());
 }
 
+// workgroups of the FP64 mailbox engine, of at most `cap` (one per compute
+// unit; half of them each where the reverse of one segment runs beside the
+// recomputation of another)
+int fwd64_grid(const mplpxx_solver* h, int cap) {
+  return std::max(1, std::min(h->m, mb_default_grid(std::min(h->max_step, cap), cap, h->m, h->L, [] { return 1; },
+                                                    sizeof(double))));
+}
+
 template <typename T> SoloArgs<T> solo_args(mplpxx_solver* h, double* trace) {
   return SoloArgs<T>{static_cast<const T*>(h->d_tables), static_cast<T*>(h->d_phi), static_cast<T*>(h->d_U),
                      reinterpret_cast<T*>(h->d_Ulo), h->d_slots, trace, h->d_trace_e, h->L, h->m, h->n, h->S};
+}
+
+// mailboxes (of the unaries, then of their adjoints) and scratch words of the
+// FP64 mailbox engine
+hipError_t ensure_mb64(mplpxx_solver* h) {
+  hipError_t e = hipSuccess;
+  if (!h->d_mb64) e = hipMalloc(&h->d_mb64, 2 * (size_t)h->n * mb64_row_words(h->L) * sizeof(unsigned long long));
+  if (e == hipSuccess && !h->d_sink64)
+    e = hipMalloc(&h->d_sink64, (size_t)h->num_cus * kF64Sink * sizeof(unsigned long long));
+  return e;
+}
+
+// `iters` iterations of the FP64 mailbox forward from the state in d_mb64
+hipError_t fwd64_args(mplpxx_solver* h, int iters, Fwd64Args* f) {
+  const hipError_t e = ensure_mb64(h);
+  if (e != hipSuccess) return e;
+  *f = Fwd64Args{static_cast<const double*>(h->d_tables), static_cast<double*>(h->d_phi), h->d_mb64, h->d_slots, h->L,
+                 h->m, h->n, iters, nullptr, nullptr, h->d_sink64, h->d_err, h->spin_limit, fwd64_grid(h, h->num_cus)};
+  return hipSuccess;
 }
 
 template <typename T> int iterate_t(mplpxx_solver* h, int k, double* trace_host) {
@@ -577,16 +606,15 @@ template <typename T> int iterate_t(mplpxx_solver* h, int k, double* trace_host)
                                      h->gen_tiles() ? h->potts : 0, rule_mb ? h->rule : MPLPXX_RULE_H));
       HIP_TRY(launch_mb_fini(static_cast<float*>(h->d_U), h->d_Ulo, h->d_mb, h->n, h->L, a.mbs,
                              trace_host ? h->d_trace_nodes + (size_t)(k - 1) * h->n : nullptr, st));
-    } else if (!trace_host && h->L <= 64) {
-      // FP64 without a trace: the mailbox forward (two tagged words per
-      // label, no fences; bitwise the version-counter engine below)
-      const size_t nL = (size_t)h->n * h->L;
-      if (!h->d_mb64) HIP_TRY(hipMalloc(&h->d_mb64, 2 * nL * 2 * sizeof(unsigned long long)));
-      HIP_TRY(launch_mb64_init(static_cast<const double*>(h->d_U), h->d_mb64, nL, st));
-      HIP_TRY(launch_adj64(static_cast<const double*>(h->d_tables), static_cast<double*>(h->d_phi), h->d_mb64, k,
-                           nullptr, std::max(1, std::min(h->m, h->num_cus)), nullptr, nullptr, nullptr, nullptr, nullptr,
-                           0, 0, h->d_slots, h->L, h->m, h->d_err, h->spin_limit, st));
-      HIP_TRY(launch_mb64_fini(static_cast<double*>(h->d_U), h->d_mb64, nL, st));
+    } else if (h->L <= 64) {
+      // FP64: the mailbox forward (two tagged words per label, no fences)
+      Fwd64Args f{};
+      HIP_TRY(fwd64_args(h, k, &f));
+      f.trace = trace_host ? h->d_trace_nodes : nullptr;
+      HIP_TRY(launch_mb64_init(static_cast<const double*>(h->d_U), h->d_mb64, h->n, h->L, st));
+      HIP_TRY(launch_fwd64(f, st));
+      HIP_TRY(launch_mb64_fini(static_cast<double*>(h->d_U), h->d_mb64, h->n, h->L,
+                               trace_host ? h->d_trace_nodes + (size_t)(k - 1) * h->n : nullptr, st));
     } else {
       HsArgs<T> a = hs_args<T>(h, trace_host ? h->d_trace_nodes : nullptr);
       HIP_TRY(launch_fill_int(h->d_ver, 0, h->n, st));
@@ -626,28 +654,19 @@ namespace {
 template <typename T> bool adjoint_persistent(const mplpxx_solver* h) {
   return sizeof(T) == 8 && h->L <= 64 && h->m > 0 && h->engine() != ENGINE_STEP;
 }
-// workgroups of one role of the persistent adjoint launch: one per compute
-// unit for a launch with one role, half of them each when the reverse of
-// one segment runs beside the recomputation of the previous one (a
-// workgroup of either role fits beside one of the other on a unit); at most
-// one per slot
-int adjoint_grid(const mplpxx_solver* h, bool two_roles) {
-  return std::max(1, std::min(h->m, two_roles ? h->num_cus / 2 : h->num_cus));
-}
-
 // `seg` iterations of an FP64 handle on the persistent forward, the
-// unaries through the mailboxes
-int fwd64_segment(mplpxx_solver* h, int seg) {
+// unaries through the mailboxes; rec: with argmin records
+int fwd64_segment(mplpxx_solver* h, int seg, unsigned char* rec) {
   hipStream_t st = h->stream();
-  const size_t nL = (size_t)h->n * h->L;
-  if (h->solo(false)) {
+  if (!rec && h->solo(false)) {
     HIP_TRY(launch_solo<double>(solo_args<double>(h, nullptr), h->max_step, seg, st));
   } else {
-    HIP_TRY(launch_mb64_init(static_cast<const double*>(h->d_U), h->d_mb64, nL, st));
-    HIP_TRY(launch_adj64(static_cast<const double*>(h->d_tables), static_cast<double*>(h->d_phi), h->d_mb64, seg, nullptr,
-                         adjoint_grid(h, false), nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, h->d_slots, h->L,
-                         h->m, h->d_err, h->spin_limit, st));
-    HIP_TRY(launch_mb64_fini(static_cast<double*>(h->d_U), h->d_mb64, nL, st));
+    Fwd64Args f{};
+    HIP_TRY(fwd64_args(h, seg, &f));
+    f.rec = rec;
+    HIP_TRY(launch_mb64_init(static_cast<const double*>(h->d_U), h->d_mb64, h->n, h->L, st));
+    HIP_TRY(rec ? launch_adj64(f, Rev64Args{}, nullptr, st) : launch_fwd64(f, st));
+    HIP_TRY(launch_mb64_fini(static_cast<double*>(h->d_U), h->d_mb64, h->n, h->L, nullptr, st));
   }
   const int rc = sync_and_check(h);
   if (rc == MPLPXX_OK) h->iterations += seg;
@@ -663,7 +682,7 @@ template <typename T> int adjoint_forward_t(mplpxx_solver* h, int K, int every, 
   for (void** p : {&h->d_ck_U, &h->d_ck_phi, (void**)&h->d_rec, (void**)&h->d_ck_Ulo, (void**)&h->d_contrib})
     if (*p) { (void)hipFree(*p); *p = nullptr; }
   if (pers) {
-    if (!h->d_mb64) HIP_TRY(hipMalloc(&h->d_mb64, 2 * nL * 2 * sizeof(unsigned long long)));
+    HIP_TRY(ensure_mb64(h));
     HIP_TRY(hipMalloc(&h->d_contrib, (size_t)every * h->m * 3 * h->L * sizeof(double)));
   }
   const size_t rec_bytes = (pers ? 2 : 1) * (size_t)every * h->m * 3 * h->L;
@@ -695,7 +714,12 @@ template <typename T> int adjoint_forward_t(mplpxx_solver* h, int K, int every, 
       HIP_TRY(hipMemcpyAsync(h->d_ck_Ulo + c * nL, h->d_Ulo, nL * sizeof(float), hipMemcpyDeviceToDevice, st));
     if (h->m) HIP_TRY(hipMemcpyAsync((char*)h->d_ck_phi + c * mp * esz, h->d_phi, mp * esz, hipMemcpyDeviceToDevice, st));
     const int seg = std::min(every, K - c * every);
-    const int rc = pers ? fwd64_segment(h, seg) : iterate_t<T>(h, seg, nullptr);
+    // (the record buffers hold two segments: the last two, which the reverse
+    // needs first, are recorded here; a small model's forward is shorter on one
+    // workgroup, without records)
+    const bool record = pers && c >= nck - 2 && !h->solo(false);
+    const int rc = pers ? fwd64_segment(h, seg, record ? h->d_rec + (size_t)(c & 1) * every * h->m * 3 * h->L : nullptr)
+                        : iterate_t<T>(h, seg, nullptr);
     if (rc != MPLPXX_OK) return rc;
   }
   HIP_TRY(hipMemcpyAsync((char*)h->d_ck_U + nck * nL * esz, h->d_U, nL * esz, hipMemcpyDeviceToDevice, st));
@@ -710,6 +734,7 @@ template <typename T> int adjoint_forward_t(mplpxx_solver* h, int K, int every, 
   h->adj_K = K;
   h->adj_every = every;
   h->adj_nck = nck;
+  h->adj_rec_from = pers && !h->solo(false) ? std::max(0, nck - 2) : nck;
   h->adj_ready = true;
   h->adj_iter_mark = h->iterations;
   if (loss) {
@@ -741,39 +766,43 @@ template <typename T> int adjoint_backward_t(mplpxx_solver* h, void* grad_u, voi
     HIP_TRY(hipMemsetAsync(h->d_pb, 0, mp * esz, st));
     HIP_TRY(hipMemsetAsync(h->d_thb, 0, (size_t)h->m * h->L * h->L * esz, st));
   }
-  const bool pers = adjoint_persistent<T>(h) && h->d_mb64 && h->d_contrib;
+  const bool pers = adjoint_persistent<T>(h) && h->d_contrib;
   if (pers) {
-    // Persistent pipeline: launch c runs the reverse of segment c beside
-    // the recomputation (with argmin records) of segment c - 1, which needs
-    // only its checkpoint; records alternate between two buffers.  The
-    // first launch recomputes the last segment alone, the last reverses
-    // segment 0 alone.
+    // Persistent pipeline: launch c runs the reverse of segment c beside the
+    // recomputation (with argmin records) of segment c - 1, which needs only
+    // its checkpoint, where the forward kept no record of it; records
+    // alternate between two buffers.
     unsigned long long* mb_fwd = h->d_mb64;
-    unsigned long long* mb_rev = h->d_mb64 + 2 * nL;
+    unsigned long long* mb_rev = h->d_mb64 + (size_t)h->n * mb64_row_words(h->L);
     auto rec_of = [&](int c) { return h->d_rec + (size_t)(c & 1) * every * rec_it; };
     auto seg_of = [&](int c) { return std::min(every, K - c * every); };
     auto restore = [&](int c) -> hipError_t {
       hipError_t e = hipMemcpyAsync(h->d_U, (char*)h->d_ck_U + c * nL * esz, nL * esz, hipMemcpyDeviceToDevice, st);
       if (e == hipSuccess)
         e = hipMemcpyAsync(h->d_phi, (char*)h->d_ck_phi + c * mp * esz, mp * esz, hipMemcpyDeviceToDevice, st);
-      if (e == hipSuccess) e = launch_mb64_init(static_cast<const double*>(h->d_U), mb_fwd, nL, st);
+      if (e == hipSuccess) e = launch_mb64_init(static_cast<const double*>(h->d_U), mb_fwd, h->n, h->L, st);
       return e;
     };
     for (int c = nck; c >= 0; --c) {
-      // reverse of segment c (c < nck), recomputation of segment c - 1 (c >= 1)
-      const bool rev = c < nck, fwd = c >= 1;
+      const bool rev = c < nck, fwd = c >= 1 && c - 1 < h->adj_rec_from;
+      if (!rev && !fwd) continue;
       if (fwd) HIP_TRY(restore(c - 1));
-      if (rev) HIP_TRY(launch_mb64_init(static_cast<const double*>(h->d_Ub), mb_rev, nL, st));
-      const bool both = rev && fwd;
-      HIP_TRY(launch_adj64(static_cast<const double*>(h->d_tables), static_cast<double*>(h->d_phi), mb_fwd,
-                           fwd ? seg_of(c - 1) : 0, fwd ? rec_of(c - 1) : nullptr, adjoint_grid(h, both),
-                           rev ? rec_of(c) : nullptr, mb_rev, static_cast<double*>(h->d_pb), h->d_contrib,
-                           static_cast<double*>(h->d_thb), rev ? seg_of(c) : 0, adjoint_grid(h, both), h->d_slots,
-                           h->L, h->m, h->d_err, h->spin_limit, st));
-      if (rev) HIP_TRY(launch_mb64_fini(static_cast<double*>(h->d_Ub), mb_rev, nL, st));
+      if (rev) HIP_TRY(launch_mb64_init(static_cast<const double*>(h->d_Ub), mb_rev, h->n, h->L, st));
+      const int cap = rev && fwd ? h->num_cus / 2 : h->num_cus;
+      Fwd64Args f{};
+      HIP_TRY(fwd64_args(h, fwd ? seg_of(c - 1) : 0, &f));
+      f.rec = fwd ? rec_of(c - 1) : nullptr;
+      f.grid = fwd ? fwd64_grid(h, cap) : 0;
+      const Rev64Args r{h->d_slots, h->L, h->m, rev ? seg_of(c) : 0, rev ? rec_of(c) : nullptr, mb_rev,
+                        static_cast<double*>(h->d_pb), h->d_contrib, h->d_err, h->spin_limit,
+                        rev ? fwd64_grid(h, cap) : 0};
+      HIP_TRY(launch_adj64(f, r, static_cast<double*>(h->d_thb), st));
+      if (rev) HIP_TRY(launch_mb64_fini(static_cast<double*>(h->d_Ub), mb_rev, h->n, h->L, nullptr, st));
       const int rc = sync_and_check(h);
       if (rc != MPLPXX_OK) return rc;
     }
+    // (recomputed segments have taken the buffers of the recorded ones)
+    if (h->adj_rec_from > 0) h->adj_rec_from = nck;
   }
   for (int c = nck - 1; c >= 0 && h->m > 0 && !pers; --c) {
     const int seg = std::min(every, K - c * every);

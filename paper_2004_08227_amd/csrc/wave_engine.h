@@ -50,15 +50,6 @@ struct WvScratch {
   float qq[64];
 };
 
-// Stops the compiler from moving memory operations across this point (LDS
-// exchanges between the lanes of one wave need no hardware wait: a wave's
-// LDS operations execute in order).
-__device__ __forceinline__ void wave_sync() {
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  __builtin_amdgcn_wave_barrier();
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
 // minimum over the 8 lanes of an octet (lane bits 0..2), N values at once
 template <int N> __device__ __forceinline__ void oct_min_n(float (&x)[N]) {
 #pragma unroll
