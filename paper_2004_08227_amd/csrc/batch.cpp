@@ -78,6 +78,8 @@ struct mplpxx_batch {
   double* d_node_min = nullptr;
   double* d_edge_min = nullptr;
   double* d_duals = nullptr;
+  int* d_slot_of_edge = nullptr;         // all models', for get_state
+  float* d_export = nullptr;             // the largest model's messages in edge order
   // plan
   int grid = 0;
   int grid_opt = 0;
@@ -337,13 +339,39 @@ int plan(mplpxx_batch* b) {
 void free_batch(mplpxx_batch* b) {
   void* ptrs[] = {b->d_tables, b->d_phi, b->d_U, b->d_Ulo, b->d_unaries, b->d_mb, b->d_slots, b->d_deg, b->d_models,
                   b->d_tasks, b->d_task_ptr, b->d_err, b->d_ticket, b->d_sink, b->d_wg_time, b->d_node_model,
-                  b->d_slot_model, b->d_node_ptr, b->d_inc, b->d_node_min, b->d_edge_min, b->d_duals};
+                  b->d_slot_model, b->d_node_ptr, b->d_inc, b->d_node_min, b->d_edge_min, b->d_duals, b->d_slot_of_edge, b->d_export};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
   if (b->ev0) (void)hipEventDestroy(b->ev0);
   if (b->ev1) (void)hipEventDestroy(b->ev1);
   if (b->stream) (void)hipStreamDestroy(b->stream);
+}
+
+// slots by edge of every model and room for one model's messages, made by the
+// first state that is read
+hipError_t ensure_export(mplpxx_batch* b) {
+  if (b->d_export) return hipSuccess;
+  size_t most = 0;
+  std::vector<int> soe;
+  soe.reserve(b->total_slots);
+  for (const ModelHost& h : b->mh) {
+    most = std::max(most, (size_t)h.m * 2 * h.L);
+    soe.insert(soe.end(), h.slot_of_edge.begin(), h.slot_of_edge.end());
+  }
+  hipError_t e = hipSuccess;
+  if (!b->d_slot_of_edge) {
+    e = hipMalloc(&b->d_slot_of_edge, std::max<size_t>(1, soe.size()) * sizeof(int));
+    if (e != hipSuccess) return e;
+    e = hipMemcpyAsync(b->d_slot_of_edge, soe.data(), soe.size() * sizeof(int), hipMemcpyHostToDevice, b->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
+    if (e != hipSuccess) {
+      (void)hipFree(b->d_slot_of_edge);
+      b->d_slot_of_edge = nullptr;
+      return e;
+    }
+  }
+  return hipMalloc(&b->d_export, std::max<size_t>(1, most) * sizeof(float));
 }
 
 hipError_t enqueue(mplpxx_batch* b, int k) {
@@ -645,6 +673,18 @@ int mplpxx_batch_get_state(mplpxx_batch* b, int32_t model, float* U, float* phi,
   if (U_comp)
     HIP_TRY(hipMemcpy(U_comp, b->d_Ulo + d.u_off, (size_t)h.n * h.L * sizeof(float), hipMemcpyDeviceToHost));
   if (phi && h.m) {
+    // ordered on the device (see mplpxx_get_state)
+    bool on_device = (size_t)h.m * 2 * h.L * sizeof(float) >= kExportOnDevice;
+    if (on_device && ensure_export(b) != hipSuccess) {
+      (void)hipGetLastError();  // no memory for the ordered copy
+      on_device = false;
+    }
+    if (on_device) {
+      HIP_TRY(launch_phi_by_edge<float>(b->d_phi + d.phi_off, b->d_slot_of_edge + d.slot_off, h.m, h.L, b->d_export, b->stream));
+      HIP_TRY(hipMemcpyAsync(phi, b->d_export, (size_t)h.m * 2 * h.L * sizeof(float), hipMemcpyDeviceToHost, b->stream));
+      HIP_TRY(hipStreamSynchronize(b->stream));
+      return MPLPXX_OK;
+    }
     std::vector<float> tmp((size_t)h.m * 2 * h.L);
     HIP_TRY(hipMemcpy(tmp.data(), b->d_phi + d.phi_off, tmp.size() * sizeof(float), hipMemcpyDeviceToHost));
     const size_t row = 2 * (size_t)h.L;

@@ -14,6 +14,7 @@
 // whole updates on the wave engine (L <= 64, many updates in flight per
 // compute unit).
 #include "device_common.h"
+#include "dual_terms.h"
 #include "wave_engine.h"
 #include "wave_batch.h"
 
@@ -352,51 +353,35 @@ __device__ __forceinline__ double breduce(double v, double* sh) {
   return r;
 }
 
-__global__ void __launch_bounds__(128) k_batch_node_terms(const float* __restrict__ unaries, const float* __restrict__ phi,
-                                                          const BatchModel* __restrict__ models,
-                                                          const int* __restrict__ node_model,
-                                                          const int* __restrict__ node_ptr, const int* __restrict__ inc,
-                                                          double* __restrict__ node_min) {
-  __shared__ double sh[128];
-  const int g = blockIdx.x;
-  const BatchModel md = models[node_model[g]];
-  const int u = g - md.node_off;
-  const int L = md.L;
-  const int s = threadIdx.x;
-  double acc = __builtin_inf();
-  if (s < L) {
-    acc = (double)unaries[md.u_off + (size_t)u * L + s];
+// waves [0, total_nodes) take a node each, the others a slot (dual_terms.h)
+__global__ void __launch_bounds__(256) k_batch_terms(const float* __restrict__ unaries, const float* __restrict__ tables,
+                                                     const float* __restrict__ phi, const BatchModel* __restrict__ models,
+                                                     const int* __restrict__ node_model, const int* __restrict__ slot_model,
+                                                     const int* __restrict__ node_ptr, const int* __restrict__ inc,
+                                                     int total_nodes, int total_slots, double* __restrict__ node_min,
+                                                     double* __restrict__ edge_min) {
+  __shared__ float sh[4][2 * MPLPXX_MAX_LABELS];
+  const int w = uni((int)(blockIdx.x * 4 + (threadIdx.x >> 6))), lane = threadIdx.x & 63;
+  if (w < total_nodes) {
+    const BatchModel md = models[uni(node_model[w])];
+    const int u = w - md.node_off;
     const int* np = node_ptr + md.csr_off;
-    for (int k = np[u]; k < np[u + 1]; ++k) {
-      const int code = inc[md.inc_off + k];
-      acc += (double)phi[md.phi_off + (size_t)(code >> 1) * 2 * L + (size_t)(code & 1) * L + s];
-    }
+    const double mn = node_term(unaries + md.u_off + (size_t)u * md.L, phi + md.phi_off, inc + md.inc_off, uni(np[u]),
+                                uni(np[u + 1]), md.L);
+    if (lane == 0) node_min[w] = mn;
+  } else if (w - total_nodes < total_slots) {
+    const int g = w - total_nodes;
+    const BatchModel md = models[uni(slot_model[g])];
+    const int slot = g - md.slot_off, L = md.L;
+    const float* ph = phi + md.phi_off + (size_t)slot * 2 * L;
+    const float* tab = tables + md.table_off + (size_t)slot * (md.potts ? cost_params(md.potts) : L * L);
+    // (a model's tables start anywhere: four entries a load where that is a
+    // multiple of 16 bytes too)
+    const double mn = !md.potts && L % 4 == 0 && (md.table_off & 3) == 0
+                          ? edge_term<float, 4>(tab, ph, L, 0, sh[threadIdx.x >> 6])
+                          : edge_term<float, 1>(tab, ph, L, md.potts, sh[threadIdx.x >> 6]);
+    if (lane == 0) edge_min[g] = mn;
   }
-  const double mn = breduce<128, true>(acc, sh);
-  if (s == 0) node_min[g] = mn;
-}
-
-__global__ void __launch_bounds__(256) k_batch_edge_terms(const float* __restrict__ tables, const float* __restrict__ phi,
-                                                          const BatchModel* __restrict__ models,
-                                                          const int* __restrict__ slot_model,
-                                                          double* __restrict__ edge_min) {
-  __shared__ double sh[256];
-  const int g = blockIdx.x;
-  const BatchModel md = models[slot_model[g]];
-  const int slot = g - md.slot_off;
-  const int L = md.L;
-  // (structured costs: the expanded table from the slot's parameters)
-  const float* tab = tables + md.table_off + (md.potts ? (size_t)slot * cost_params(md.potts) : (size_t)slot * L * L);
-  const float* p0 = phi + md.phi_off + (size_t)slot * 2 * L;
-  const float* p1 = p0 + L;
-  double mn = __builtin_inf();
-  for (int i = threadIdx.x; i < L * L; i += 256) {
-    const int s = i / L, t = i - s * L;
-    const float th = md.potts ? structured_cost(md.potts, tab, s, t) : tab[i];
-    mn = __builtin_fmin(mn, (double)th - (double)p0[s] - (double)p1[t]);
-  }
-  mn = breduce<256, true>(mn, sh);
-  if (threadIdx.x == 0) edge_min[g] = mn;
 }
 
 __global__ void __launch_bounds__(256) k_batch_sum(const BatchModel* __restrict__ models,
@@ -415,11 +400,9 @@ hipError_t launch_batch_dual(const float* unaries, const float* tables, const fl
                              const int* node_model, const int* slot_model, const int* node_ptr, const int* inc,
                              int total_nodes, int total_slots, int count, double* node_min, double* edge_min,
                              double* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_batch_node_terms, dim3(total_nodes), dim3(128), 0, st, unaries, phi, models, node_model,
-                     node_ptr, inc, node_min);
-  if (total_slots > 0)
-    hipLaunchKernelGGL(k_batch_edge_terms, dim3(total_slots), dim3(256), 0, st, tables, phi, models, slot_model,
-                       edge_min);
+  hipLaunchKernelGGL(k_batch_terms, dim3((unsigned)((total_nodes + (size_t)total_slots + 3) / 4)), dim3(256), 0, st, unaries,
+                     tables, phi, models, node_model, slot_model, node_ptr, inc, total_nodes, total_slots, node_min,
+                     edge_min);
   hipLaunchKernelGGL(k_batch_sum, dim3(count), dim3(256), 0, st, models, node_min, edge_min, out);
   return hipGetLastError();
 }

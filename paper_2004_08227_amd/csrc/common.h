@@ -230,6 +230,8 @@ hipError_t launch_check_finite(const T* p, size_t count, int* flag, hipStream_t 
 template <typename T>
 hipError_t launch_pack_tables(const T* src, T* dst, const int* slot_edge, const int* slot_flip, int m, int L,
                               hipStream_t st);
+template <typename T>
+hipError_t launch_phi_by_edge(const T* phi_slot, const int* slot_of_edge, int m, int L, T* out, hipStream_t st);
 hipError_t launch_fill_int(int* p, int value, size_t count, hipStream_t st);
 hipError_t launch_convert(const float* src, double* dst, size_t count, hipStream_t st);
 hipError_t launch_convert(const double* src, float* dst, size_t count, hipStream_t st);

@@ -10,10 +10,9 @@
 #include <algorithm>
 
 #include "device_common.h"
+#include "dual_terms.h"
 
 namespace mplpxx {
-
-__device__ __forceinline__ double dmin(double a, double b) { return __builtin_fmin(a, b); }
 
 // fixed-order block reduction of one double per thread (blockDim power of 2)
 template <int NT, bool kMin>
@@ -31,26 +30,6 @@ __device__ __forceinline__ double block_reduce(double v, double* sh) {
   return r;
 }
 
-// node terms: one workgroup per node, one thread per label
-template <typename T>
-__global__ void __launch_bounds__(128) k_node_terms(const T* __restrict__ unaries, const T* __restrict__ phi,
-                                                    const int* __restrict__ node_ptr, const int* __restrict__ inc,
-                                                    int L, double* __restrict__ node_min) {
-  __shared__ double sh[128];
-  const int u = blockIdx.x;
-  const int s = threadIdx.x;
-  double acc = __builtin_inf();
-  if (s < L) {
-    acc = (double)unaries[(size_t)u * L + s];
-    for (int k = node_ptr[u]; k < node_ptr[u + 1]; ++k) {
-      const int code = inc[k];
-      acc += (double)phi[(size_t)(code >> 1) * 2 * L + (size_t)(code & 1) * L + s];
-    }
-  }
-  const double mn = block_reduce<128, true>(acc, sh);
-  if (s == 0) node_min[u] = mn;
-}
-
 // th(s, t) of the edge in `slot`: its table, or, for structured costs (their
 // parameters per slot), the expanded table entry
 template <typename T>
@@ -59,23 +38,6 @@ __device__ __forceinline__ T table_at(const T* tables, int slot, int L, int s, i
     if (potts) return structured_cost(potts, tables + (size_t)slot * cost_params(potts), s, t);
   }
   return tables[(size_t)slot * L * L + (size_t)s * L + t];
-}
-
-// edge terms: one workgroup per slot
-template <typename T>
-__global__ void __launch_bounds__(256) k_edge_terms(const T* __restrict__ tables, const T* __restrict__ phi, int L,
-                                                    int potts, double* __restrict__ edge_min) {
-  __shared__ double sh[256];
-  const int slot = blockIdx.x;
-  const T* p0 = phi + (size_t)slot * 2 * L;
-  const T* p1 = p0 + L;
-  double mn = __builtin_inf();
-  for (int i = threadIdx.x; i < L * L; i += 256) {
-    const int s = i / L, t = i - s * L;
-    mn = dmin(mn, (double)table_at(tables, slot, L, s, t, potts) - (double)p0[s] - (double)p1[t]);
-  }
-  mn = block_reduce<256, true>(mn, sh);
-  if (threadIdx.x == 0) edge_min[slot] = mn;
 }
 
 // out = sum(a[0..na)) + sum(b[0..nb)), fixed order, one workgroup
@@ -89,11 +51,38 @@ __global__ void __launch_bounds__(1024) k_sum2(const double* __restrict__ a, int
   if (threadIdx.x == 0) *out = acc;
 }
 
+// Node and edge terms of Eq. (3) in one launch (dual_terms.h): waves [0, n)
+// take a node each, the others a slot.
+template <typename T, int V>
+__global__ void __launch_bounds__(256) k_dual_terms(const T* __restrict__ unaries, const T* __restrict__ tables,
+                                                    const T* __restrict__ phi, const int* __restrict__ node_ptr,
+                                                    const int* __restrict__ inc, int n, int L, int m, int potts,
+                                                    double* __restrict__ node_min, double* __restrict__ edge_min) {
+  __shared__ T sh[4][2 * MPLPXX_MAX_LABELS];
+  const int w = uni((int)(blockIdx.x * 4 + (threadIdx.x >> 6))), lane = threadIdx.x & 63;
+  if (w < n) {
+    const double mn = node_term(unaries + (size_t)w * L, phi, inc, uni(node_ptr[w]), uni(node_ptr[w + 1]), L);
+    if (lane == 0) node_min[w] = mn;
+  } else if (w - n < m) {
+    const int slot = w - n;
+    const size_t step = potts ? (size_t)cost_params(potts) : (size_t)L * L;
+    const double mn = edge_term<T, V>(tables + slot * step, phi + (size_t)slot * 2 * L, L, potts, sh[threadIdx.x >> 6]);
+    if (lane == 0) edge_min[slot] = mn;
+  }
+}
+
 template <typename T>
 hipError_t launch_dual(const T* unaries, const T* tables, const T* phi, const int* node_ptr, const int* inc, int n,
                        int L, int m, double* node_min, double* edge_min, double* out, hipStream_t st, int potts) {
-  hipLaunchKernelGGL(k_node_terms<T>, dim3(n), dim3(128), 0, st, unaries, phi, node_ptr, inc, L, node_min);
-  if (m > 0) hipLaunchKernelGGL(k_edge_terms<T>, dim3(m), dim3(256), 0, st, tables, phi, L, potts, edge_min);
+  const dim3 grid((unsigned)((n + (size_t)m + 3) / 4));
+  // (a vector of 16 bytes stays inside a row, and is aligned, where its width divides L)
+  constexpr int V = 16 / sizeof(T);
+  if (!potts && L % V == 0)
+    hipLaunchKernelGGL((k_dual_terms<T, V>), grid, dim3(256), 0, st, unaries, tables, phi, node_ptr, inc, n, L, m, potts,
+                       node_min, edge_min);
+  else
+    hipLaunchKernelGGL((k_dual_terms<T, 1>), grid, dim3(256), 0, st, unaries, tables, phi, node_ptr, inc, n, L, m, potts,
+                       node_min, edge_min);
   hipLaunchKernelGGL(k_sum2, dim3(1), dim3(1024), 0, st, node_min, n, edge_min, m, out);
   return hipGetLastError();
 }
@@ -221,21 +210,6 @@ __global__ void k_decode_init(int* __restrict__ labels, int n, int* __restrict__
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) labels[i] = -1;
   if (i == 0) *ticket = 0;
-}
-
-// exact minimum over the 64 lanes
-__device__ __forceinline__ double wave_min64(double x) {
-  x = row16_min(x);
-  {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
-    x = dmin(dbl_of(lo[0], hi[0]), dbl_of(lo[1], hi[1]));
-  }
-  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
-  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
-  return dmin(dbl_of(lo[0], hi[0]), dbl_of(lo[1], hi[1]));
 }
 
 // PER: labels per lane (1 up to 64 labels, 2 up to 128); B: incidences a wave
@@ -467,6 +441,22 @@ hipError_t launch_pack_tables(const T* src, T* dst, const int* slot_edge, const 
   return hipGetLastError();
 }
 
+// messages in the caller's edge order from slot order
+template <typename T>
+__global__ void __launch_bounds__(128) k_phi_by_edge(const T* __restrict__ phi_slot, const int* __restrict__ slot_of_edge,
+                                                     int row, T* __restrict__ out) {
+  const size_t e = blockIdx.x;
+  const T* src = phi_slot + (size_t)slot_of_edge[e] * row;
+  for (int i = threadIdx.x; i < row; i += 128) out[e * row + i] = src[i];
+}
+
+template <typename T>
+hipError_t launch_phi_by_edge(const T* phi_slot, const int* slot_of_edge, int m, int L, T* out, hipStream_t st) {
+  if (m <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_phi_by_edge<T>, dim3((unsigned)m), dim3(128), 0, st, phi_slot, slot_of_edge, 2 * L, out);
+  return hipGetLastError();
+}
+
 __global__ void k_fill_int(int* __restrict__ p, int value, size_t count) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < count; i += (size_t)gridDim.x * blockDim.x)
     p[i] = value;
@@ -510,6 +500,7 @@ hipError_t launch_fill_int(int* p, int value, size_t count, hipStream_t st) {
   template hipError_t launch_decode<T>(const T*, const T*, const T*, const SlotInfo*, const int*, const int*, int, \
                                        int, int, int*, int*, double*, double*, double*, int*, long long,           \
                                        hipStream_t, int);                                                          \
+  template hipError_t launch_phi_by_edge<T>(const T*, const int*, int, int, T*, hipStream_t);                      \
   template hipError_t launch_check_finite<T>(const T*, size_t, int*, hipStream_t);                                 \
   template hipError_t launch_pack_tables<T>(const T*, T*, const int*, const int*, int, int, hipStream_t);
 MPLPXX_INST(float)

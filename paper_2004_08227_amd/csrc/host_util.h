@@ -104,6 +104,10 @@ inline int mb_default_grid(int max_step, int num_cus, long long m, int L, const 
   return (int)std::min<long long>(num_cus, std::max<long long>(2ll * max_step, fit));
 }
 
+// messages of at least this size are put into the caller's edge order on the
+// device when a state is read (figures at mplpxx_get_state)
+constexpr size_t kExportOnDevice = 1 << 20;
+
 // smallest register tile (16, 32, 64, 128) holding L labels
 inline int next_tile(int L) {
   int lt = 16;

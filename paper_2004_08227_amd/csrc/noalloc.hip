@@ -69,15 +69,6 @@ bool device_memory_of(const void* p, int dev) {
   return (a.type == hipMemoryTypeDevice || a.type == hipMemoryTypeManaged) && a.device == dev;
 }
 
-// phi in the caller's edge order from phi in slot order
-__global__ void __launch_bounds__(256) k_phi_by_edge(const float* __restrict__ phi_slot,
-                                                     const int* __restrict__ slot_of_edge, int row,
-                                                     float* __restrict__ out) {
-  const int e = blockIdx.x;
-  const float* src = phi_slot + (size_t)slot_of_edge[e] * row;
-  for (int i = threadIdx.x; i < row; i += 256) out[(size_t)e * row + i] = src[i];
-}
-
 }  // namespace
 
 extern "C" int mplpxx_solve_noalloc(int32_t n, int32_t L, int64_t m, const int32_t* edges, const float* unaries_dev,
@@ -226,8 +217,7 @@ extern "C" int mplpxx_solve_noalloc(int32_t n, int32_t L, int64_t m, const int32
     }
   }
   HIP_TRY(launch_dual<float>(unaries_dev, d_tab, d_phi, d_nptr, d_inc, n, L, (int)m, d_nmin, d_emin, d_dual, st));
-  if (m > 0) hipLaunchKernelGGL(k_phi_by_edge, dim3((unsigned)m), dim3(256), 0, st, d_phi, d_soe, 2 * L, phi_dev);
-  HIP_TRY(hipGetLastError());
+  HIP_TRY(launch_phi_by_edge<float>(d_phi, d_soe, (int)m, L, phi_dev, st));
   HIP_TRY(hipStreamSynchronize(st));
   int err[8] = {0};
   HIP_TRY(hipMemcpy(err, d_err, sizeof(err), hipMemcpyDeviceToHost));

@@ -103,6 +103,7 @@ struct mplpxx_solver {
   size_t adj_bytes = 0;                   // device bytes of the adjoint buffers above
   int* d_slot_of_edge = nullptr;          // [m]
   int* d_edge_flip = nullptr;             // [m]
+  void* d_export = nullptr;               // [m][2][L] messages in edge order (get_state)
   int adjoint_f64 = 1;                    // FP32 handles: differentiate an FP64 run
   mplpxx_solver* shadow = nullptr;        // the FP64 twin for that (same graph, widened costs)
   // execution
@@ -197,7 +198,7 @@ void free_all(mplpxx_solver* h) {
   void* ptrs[] = {h->d_tables, h->d_phi, h->d_U, h->d_Ulo, h->d_ck_Ulo, h->d_unaries, h->d_slots, h->d_deg, h->d_ver, h->d_err,
                   h->d_node_ptr, h->d_inc, h->d_node_min, h->d_edge_min, h->d_scalar, h->d_labels,
                   h->d_trace_nodes, h->d_trace_out, h->d_trace_e, h->d_mb, h->d_sink, h->d_stamps, h->d_ck_U, h->d_ck_phi,
-                  h->d_rec, h->d_Ub, h->d_pb, h->d_thb, h->d_slot_of_edge, h->d_edge_flip, h->d_mb64, h->d_sink64, h->d_contrib};
+                  h->d_rec, h->d_Ub, h->d_pb, h->d_thb, h->d_slot_of_edge, h->d_edge_flip, h->d_export, h->d_mb64, h->d_sink64, h->d_contrib};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (h->ev0) (void)hipEventDestroy(h->ev0);
@@ -458,6 +459,17 @@ int sync_and_check(mplpxx_solver* h) {
   return MPLPXX_OK;
 }
 
+hipError_t ensure_slot_of_edge(mplpxx_solver* h) {
+  if (h->d_slot_of_edge || !h->m) return hipSuccess;
+  int* p = nullptr;
+  hipError_t e = hipMalloc(&p, h->m * sizeof(int));
+  if (e != hipSuccess) return e;
+  e = hipMemcpyAsync(p, h->slot_of_edge.data(), h->m * sizeof(int), hipMemcpyHostToDevice, h->stream());
+  if (e == hipSuccess) h->d_slot_of_edge = p;
+  else (void)hipFree(p);
+  return e;
+}
+
 template <typename T> HsArgs<T> hs_args(mplpxx_solver* h, double* trace) {
   HsArgs<T> a{};
   a.tables = static_cast<const T*>(h->d_tables);
@@ -696,10 +708,9 @@ template <typename T> int adjoint_forward_t(mplpxx_solver* h, int K, int every, 
   h->adj_bytes = (nck + 1) * nL * esz + (h->d_Ulo ? (nck + 1) * nL * sizeof(float) : 0) + (nck + 1) * mp * esz +
                  rec_bytes + nL * esz + mp * esz + (size_t)h->m * h->L * h->L * esz + (size_t)h->m * 2 * sizeof(int) +
                  (pers ? 2 * nL * 2 * sizeof(unsigned long long) + (size_t)every * h->m * 3 * h->L * sizeof(double) : 0);
-  if (!h->d_slot_of_edge && h->m) {
-    HIP_TRY(hipMalloc(&h->d_slot_of_edge, h->m * sizeof(int)));
+  HIP_TRY(ensure_slot_of_edge(h));
+  if (!h->d_edge_flip && h->m) {
     HIP_TRY(hipMalloc(&h->d_edge_flip, h->m * sizeof(int)));
-    HIP_TRY(hipMemcpyAsync(h->d_slot_of_edge, h->slot_of_edge.data(), h->m * sizeof(int), hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(h->d_edge_flip, h->flip.data(), h->m * sizeof(int), hipMemcpyHostToDevice, st));
   }
   // start from phi = 0, U = theta_u
@@ -1147,7 +1158,32 @@ int mplpxx_get_state(mplpxx_solver* h, void* U, void* phi, float* U_comp) {
       std::fill(U_comp, U_comp + (size_t)h->n * L, 0.0f);
   }
   if (phi && h->m) {
-    std::vector<char> tmp((size_t)h->m * 2 * L * esz);
+    // From 1 MB on, put into the caller's order on the device and copied
+    // there at once; below, through a host buffer in slot order and a copy per
+    // edge, which saves the launch (microseconds of the call, host / device:
+    // 10 MB 1290 / 777, 1.6 MB 548 / 304, 1.3 MB 255 / 150, 0.6 MB 84 / 98,
+    // 12 KB 45 / 53).
+    const size_t bytes = (size_t)h->m * 2 * L * esz;
+    bool on_device = bytes >= kExportOnDevice;
+    if (on_device) {
+      hipError_t e = ensure_slot_of_edge(h);
+      if (e == hipSuccess && !h->d_export) e = hipMalloc(&h->d_export, bytes);
+      if (e != hipSuccess) {
+        (void)hipGetLastError();  // no memory for the ordered copy
+        on_device = false;
+      }
+    }
+    if (on_device) {
+      HIP_TRY(h->dtype == MPLPXX_F32
+                  ? launch_phi_by_edge<float>(static_cast<const float*>(h->d_phi), h->d_slot_of_edge, h->m, h->L,
+                                              static_cast<float*>(h->d_export), h->stream())
+                  : launch_phi_by_edge<double>(static_cast<const double*>(h->d_phi), h->d_slot_of_edge, h->m, h->L,
+                                               static_cast<double*>(h->d_export), h->stream()));
+      HIP_TRY(hipMemcpyAsync(phi, h->d_export, bytes, hipMemcpyDeviceToHost, h->stream()));
+      HIP_TRY(hipStreamSynchronize(h->stream()));
+      return MPLPXX_OK;
+    }
+    std::vector<char> tmp(bytes);
     HIP_TRY(hipMemcpy(tmp.data(), h->d_phi, tmp.size(), hipMemcpyDeviceToHost));
     char* dst = static_cast<char*>(phi);
     const size_t row = 2 * L * esz;

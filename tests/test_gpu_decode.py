@@ -83,3 +83,31 @@ def test_decode_structured(kind):
         ref, ref_energy = walk(dense, s.get_state()[1], s.schedule()[1])
     np.testing.assert_array_equal(labels, ref)
     assert energy == ref_energy
+
+
+@pytest.mark.parametrize("n,L,dtype", [(3, 1, np.float32), (40, 20, np.float64), (131, 16, np.float32), (101, 13, np.float64),
+                                       (230, 5, np.float32), (90, 100, np.float32), (70, 3, np.float64)])
+def test_dual_bound_and_state_order(n, L, dtype):
+    """The bound recomputed in numpy from the state the call returns, whose messages are in
+    the caller's edge order (ordered on the host below 1 MB, on the device from there on),
+    with edges given in a shuffled order and both orientations."""
+    model = W.random_graph_model(n, L, 0.9, seed=n, dtype=dtype)
+    rng = np.random.default_rng(L)
+    order = rng.permutation(model.m)
+    e, pw = model.edges[order].copy(), model.pairwise[order].copy()
+    flip = rng.random(model.m) < 0.5
+    e[flip] = e[flip][:, ::-1]
+    pw[flip] = pw[flip].transpose(0, 2, 1)
+    with M.Solver(n, L, e, model.unaries, pw) as s:
+        s.iterate(2)
+        d = s.dual_bound()
+        U, phi, c = s.get_state(comp=True)
+    lo, hi = e.min(1), e.max(1)
+    th = np.where(flip[:, None, None], pw.transpose(0, 2, 1), pw).astype(np.float64)
+    node = model.unaries.astype(np.float64).copy()
+    np.add.at(node, lo, phi[:, 0].astype(np.float64))
+    np.add.at(node, hi, phi[:, 1].astype(np.float64))
+    assert np.abs(node - (U.astype(np.float64) + c)).max() <= (1e-4 if dtype == np.float32 else 1e-11)
+    edge = (th - phi[:, 0].astype(np.float64)[:, :, None] - phi[:, 1].astype(np.float64)[:, None, :]).reshape(len(e), -1).min(1)
+    ref = node.min(1).sum() + edge.sum()
+    assert abs(d - ref) <= 1e-12 * max(1.0, abs(ref)) * model.m
