@@ -23,7 +23,8 @@ LIB = os.path.join(HERE, "libmplpxx.so")
 LIB_ROCM = os.path.join(HERE, "libmplpxx_rocm.so")
 
 SOURCES = ["solver.cpp", "batch.cpp", "schedule.cpp", "handshake.hip", "dual.hip", "batch.hip", "adjoint.hip",
-           "rules.hip", "noalloc.hip", "probe.hip", "solo.hip"]
+           "rules.hip", "noalloc.hip", "probe.hip", "solo.hip",
+           "mb_tiles.hip"]
 ARCH = os.environ.get("MPLPXX_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -39,7 +40,8 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-Wno-unused-comman
 # reductions skip the quieting of their operands and fold into DPP forms;
 # on non-NaN operands the results are bitwise the same.
 EXTRA = {"handshake.hip": ["-fno-honor-nans"], "batch.hip": ["-fno-honor-nans"], "rules.hip": ["-fno-honor-nans"],
-         "solo.hip": ["-fno-honor-nans"], "adjoint.hip": ["-fno-honor-nans"]}
+         "solo.hip": ["-fno-honor-nans"], "adjoint.hip": ["-fno-honor-nans"],
+         "mb_tiles.hip": ["-fno-honor-nans"]}
 
 
 def _compile(src: str, build_dir: str = BUILD, defines=()) -> str:

@@ -88,19 +88,19 @@ __device__ __forceinline__ float join32_min(float a, float b) {
 template <int BC>
 __device__ __forceinline__ void col4_min_store(const float (&x)[BC], float* red, int cb, int lane) {
   const int k = lane >> 4;
-  if constexpr (BC == 1) {
-    const float m = col4_min(x[0]);
-    if (lane < 16) red[cb] = m;
-  } else if constexpr (BC == 2) {
-    // row blocks 0..3 end with columns 0, 1, 0, 1
-    const float m = pair16_min(x[0], x[1]);
-    const float f = join32_min(m, m);
-    if (lane < 32) red[cb * 2 + k] = f;
-  } else {
-    static_assert(BC % 4 == 0, "columns per lane");
+  constexpr int Q = BC / 4 * 4;  // columns in groups of four, then two, then one
 #pragma unroll
-    for (int g = 0; g < BC; g += 4)
-      red[cb * BC + g + k] = join32_min(pair16_min(x[g], x[g + 1]), pair16_min(x[g + 2], x[g + 3]));
+  for (int g = 0; g < Q; g += 4)
+    red[cb * BC + g + k] = join32_min(pair16_min(x[g], x[g + 1]), pair16_min(x[g + 2], x[g + 3]));
+  if constexpr (BC - Q >= 2) {
+    // row blocks 0..3 end with columns Q, Q + 1, Q, Q + 1
+    const float m = pair16_min(x[Q], x[Q + 1]);
+    const float f = join32_min(m, m);
+    if (lane < 32) red[cb * BC + Q + k] = f;
+  }
+  if constexpr (BC % 2 == 1) {
+    const float m = col4_min(x[BC - 1]);
+    if (lane < 16) red[cb * BC + BC - 1] = m;
   }
 }
 
@@ -380,7 +380,7 @@ __device__ __forceinline__ void mb_store(unsigned long long* p, unsigned long lo
 }
 
 template <int LT, int NT> struct SmemMB {
-  float uu[2][LT];   // centred (hi - c) + lo of U_u from the sync wave (double buffered by slot parity)
+  alignas(16) float uu[2][LT];   // centred (hi - c) + lo of U_u from the sync wave (double buffered by slot parity)
   float uv[2][LT];
   float uh[2][LT];   // hi of U_u
   float vh[2][LT];
@@ -586,30 +586,17 @@ __device__ __forceinline__ void gen_tile(const float* prm, float (&x)[TileShape<
 }
 
 // Messages of one slot for this thread's rows (into u) and columns (into v).
-template <int LT, int NT, bool PHI_LDS, bool FULL>
+// No clamping: padded labels read the following messages, the array's zeroed
+// tail or the tail of the LDS block, and their values are not used.
+template <int LT, int NT>
 __device__ __forceinline__ void load_phi(const float* src, int L, float (&pu)[TileShape<float, LT, NT>::BR],
                                          float (&pv)[TileShape<float, LT, NT>::BC]) {
   using S = TileShape<float, LT, NT>;
   const int rb = threadIdx.x >> 4, cb = threadIdx.x & 15;
-  if (PHI_LDS) {
 #pragma unroll
-    for (int i = 0; i < S::BR; ++i) {
-      const int s = rb * S::BR + i;
-      pu[i] = src[(FULL || s < L) ? s : L - 1];
-    }
+  for (int i = 0; i < S::BR; ++i) pu[i] = src[rb * S::BR + i];
 #pragma unroll
-    for (int jj = 0; jj < S::BC; ++jj) {
-      const int t = cb * S::BC + jj;
-      pv[jj] = src[L + ((FULL || t < L) ? t : L - 1)];
-    }
-  } else {
-    // global messages: no clamping (padded labels read the following
-    // messages or the allocation's zeroed tail; any finite value will do)
-#pragma unroll
-    for (int i = 0; i < S::BR; ++i) pu[i] = src[rb * S::BR + i];
-#pragma unroll
-    for (int jj = 0; jj < S::BC; ++jj) pv[jj] = src[L + cb * S::BC + jj];
-  }
+  for (int jj = 0; jj < S::BC; ++jj) pv[jj] = src[L + cb * S::BC + jj];
 }
 
 // Runs `iters` iterations over the slots first, first+stride, ... of one
@@ -750,7 +737,7 @@ __device__ __forceinline__ bool mb_run(const MbView& v_in, int first_in, int str
   PhiSet f0, f1, f2;
   auto load_phiset = [&](PhiSet& f, int jq) __attribute__((always_inline)) {
     const float* src = phi_of(first + jq * stride, jq);
-    load_phi<LT, NT, PHI_LDS, FULL>(src, L, f.pu, f.pv);
+    load_phi<LT, NT>(src, L, f.pu, f.pv);
     f.pvo = src[L + out_ic];  // (used by column lanes only)
   };
   // The messages of step q + DEPTH are last written by this workgroup at
@@ -824,18 +811,19 @@ __device__ __forceinline__ bool mb_run(const MbView& v_in, int first_in, int str
 #if MPLPXX_FINE_STAMPS
     if (v.stamps && last_iter && tid == 0) v.stamps[(size_t)slot * kStampStride + 5] = wall_clock64();
 #endif
-    // a' = centred U - phi; padded labels take the pads of kPadBig's comment
+    // a' = centred U - phi; padded labels (whose LDS words nobody wrote) take
+    // the pads of kPadBig's comment
     float av[S::BC], au[S::BR];
 #pragma unroll
     for (int jj = 0; jj < S::BC; ++jj) {
       const int t = cb * S::BC + jj;
-      const float x = sm.uv[parity][(FULL || t < L) ? t : L - 1] - pv[jj];
+      const float x = sm.uv[parity][t] - pv[jj];
       av[jj] = (FULL || t < L) ? x : kPadBig;
     }
 #pragma unroll
     for (int i = 0; i < S::BR; ++i) {
       const int s = rb * S::BR + i;
-      const float x = sm.uu[parity][(FULL || s < L) ? s : L - 1] - pu[i];
+      const float x = sm.uu[parity][s] - pu[i];
       au[i] = (FULL || s < L) ? x : 2.0f * kPadBig;
     }
     // the old value (hi, lo) and message of this lane's output; the shift

@@ -35,6 +35,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "mb_kernel.h"
 #include "step_common.h"
 #include "potts_mb.h"
 
@@ -265,34 +266,6 @@ __global__ void __launch_bounds__(NT) k_persistent(HsArgs<T> a, int iters) {
   }
 }
 
-template <int LT, int NT, bool PHI_LDS, bool FULL, bool TRACE, bool PHI_FAR, int DEPTH = (LT <= 64 ? 2 : 1),
-          int KIND = kCostDense, int RULE = MPLPXX_RULE_H>
-__global__ void __launch_bounds__(NT + 128) k_persistent_mb(HsArgs<float> a, unsigned long long* __restrict__ mb,
-                                                            int iters) {
-  __shared__ SmemMB<LT, NT> sm;
-  extern __shared__ float phi_lds[];
-  const int tid = threadIdx.x;
-  const int L = FULL ? LT : a.L;
-  const int G = gridDim.x;
-  if ((int)blockIdx.x >= a.m) return;
-  if (tid == 0) sm.abort_flag = 0;
-  if (PHI_LDS) {
-    for (int slot = blockIdx.x, j = 0; slot < a.m; slot += G, ++j)
-      for (int k = tid; k < 2 * L; k += NT + 128) phi_lds[j * 2 * L + k] = a.phi[(size_t)slot * 2 * L + k];
-  }
-  __syncthreads();
-  MbView v{a.tables, a.phi, mb, a.slots, a.deg, a.trace, a.trace_e, a.stamps, L, a.m, a.n, nullptr, nullptr,
-           a.sink + (size_t)blockIdx.x * (NT + 128), a.mbs};
-  if (!mb_run<LT, NT, PHI_LDS, FULL, TRACE, false, PHI_FAR, DEPTH, KIND, RULE>(v, blockIdx.x, G, iters, sm, phi_lds,
-                                                                         a.spin_limit, a.err))
-    return;
-  __syncthreads();
-  if (PHI_LDS) {
-    for (int slot = blockIdx.x, j = 0; slot < a.m; slot += G, ++j)
-      for (int k = tid; k < 2 * L; k += NT + 128) a.phi[(size_t)slot * 2 * L + k] = phi_lds[j * 2 * L + k];
-  }
-}
-
 // Potts models (one weight per slot, L <= 64): one compute wave in label
 // order plus the two sync waves (potts_mb.h)
 template <bool PHI_LDS, int KIND>
@@ -482,6 +455,9 @@ int max_blocks_per_cu_mb(int LT, int NT) {
 
 hipError_t launch_persistent_mb(const HsArgs<float>& a, unsigned long long* mb, int LT, int NT, int grid, int iters,
                                 int phi_in_lds, size_t dyn_lds, hipStream_t st, int prefetch, int kind, int rule) {
+  if (phi_in_lds) dyn_lds += kPhiLdsTail;
+  if (NT == 256 && kind == kCostDense && rule == MPLPXX_RULE_H && !a.trace && prefetch != 1 && mb_odd_tile(a.L))
+    return launch_mb_odd(a, mb, grid, iters, phi_in_lds, dyn_lds, st);
 #define MPLPXX_CASE(lt, nt) \
   if (LT == lt && NT == nt) return launch_mb_one<lt, nt>(a, mb, grid, iters, phi_in_lds, dyn_lds, st, prefetch, kind, rule);
   MPLPXX_CASE(16, 64)
@@ -506,6 +482,7 @@ int max_blocks_per_cu_mb_potts() {
 
 hipError_t launch_persistent_mb_potts(const HsArgs<float>& a, unsigned long long* mb, int grid, int iters,
                                       int phi_in_lds, size_t dyn_lds, hipStream_t st, int kind) {
+  if (phi_in_lds) dyn_lds += kPhiLdsTail;
   void* args[] = {(void*)&a, (void*)&mb, (void*)&iters};
   const void* f = kind == MPLPXX_COST_TRUNC_QUAD
                       ? (phi_in_lds ? (const void*)k_persistent_mb_potts<true, MPLPXX_COST_TRUNC_QUAD>
