@@ -227,8 +227,8 @@ hipError_t launch_decode(const T* unaries, const T* tables, const T* phi, const 
                          double* energy, int* err, long long spin_limit, hipStream_t st, int potts = 0);
 template <typename T>
 hipError_t launch_check_finite(const T* p, size_t count, int* flag, hipStream_t st);
-template <typename T>
-hipError_t launch_pack_tables(const T* src, T* dst, const int* slot_edge, const int* slot_flip, int m, int L,
+template <typename S, typename D>
+hipError_t launch_pack_tables(const S* src, D* dst, const int* slot_edge, const int* slot_flip, int m, int L,
                               hipStream_t st);
 template <typename T>
 hipError_t launch_phi_by_edge(const T* phi_slot, const int* slot_of_edge, int m, int L, T* out, hipStream_t st);

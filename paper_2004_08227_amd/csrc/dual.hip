@@ -420,26 +420,30 @@ hipError_t launch_check_finite(const T* p, size_t count, int* flag, hipStream_t 
 }
 
 // dst slot i <- src edge slot_edge[i], transposed when slot_flip[i]
-template <typename T>
-__global__ void k_pack_tables(const T* __restrict__ src, T* __restrict__ dst, const int* __restrict__ slot_edge,
-                              const int* __restrict__ slot_flip, int L) {
+template <typename S, typename D>
+__global__ void __launch_bounds__(256) k_pack_tables(const S* __restrict__ src, D* __restrict__ dst,
+                                                     const int* __restrict__ slot_edge,
+                                                     const int* __restrict__ slot_flip, int L) {
   const int slot = blockIdx.x;
-  const T* s = src + (size_t)slot_edge[slot] * L * L;
-  T* d = dst + (size_t)slot * L * L;
+  const S* s = src + (size_t)slot_edge[slot] * L * L;
+  D* d = dst + (size_t)slot * L * L;
   const bool flip = slot_flip[slot] != 0;
-  for (int i = threadIdx.x; i < L * L; i += blockDim.x) {
+  for (int i = threadIdx.x; i < L * L; i += 256) {
     const int r = i / L, c = i - r * L;
-    d[i] = flip ? s[(size_t)c * L + r] : s[i];
+    d[i] = (D)(flip ? s[(size_t)c * L + r] : s[i]);
   }
 }
 
-template <typename T>
-hipError_t launch_pack_tables(const T* src, T* dst, const int* slot_edge, const int* slot_flip, int m, int L,
+template <typename S, typename D>
+hipError_t launch_pack_tables(const S* src, D* dst, const int* slot_edge, const int* slot_flip, int m, int L,
                               hipStream_t st) {
   if (m == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_pack_tables<T>, dim3(m), dim3(256), 0, st, src, dst, slot_edge, slot_flip, L);
+  hipLaunchKernelGGL((k_pack_tables<S, D>), dim3(m), dim3(256), 0, st, src, dst, slot_edge, slot_flip, L);
   return hipGetLastError();
 }
+template hipError_t launch_pack_tables<float, float>(const float*, float*, const int*, const int*, int, int, hipStream_t);
+template hipError_t launch_pack_tables<double, double>(const double*, double*, const int*, const int*, int, int, hipStream_t);
+template hipError_t launch_pack_tables<double, float>(const double*, float*, const int*, const int*, int, int, hipStream_t);
 
 // messages in the caller's edge order from slot order
 template <typename T>
@@ -501,8 +505,7 @@ hipError_t launch_fill_int(int* p, int value, size_t count, hipStream_t st) {
                                        int, int, int*, int*, double*, double*, double*, int*, long long,           \
                                        hipStream_t, int);                                                          \
   template hipError_t launch_phi_by_edge<T>(const T*, const int*, int, int, T*, hipStream_t);                      \
-  template hipError_t launch_check_finite<T>(const T*, size_t, int*, hipStream_t);                                 \
-  template hipError_t launch_pack_tables<T>(const T*, T*, const int*, const int*, int, int, hipStream_t);
+  template hipError_t launch_check_finite<T>(const T*, size_t, int*, hipStream_t);
 MPLPXX_INST(float)
 MPLPXX_INST(double)
 #undef MPLPXX_INST

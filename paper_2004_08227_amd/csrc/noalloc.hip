@@ -186,7 +186,7 @@ extern "C" int mplpxx_solve_noalloc(int32_t n, int32_t L, int64_t m, const int32
   HIP_TRY(launch_check_finite<float>(unaries_dev, nL, d_err + 7, st));
   if (m > 0) HIP_TRY(launch_check_finite<float>(pairwise_dev, mLL, d_err + 7, st));
   HIP_TRY(hipMemcpyAsync(U_dev, unaries_dev, nL * sizeof(float), hipMemcpyDeviceToDevice, st));
-  if (m > 0) HIP_TRY(launch_pack_tables<float>(pairwise_dev, d_tab, d_se, d_sf, (int)m, L, st));
+  if (m > 0) HIP_TRY(launch_pack_tables(pairwise_dev, d_tab, d_se, d_sf, (int)m, L, st));
   HIP_TRY(hipStreamSynchronize(st));  // (the host vectors above go out of scope)
   int flag = 0;
   HIP_TRY(hipMemcpy(&flag, d_err + 7, sizeof(int), hipMemcpyDeviceToHost));

@@ -87,6 +87,8 @@ struct mplpxx_solver {
   int adj_rec_from = 0;                   // segments from this one on have their records (persistent path)
   bool adj_ready = false;
   long long adj_iter_mark = -1;           // `iterations` right after the forward
+  char* d_adj = nullptr;                  // the allocation that the next eight are parts of
+  size_t adj_size = 0;
   void* d_ck_U = nullptr;                 // [nck + 1][n][L] (last = final state)
   float* d_ck_Ulo = nullptr;              // FP32: [nck + 1][n][L] corrections
   void* d_ck_phi = nullptr;               // [nck + 1][m][2][L]
@@ -195,10 +197,9 @@ struct mplpxx_solver {
 namespace {
 
 void free_all(mplpxx_solver* h) {
-  void* ptrs[] = {h->d_tables, h->d_phi, h->d_U, h->d_Ulo, h->d_ck_Ulo, h->d_unaries, h->d_slots, h->d_deg, h->d_ver, h->d_err,
+  void* ptrs[] = {h->d_tables, h->d_phi, h->d_U, h->d_Ulo, h->d_adj, h->d_unaries, h->d_slots, h->d_deg, h->d_ver, h->d_err,
                   h->d_node_ptr, h->d_inc, h->d_node_min, h->d_edge_min, h->d_scalar, h->d_labels,
-                  h->d_trace_nodes, h->d_trace_out, h->d_trace_e, h->d_mb, h->d_sink, h->d_stamps, h->d_ck_U, h->d_ck_phi,
-                  h->d_rec, h->d_Ub, h->d_pb, h->d_thb, h->d_slot_of_edge, h->d_edge_flip, h->d_export, h->d_mb64, h->d_sink64, h->d_contrib};
+                  h->d_trace_nodes, h->d_trace_out, h->d_trace_e, h->d_mb, h->d_sink, h->d_stamps, h->d_slot_of_edge, h->d_edge_flip, h->d_export, h->d_mb64, h->d_sink64};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (h->ev0) (void)hipEventDestroy(h->ev0);
@@ -253,7 +254,9 @@ bool is_device_memory(const void* p, int dev) {
 
 int create_impl(int32_t n, int32_t L, int64_t m, const int32_t* edges, const void* unaries, const void* pairwise,
                 int32_t dtype, bool device_costs, hipStream_t copy_stream, mplpxx_solver** out,
-                int32_t sched = MPLPXX_SCHED_AUTO, int potts = 0) {
+                int32_t sched = MPLPXX_SCHED_AUTO, int potts = 0, const mplpxx_solver* twin_of = nullptr) {
+  // (twin_of: an FP64 handle with that FP32 handle's graph and costs, whatever
+  // edges, unaries and pairwise say)
   if (!out) return fail(MPLPXX_EINVAL, "out is NULL");
   *out = nullptr;
   if (dtype != MPLPXX_F32 && dtype != MPLPXX_F64) return fail(MPLPXX_EINVAL, "unknown dtype %d", dtype);
@@ -261,10 +264,10 @@ int create_impl(int32_t n, int32_t L, int64_t m, const int32_t* edges, const voi
   if (L < 1 || L > MPLPXX_MAX_LABELS) return fail(MPLPXX_EINVAL, "L must be in [1, %d] (got %d)", MPLPXX_MAX_LABELS, L);
   if (m < 0 || m > (int64_t)n * (n - 1) / 2) return fail(MPLPXX_EINVAL, "m must be in [0, n(n-1)/2] (got %lld)", (long long)m);
   if (m > 0x3fffffff) return fail(MPLPXX_EINVAL, "too many edges");
-  if (!unaries) return fail(MPLPXX_EINVAL, "unaries is NULL");
+  if (!unaries && !twin_of) return fail(MPLPXX_EINVAL, "unaries is NULL");
   if (sched != MPLPXX_SCHED_AUTO && sched != MPLPXX_SCHED_GREEDY && sched != MPLPXX_SCHED_COLOR)
     return fail(MPLPXX_EINVAL, "unknown schedule kind %d", sched);
-  if (m > 0 && (!edges || !pairwise)) return fail(MPLPXX_EINVAL, "edges/pairwise is NULL");
+  if (m > 0 && !twin_of && (!edges || !pairwise)) return fail(MPLPXX_EINVAL, "edges/pairwise is NULL");
   if (potts && !known_cost_kind(potts)) return fail(MPLPXX_EINVAL, "unknown cost kind %d", potts);
   if (potts && (dtype != MPLPXX_F32 || device_costs)) return fail(MPLPXX_EINVAL, "structured costs take FP32 host costs");
   if (potts && L > 64) return fail(MPLPXX_EINVAL, "structured costs take L <= 64 (got %d)", L);
@@ -284,10 +287,22 @@ int create_impl(int32_t n, int32_t L, int64_t m, const int32_t* edges, const voi
   h->esz = esz;
   h->sched = sched;
   h->potts = potts;
-  int rc = prepare_solver_graph(h, edges);
-  if (rc != MPLPXX_OK) {
-    delete h;
-    return rc;
+  if (twin_of) {
+    h->S = twin_of->S;
+    h->step_ptr = twin_of->step_ptr;
+    h->order = twin_of->order;
+    h->slot_of_edge = twin_of->slot_of_edge;
+    h->slots = twin_of->slots;
+    h->flip = twin_of->flip;
+    h->deg = twin_of->deg;
+    h->max_deg = twin_of->max_deg;
+    h->max_step = twin_of->max_step;
+  } else {
+    const int rc = prepare_solver_graph(h, edges);
+    if (rc != MPLPXX_OK) {
+      delete h;
+      return rc;
+    }
   }
   if (potts && h->max_deg >= 65536) {
     delete h;
@@ -309,7 +324,7 @@ int create_impl(int32_t n, int32_t L, int64_t m, const int32_t* edges, const voi
   } while (0)
   int dev = 0;
   TRY(hipGetDevice(&dev));
-  if (device_costs && (!is_device_memory(unaries, dev) || (m > 0 && !is_device_memory(pairwise, dev)))) {
+  if (device_costs && !twin_of && (!is_device_memory(unaries, dev) || (m > 0 && !is_device_memory(pairwise, dev)))) {
     fail(MPLPXX_EINVAL, "unaries/pairwise must be device memory of the current device %d", dev);
     return bail(MPLPXX_EINVAL);
   }
@@ -363,7 +378,12 @@ int create_impl(int32_t n, int32_t L, int64_t m, const int32_t* edges, const voi
   TRY(hipMemsetAsync(static_cast<char*>(h->d_tables) + mLL * esz, 0, kTailPad * esz, st));
   TRY(hipMemsetAsync(h->d_err, 0, 8 * sizeof(int), st));
 
-  if (!device_costs) {
+  if (twin_of) {
+    TRY(hipStreamSynchronize(twin_of->stream()));
+    TRY(launch_convert(static_cast<const float*>(twin_of->d_unaries), static_cast<double*>(h->d_unaries), nL, st));
+    TRY(launch_convert(static_cast<const float*>(twin_of->d_tables), static_cast<double*>(h->d_tables), mLL, st));
+    TRY(hipStreamSynchronize(st));  // (the host vectors above go out of scope)
+  } else if (!device_costs) {
     TRY(hipMemcpyAsync(h->d_unaries, unaries, nL * esz, hipMemcpyHostToDevice, st));
     if (m) {
       // pack tables in slot order, transposing edges given as (v, u)
@@ -423,9 +443,9 @@ int create_impl(int32_t n, int32_t L, int64_t m, const int32_t* edges, const voi
       TRY(hipMemcpyAsync(d_se, se.data(), m * sizeof(int), hipMemcpyHostToDevice, cs));
       TRY(hipMemcpyAsync(d_sf, sf.data(), m * sizeof(int), hipMemcpyHostToDevice, cs));
       if (dtype == MPLPXX_F32)
-        TRY(launch_pack_tables<float>((const float*)pairwise, (float*)h->d_tables, d_se, d_sf, h->m, L, cs));
+        TRY(launch_pack_tables((const float*)pairwise, (float*)h->d_tables, d_se, d_sf, h->m, L, cs));
       else
-        TRY(launch_pack_tables<double>((const double*)pairwise, (double*)h->d_tables, d_se, d_sf, h->m, L, cs));
+        TRY(launch_pack_tables((const double*)pairwise, (double*)h->d_tables, d_se, d_sf, h->m, L, cs));
     }
     int flag = 0;
     TRY(hipMemcpyAsync(&flag, d_flag, sizeof(int), hipMemcpyDeviceToHost, cs));
@@ -690,21 +710,36 @@ template <typename T> int adjoint_forward_t(mplpxx_solver* h, int K, int every, 
   const size_t nL = (size_t)h->n * h->L, mp = (size_t)h->m * 2 * h->L, esz = sizeof(T);
   const int nck = (int)(((long long)K + every - 1) / every);  // (64-bit: K + every can pass 2^31)
   const bool pers = adjoint_persistent<T>(h);
-  // (re)allocate checkpoint and record storage
-  for (void** p : {&h->d_ck_U, &h->d_ck_phi, (void**)&h->d_rec, (void**)&h->d_ck_Ulo, (void**)&h->d_contrib})
-    if (*p) { (void)hipFree(*p); *p = nullptr; }
-  if (pers) {
-    HIP_TRY(ensure_mb64(h));
-    HIP_TRY(hipMalloc(&h->d_contrib, (size_t)every * h->m * 3 * h->L * sizeof(double)));
-  }
+  if (pers) HIP_TRY(ensure_mb64(h));
   const size_t rec_bytes = (pers ? 2 : 1) * (size_t)every * h->m * 3 * h->L;
-  HIP_TRY(hipMalloc(&h->d_ck_U, (nck + 1) * nL * esz));
-  if (h->d_Ulo) HIP_TRY(hipMalloc((void**)&h->d_ck_Ulo, (nck + 1) * nL * sizeof(float)));
-  HIP_TRY(hipMalloc(&h->d_ck_phi, std::max<size_t>(1, (nck + 1) * mp * esz)));
-  HIP_TRY(hipMalloc(&h->d_rec, std::max<size_t>(1, rec_bytes)));
-  if (!h->d_Ub) HIP_TRY(hipMalloc(&h->d_Ub, nL * esz));
-  if (!h->d_pb) HIP_TRY(hipMalloc(&h->d_pb, std::max<size_t>(1, mp * esz)));
-  if (!h->d_thb) HIP_TRY(hipMalloc(&h->d_thb, std::max<size_t>(1, (size_t)h->m * h->L * h->L * esz)));
+  // Checkpoints, records and adjoints are parts of one allocation, kept while
+  // the next forward needs the same size (a large hipMalloc or hipFree takes
+  // about 0.25 ms).
+  size_t used = 0;
+  auto part = [&](size_t bytes) {
+    const size_t at = used;
+    used += (std::min(bytes, (size_t)1 << 56) + 255) / 256 * 256;  // (a sum that cannot wrap: too much is refused)
+    return at;
+  };
+  const size_t o_U = part((nck + 1) * nL * esz), o_lo = part(h->d_Ulo ? (nck + 1) * nL * sizeof(float) : 0),
+               o_phi = part((nck + 1) * mp * esz), o_rec = part(rec_bytes), o_Ub = part(nL * esz), o_pb = part(mp * esz),
+               o_thb = part((size_t)h->m * h->L * h->L * esz),
+               o_contrib = part(pers ? (size_t)every * h->m * 3 * h->L * sizeof(double) : 0);
+  if (h->adj_size != used || !h->d_adj) {
+    if (h->d_adj) (void)hipFree(h->d_adj);
+    h->d_adj = nullptr;
+    h->adj_size = 0;
+    HIP_TRY(hipMalloc(&h->d_adj, std::max<size_t>(1, used)));
+    h->adj_size = used;
+  }
+  h->d_ck_U = h->d_adj + o_U;
+  h->d_ck_Ulo = h->d_Ulo ? reinterpret_cast<float*>(h->d_adj + o_lo) : nullptr;
+  h->d_ck_phi = h->d_adj + o_phi;
+  h->d_rec = reinterpret_cast<unsigned char*>(h->d_adj + o_rec);
+  h->d_Ub = h->d_adj + o_Ub;
+  h->d_pb = h->d_adj + o_pb;
+  h->d_thb = h->d_adj + o_thb;
+  h->d_contrib = pers ? reinterpret_cast<double*>(h->d_adj + o_contrib) : nullptr;
   h->adj_bytes = (nck + 1) * nL * esz + (h->d_Ulo ? (nck + 1) * nL * sizeof(float) : 0) + (nck + 1) * mp * esz +
                  rec_bytes + nL * esz + mp * esz + (size_t)h->m * h->L * h->L * esz + (size_t)h->m * 2 * sizeof(int) +
                  (pers ? 2 * nL * 2 * sizeof(unsigned long long) + (size_t)every * h->m * 3 * h->L * sizeof(double) : 0);
@@ -762,7 +797,9 @@ template <typename T> int adjoint_forward_t(mplpxx_solver* h, int K, int every, 
   return MPLPXX_OK;
 }
 
-template <typename T> int adjoint_backward_t(mplpxx_solver* h, void* grad_u, void* grad_pw) {
+// gradients into the caller's buffers of type O (FP32 handles differentiating
+// their FP64 twin: float from double)
+template <typename T, typename O> int adjoint_backward_t(mplpxx_solver* h, O* grad_u, O* grad_pw) {
   hipStream_t st = h->stream();
   const size_t nL = (size_t)h->n * h->L, mp = (size_t)h->m * 2 * h->L, esz = sizeof(T);
   const int K = h->adj_K, every = h->adj_every, nck = h->adj_nck;
@@ -832,10 +869,15 @@ template <typename T> int adjoint_backward_t(mplpxx_solver* h, void* grad_u, voi
                                    static_cast<T*>(h->d_thb), st));
   }
   // outputs in the caller's layout; the handle's state back to the forward's end
-  if (grad_u) HIP_TRY(hipMemcpyAsync(grad_u, h->d_Ub, nL * esz, hipMemcpyDeviceToDevice, st));
+  if (grad_u) {
+    if constexpr (sizeof(T) == sizeof(O))
+      HIP_TRY(hipMemcpyAsync(grad_u, h->d_Ub, nL * esz, hipMemcpyDeviceToDevice, st));
+    else
+      HIP_TRY(launch_convert(static_cast<const T*>(h->d_Ub), grad_u, nL, st));
+  }
   if (grad_pw && h->m)
-    HIP_TRY(launch_pack_tables<T>(static_cast<const T*>(h->d_thb), static_cast<T*>(grad_pw), h->d_slot_of_edge,
-                                  h->d_edge_flip, h->m, h->L, st));
+    HIP_TRY(launch_pack_tables(static_cast<const T*>(h->d_thb), grad_pw, h->d_slot_of_edge, h->d_edge_flip, h->m, h->L,
+                               st));
   HIP_TRY(hipMemcpyAsync(h->d_U, (char*)h->d_ck_U + nck * nL * esz, nL * esz, hipMemcpyDeviceToDevice, st));
   if (lo) HIP_TRY(hipMemcpyAsync(lo, ck_lo + nck * nL, nL * esz, hipMemcpyDeviceToDevice, st));
   if (h->m) HIP_TRY(hipMemcpyAsync(h->d_phi, (char*)h->d_ck_phi + nck * mp * esz, mp * esz, hipMemcpyDeviceToDevice, st));
@@ -846,47 +888,10 @@ template <typename T> int adjoint_backward_t(mplpxx_solver* h, void* grad_u, voi
 }  // namespace
 
 namespace {
-// FP64 twin of an FP32 handle: the same graph and costs widened exactly, in
-// the caller's layout (tables unpacked from slot order), created on the
-// handle's stream
+// FP64 twin of an FP32 handle: the same graph, schedule and slots, costs widened
+// exactly from the handle's own arrays
 int make_shadow(mplpxx_solver* h) {
-  hipStream_t st = h->stream();
-  const size_t nL = (size_t)h->n * h->L, mLL = (size_t)h->m * h->L * h->L;
-  std::vector<int32_t> edges(2 * (size_t)h->m);
-  for (int e = 0; e < h->m; ++e) {
-    const SlotInfo& si = h->slots[h->slot_of_edge[e]];
-    edges[2 * e] = h->flip[e] ? si.v : si.u;
-    edges[2 * e + 1] = h->flip[e] ? si.u : si.v;
-  }
-  double* u64 = nullptr;
-  double* t64 = nullptr;
-  double* p64 = nullptr;
-  int* d_soe = nullptr;
-  int* d_flip = nullptr;
-  auto cleanup = [&]() {
-    for (void* p : {(void*)u64, (void*)t64, (void*)p64, (void*)d_soe, (void*)d_flip})
-      if (p) (void)hipFree(p);
-  };
-  hipError_t e = hipMalloc(&u64, std::max<size_t>(1, nL) * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(&t64, std::max<size_t>(1, mLL) * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(&p64, std::max<size_t>(1, mLL) * sizeof(double));
-  if (e == hipSuccess && h->m) e = hipMalloc(&d_soe, h->m * sizeof(int));
-  if (e == hipSuccess && h->m) e = hipMalloc(&d_flip, h->m * sizeof(int));
-  if (e == hipSuccess && h->m)
-    e = hipMemcpyAsync(d_soe, h->slot_of_edge.data(), h->m * sizeof(int), hipMemcpyHostToDevice, st);
-  if (e == hipSuccess && h->m) e = hipMemcpyAsync(d_flip, h->flip.data(), h->m * sizeof(int), hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) e = launch_convert(static_cast<const float*>(h->d_unaries), u64, nL, st);
-  if (e == hipSuccess && h->m) e = launch_convert(static_cast<const float*>(h->d_tables), t64, mLL, st);
-  if (e == hipSuccess && h->m) e = launch_pack_tables<double>(t64, p64, d_soe, d_flip, h->m, h->L, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  if (e != hipSuccess) {
-    cleanup();
-    return fail(e == hipErrorOutOfMemory ? MPLPXX_ENOMEM : MPLPXX_EDEVICE, "FP64 twin: %s", hipGetErrorString(e));
-  }
-  const int rc = create_impl(h->n, h->L, h->m, h->m ? edges.data() : nullptr, u64, h->m ? p64 : nullptr, MPLPXX_F64,
-                             true, st, &h->shadow, h->sched);
-  cleanup();
-  return rc;
+  return create_impl(h->n, h->L, h->m, nullptr, nullptr, nullptr, MPLPXX_F64, true, nullptr, &h->shadow, h->sched, 0, h);
 }
 
 // nearest bf16 value, ties to even (the rounding the device applies to U_comp)
@@ -987,32 +992,14 @@ int mplpxx_adjoint_backward(mplpxx_solver* h, void* grad_unaries, void* grad_pai
   if (!h->adj_ready || h->iterations != h->adj_iter_mark)
     return fail(MPLPXX_ESTATE, "no adjoint forward to differentiate (call mplpxx_adjoint_forward first)");
   if (h->dtype == MPLPXX_F32 && h->adjoint_f64) {
-    // FP64 gradients of the twin, narrowed into the caller's FP32 buffers
-    hipStream_t st = h->stream();
-    const size_t nL = (size_t)h->n * h->L, mLL = (size_t)h->m * h->L * h->L;
-    double* gu = nullptr;
-    double* gp = nullptr;
-    HIP_TRY(hipMalloc(&gu, std::max<size_t>(1, nL) * sizeof(double)));
-    if (hipMalloc(&gp, std::max<size_t>(1, mLL) * sizeof(double)) != hipSuccess) {
-      (void)hipFree(gu);
-      return fail(MPLPXX_ENOMEM, "gradient buffers");
-    }
-    int rc = adjoint_backward_t<double>(h->shadow, grad_unaries ? gu : nullptr, grad_pairwise ? gp : nullptr);
-    hipError_t e = hipSuccess;
-    if (rc == MPLPXX_OK) {
-      HIP_TRY(hipStreamSynchronize(h->shadow->stream()));
-      if (grad_unaries) e = launch_convert(gu, static_cast<float*>(grad_unaries), nL, st);
-      if (e == hipSuccess && grad_pairwise && mLL) e = launch_convert(gp, static_cast<float*>(grad_pairwise), mLL, st);
-      if (e == hipSuccess) e = hipStreamSynchronize(st);
-    }
-    (void)hipFree(gu);
-    (void)hipFree(gp);
-    if (rc != MPLPXX_OK) return rc;
-    if (e != hipSuccess) return fail(MPLPXX_EDEVICE, "gradient narrowing: %s", hipGetErrorString(e));
-    return MPLPXX_OK;
+    // FP64 gradients of the twin, narrowed into the caller's FP32 buffers on
+    // the twin's stream, after what the handle's stream still has to do
+    HIP_TRY(hipStreamSynchronize(h->stream()));
+    return adjoint_backward_t<double>(h->shadow, static_cast<float*>(grad_unaries), static_cast<float*>(grad_pairwise));
   }
-  return h->dtype == MPLPXX_F32 ? adjoint_backward_t<float>(h, grad_unaries, grad_pairwise)
-                                : adjoint_backward_t<double>(h, grad_unaries, grad_pairwise);
+  return h->dtype == MPLPXX_F32 ? adjoint_backward_t<float>(h, static_cast<float*>(grad_unaries), static_cast<float*>(grad_pairwise))
+                                : adjoint_backward_t<double>(h, static_cast<double*>(grad_unaries),
+                                                             static_cast<double*>(grad_pairwise));
 }
 
 int mplpxx_dual_bound(mplpxx_solver* h, double* out) {
