@@ -24,7 +24,7 @@ LIB_ROCM = os.path.join(HERE, "libmplpxx_rocm.so")
 
 SOURCES = ["solver.cpp", "batch.cpp", "schedule.cpp", "handshake.hip", "dual.hip", "batch.hip", "adjoint.hip",
            "rules.hip", "noalloc.hip", "probe.hip", "solo.hip",
-           "mb_tiles.hip"]
+           "mb_tiles.hip", "adj_pair.hip"]
 ARCH = os.environ.get("MPLPXX_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -34,14 +34,13 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-Wno-unused-comman
 
 
 # The handshake kernels see no NaN: inputs are validated finite (FP32:
-# |cost| <= 1e18), padded tile entries are +inf (per-matching engine) or
-# 2^126 (mailbox and wave engines), padded labels of the structured passes
+# |cost| <= 1e18), padded tile entries are +inf or 2^126, padded labels of the structured passes
 # +inf, and no pass can form inf - inf.  Telling the compiler so lets min
 # reductions skip the quieting of their operands and fold into DPP forms;
 # on non-NaN operands the results are bitwise the same.
 EXTRA = {"handshake.hip": ["-fno-honor-nans"], "batch.hip": ["-fno-honor-nans"], "rules.hip": ["-fno-honor-nans"],
          "solo.hip": ["-fno-honor-nans"], "adjoint.hip": ["-fno-honor-nans"],
-         "mb_tiles.hip": ["-fno-honor-nans"]}
+         "mb_tiles.hip": ["-fno-honor-nans"], "adj_pair.hip": ["-fno-honor-nans"]}
 
 
 def _compile(src: str, build_dir: str = BUILD, defines=()) -> str:

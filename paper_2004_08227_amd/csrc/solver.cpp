@@ -175,13 +175,13 @@ struct mplpxx_solver {
            (threads_opt == 0 || threads_opt == 256);
   }
   bool mb_engine() const { return dtype == MPLPXX_F32 && engine() == ENGINE_PERSISTENT; }
-  // small models on one workgroup (solo.h), where no option asks for one of
-  // the other engines' ways
-  bool solo(bool trace) const {
+  // no option asks for one of the engines' ways
+  bool plain() const {
     return rule == MPLPXX_RULE_H && !potts && engine_opt == ENGINE_AUTO && threads_opt == 0 && grid_opt == 0 &&
-           phi_opt == 0 && prefetch_opt == 0 && !profile && spin_limit == kSpinDefault && max_deg < 65536 &&
-           solo_fits(n, L, m, S, max_step, esz, trace);
+           phi_opt == 0 && prefetch_opt == 0 && !profile && spin_limit == kSpinDefault && max_deg < 65536;
   }
+  // small models on one workgroup (solo.h)
+  bool solo(bool trace) const { return plain() && solo_fits(n, L, m, S, max_step, esz, trace); }
   int grid() const {
     int g = grid_opt > 0 ? grid_opt : num_cus;
     if (grid_opt == 0 && (mb_engine() || rule_mailbox()))
@@ -545,6 +545,17 @@ template <typename T> SoloArgs<T> solo_args(mplpxx_solver* h, double* trace) {
                      reinterpret_cast<T*>(h->d_Ulo), h->d_slots, trace, h->d_trace_e, h->L, h->m, h->n, h->S};
 }
 
+// scratch words of the FP32 mailbox engine
+hipError_t ensure_sink(mplpxx_solver* h, size_t words) {
+  if (h->sink_words >= words) return hipSuccess;
+  if (h->d_sink) (void)hipFree(h->d_sink);
+  h->d_sink = nullptr;
+  h->sink_words = 0;
+  const hipError_t e = hipMalloc(&h->d_sink, words * sizeof(unsigned long long));
+  if (e == hipSuccess) h->sink_words = words;
+  return e;
+}
+
 // mailboxes (of the unaries, then of their adjoints) and scratch words of the
 // FP64 mailbox engine
 hipError_t ensure_mb64(mplpxx_solver* h) {
@@ -615,14 +626,7 @@ template <typename T> int iterate_t(mplpxx_solver* h, int k, double* trace_host)
         trace_w = NT / 64;
       }
       const int G = h->grid();
-      const size_t words = (size_t)G * (NT + 128);
-      if (h->sink_words < words) {
-        if (h->d_sink) (void)hipFree(h->d_sink);
-        h->d_sink = nullptr;
-        h->sink_words = 0;
-        HIP_TRY(hipMalloc(&h->d_sink, words * sizeof(unsigned long long)));
-        h->sink_words = words;
-      }
+      HIP_TRY(ensure_sink(h, (size_t)G * (NT + 128)));
       a.sink = h->d_sink;
       a.mbs = mb_row_words(h->L);
       const size_t owned = ((size_t)h->m + G - 1) / G;
@@ -705,7 +709,57 @@ int fwd64_segment(mplpxx_solver* h, int seg, unsigned char* rec) {
   return rc;
 }
 
-template <typename T> int adjoint_forward_t(mplpxx_solver* h, int K, int every, double* loss) {
+// The FP32 run of `h` beside its FP64 twin's in one launch (adj_pair.hip),
+// where each half of the chip holds a whole matching and both runs would use
+// the mailbox engines in their default ways: the FP32 run is then free.  A
+// larger matching would take two rounds in half a chip.
+int pair_grid(const mplpxx_solver* h) {
+  const int half = h->num_cus / 2;
+  return std::max(1, std::min(h->m, mb_default_grid(std::min(h->max_step, half), half, h->m, h->L, [] { return 1; })));
+}
+bool adjoint_paired(const mplpxx_solver* h) {
+  const int half = h->num_cus / 2;
+  return h->plain() && h->max_step <= half && h->m > 0 && adjoint_persistent<double>(h->shadow) && !h->solo(false) &&
+         !h->shadow->solo(false) && adj_pair_fits(h->m, h->L, fwd64_grid(h->shadow, half), pair_grid(h));
+}
+// the FP32 handle's state at phi = 0, on stream `st`
+hipError_t clear_state32(mplpxx_solver* h, hipStream_t st) {
+  const size_t nL = (size_t)h->n * h->L;
+  hipError_t e = hipMemsetAsync(h->d_phi, 0, (size_t)h->m * 2 * h->L * sizeof(float), st);
+  if (e == hipSuccess) e = hipMemcpyAsync(h->d_U, h->d_unaries, nL * sizeof(float), hipMemcpyDeviceToDevice, st);
+  if (e == hipSuccess) e = hipMemsetAsync(h->d_Ulo, 0, nL * sizeof(float), st);
+  return e;
+}
+// `seg` iterations of both, on the twin's stream
+int pair_segment(mplpxx_solver* h, mplpxx_solver* h32, int seg, unsigned char* rec) {
+  hipStream_t st = h->stream();
+  Fwd64Args f{};
+  HIP_TRY(fwd64_args(h, seg, &f));
+  f.grid = fwd64_grid(h, h->num_cus / 2);
+  f.rec = rec;
+  const int G = pair_grid(h32);
+  HIP_TRY(ensure_sink(h32, (size_t)G * (kPairNT + 128)));
+  HsArgs<float> a = hs_args<float>(h32, nullptr);
+  a.sink = h32->d_sink;
+  a.mbs = mb_row_words(h32->L);
+  HIP_TRY(launch_mb64_init(static_cast<const double*>(h->d_U), h->d_mb64, h->n, h->L, st));
+  HIP_TRY(launch_mb_init(static_cast<const float*>(h32->d_U), h32->d_Ulo, h32->d_mb, h32->n, h32->L, a.mbs, st));
+  HIP_TRY(launch_adj_pair(f, a, h32->d_mb, G, st));
+  HIP_TRY(launch_mb64_fini(static_cast<double*>(h->d_U), h->d_mb64, h->n, h->L, nullptr, st));
+  HIP_TRY(launch_mb_fini(static_cast<float*>(h32->d_U), h32->d_Ulo, h32->d_mb, h32->n, h32->L, a.mbs, nullptr, st));
+  int rc = sync_and_check(h);
+  const int rc32 = sync_and_check(h32);  // (clears its error words, whatever the other run ended with)
+  if (rc == MPLPXX_OK) rc = rc32;
+  if (rc == MPLPXX_OK) {
+    h->iterations += seg;
+    h32->iterations += seg;
+  }
+  return rc;
+}
+
+// beside: the FP32 handle whose own run of K iterations from phi = 0 goes along
+template <typename T>
+int adjoint_forward_t(mplpxx_solver* h, int K, int every, double* loss, mplpxx_solver* beside = nullptr) {
   hipStream_t st = h->stream();
   const size_t nL = (size_t)h->n * h->L, mp = (size_t)h->m * 2 * h->L, esz = sizeof(T);
   const int nck = (int)(((long long)K + every - 1) / every);  // (64-bit: K + every can pass 2^31)
@@ -754,6 +808,12 @@ template <typename T> int adjoint_forward_t(mplpxx_solver* h, int K, int every, 
   HIP_TRY(hipMemcpyAsync(h->d_U, h->d_unaries, nL * esz, hipMemcpyDeviceToDevice, st));
   if (h->d_Ulo) HIP_TRY(hipMemsetAsync(h->d_Ulo, 0, nL * sizeof(float), st));
   h->iterations = 0;
+  if (beside) {
+    HIP_TRY(hipStreamSynchronize(beside->stream()));
+    HIP_TRY(clear_state32(beside, st));
+    beside->iterations = 0;
+    HIP_TRY(hipEventRecord(beside->ev0, st));
+  }
   for (int c = 0; c < nck; ++c) {
     HIP_TRY(hipMemcpyAsync((char*)h->d_ck_U + c * nL * esz, h->d_U, nL * esz, hipMemcpyDeviceToDevice, st));
     if (h->d_Ulo)
@@ -764,9 +824,19 @@ template <typename T> int adjoint_forward_t(mplpxx_solver* h, int K, int every, 
     // needs first, are recorded here; a small model's forward is shorter on one
     // workgroup, without records)
     const bool record = pers && c >= nck - 2 && !h->solo(false);
-    const int rc = pers ? fwd64_segment(h, seg, record ? h->d_rec + (size_t)(c & 1) * every * h->m * 3 * h->L : nullptr)
-                        : iterate_t<T>(h, seg, nullptr);
+    unsigned char* rec = record ? h->d_rec + (size_t)(c & 1) * every * h->m * 3 * h->L : nullptr;
+    const int rc = beside ? pair_segment(h, beside, seg, rec)
+                   : pers ? fwd64_segment(h, seg, rec)
+                          : iterate_t<T>(h, seg, nullptr);
     if (rc != MPLPXX_OK) return rc;
+  }
+  if (beside) {
+    HIP_TRY(hipEventRecord(beside->ev1, st));
+    HIP_TRY(hipEventSynchronize(beside->ev1));
+    float ms = 0.f;
+    HIP_TRY(hipEventElapsedTime(&ms, beside->ev0, beside->ev1));
+    beside->last_ms = ms;
+    beside->timed = true;
   }
   HIP_TRY(hipMemcpyAsync((char*)h->d_ck_U + nck * nL * esz, h->d_U, nL * esz, hipMemcpyDeviceToDevice, st));
   if (h->d_Ulo)
@@ -966,15 +1036,18 @@ int mplpxx_adjoint_forward(mplpxx_solver* h, int32_t K, int32_t every, double* l
     }
     h->shadow->engine_opt = h->engine_opt;  // (one launch per matching, or persistent)
     h->shadow->spin_limit = h->spin_limit;
-    int rc = adjoint_forward_t<double>(h->shadow, K, every, loss);
+    const bool paired = adjoint_paired(h);
+    int rc = adjoint_forward_t<double>(h->shadow, K, every, loss, paired ? h : nullptr);
     if (rc != MPLPXX_OK) return rc;
+    if (paired) {
+      h->adj_ready = true;
+      h->adj_iter_mark = h->iterations;
+      return MPLPXX_OK;
+    }
     // the handle's own FP32 run of K iterations from phi = 0
     hipStream_t st = h->stream();
-    const size_t nL = (size_t)h->n * h->L;
     HIP_TRY(hipStreamSynchronize(st));
-    HIP_TRY(hipMemsetAsync(h->d_phi, 0, (size_t)h->m * 2 * h->L * sizeof(float), st));
-    HIP_TRY(hipMemcpyAsync(h->d_U, h->d_unaries, nL * sizeof(float), hipMemcpyDeviceToDevice, st));
-    HIP_TRY(hipMemsetAsync(h->d_Ulo, 0, nL * sizeof(float), st));
+    HIP_TRY(clear_state32(h, st));
     h->iterations = 0;
     rc = iterate_t<float>(h, K, nullptr);
     if (rc != MPLPXX_OK) return rc;
