@@ -24,7 +24,7 @@ LIB_ROCM = os.path.join(HERE, "libmplpxx_rocm.so")
 
 SOURCES = ["solver.cpp", "batch.cpp", "schedule.cpp", "handshake.hip", "dual.hip", "batch.hip", "adjoint.hip",
            "rules.hip", "noalloc.hip", "probe.hip", "solo.hip",
-           "mb_tiles.hip", "adj_pair.hip"]
+           "mb_tiles.hip", "adj_pair.hip", "mb_snap.hip"]
 ARCH = os.environ.get("MPLPXX_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -40,7 +40,8 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-Wno-unused-comman
 # on non-NaN operands the results are bitwise the same.
 EXTRA = {"handshake.hip": ["-fno-honor-nans"], "batch.hip": ["-fno-honor-nans"], "rules.hip": ["-fno-honor-nans"],
          "solo.hip": ["-fno-honor-nans"], "adjoint.hip": ["-fno-honor-nans"],
-         "mb_tiles.hip": ["-fno-honor-nans"], "adj_pair.hip": ["-fno-honor-nans"]}
+         "mb_tiles.hip": ["-fno-honor-nans"], "adj_pair.hip": ["-fno-honor-nans"],
+         "mb_snap.hip": ["-fno-honor-nans"]}
 
 
 def _compile(src: str, build_dir: str = BUILD, defines=()) -> str:

@@ -77,6 +77,7 @@ template <typename T> struct HsArgs {
   unsigned long long* sink;  // FP32 mailbox engine: [grid][NT + 128] scratch words
   int L, m, n;
   int mbs;                // FP32 mailbox engine: words from one node's mailbox row to the next
+  float* snap;            // [iters][m][2][L] messages of every iteration (launch_mb_snap)
   long long spin_limit;
 };
 
@@ -209,16 +210,22 @@ hipError_t launch_persistent_mb(const HsArgs<float>& a, unsigned long long* mb, 
 int max_blocks_per_cu_mb_potts();
 hipError_t launch_persistent_mb_potts(const HsArgs<float>& a, unsigned long long* mb, int grid, int iters,
                                       int phi_in_lds, size_t dyn_lds, hipStream_t st, int kind = MPLPXX_COST_POTTS);
+// the same on `grid` workgroups, the messages of every iteration kept in a.snap
+// (mb_snap.hip); mb_snap_fits: whether this model can
+bool mb_snap_fits(int m, int L, int grid);
+hipError_t launch_mb_snap(const HsArgs<float>& a, unsigned long long* mb, int grid, int iters, hipStream_t st);
 // (mbs: words of a node's mailbox row)
 hipError_t launch_mb_init(const float* U, const float* Ulo, unsigned long long* mb, int n, int L, int mbs,
                           hipStream_t st);
 hipError_t launch_mb_fini(float* U, float* Ulo, const unsigned long long* mb, int n, int L, int mbs, double* trace_row,
                           hipStream_t st);
 
-// dual bound, traces, decode (dual.hip)
+// dual bound, traces, decode (dual.hip); states: of so many message arrays one
+// after another, with as many outputs and scratch terms
 template <typename T>
 hipError_t launch_dual(const T* unaries, const T* tables, const T* phi, const int* node_ptr, const int* inc, int n,
-                       int L, int m, double* node_min, double* edge_min, double* out, hipStream_t st, int potts = 0);
+                       int L, int m, double* node_min, double* edge_min, double* out, hipStream_t st, int potts = 0,
+                       int states = 1);
 template <typename T>
 hipError_t launch_trace_nodes(const T* U, const T* Ulo, int n, int L, double* row, hipStream_t st);
 template <typename T>
@@ -232,7 +239,7 @@ hipError_t launch_trace_sum(double* trace_nodes, const float* trace_e, int m, in
 template <typename T>
 hipError_t launch_decode(const T* unaries, const T* tables, const T* phi, const SlotInfo* slots, const int* node_ptr,
                          const int* inc, int n, int L, int m, int* labels, int* ticket, double* node_e, double* edge_e,
-                         double* energy, int* err, long long spin_limit, hipStream_t st, int potts = 0);
+                         double* energy, int* err, long long spin_limit, hipStream_t st, int potts = 0, int states = 1);
 template <typename T>
 hipError_t launch_check_finite(const T* p, size_t count, int* flag, hipStream_t st);
 template <typename S, typename D>

@@ -473,6 +473,7 @@ struct MbView {
   unsigned short* lds_lo;
   unsigned long long* sink;     // this workgroup's scratch words [NT + 128] (see the output stores)
   int mbs;                      // words of a node's mailbox row
+  float* snap;                  // SNAP: [iters][m][2][L] the messages after every iteration
 };
 
 // The gather of the LDS-resident mode: hi, lo, centred values and reference
@@ -625,7 +626,7 @@ __device__ __forceinline__ void load_phi(const float* src, int L, float (&pu)[Ti
 // slot is formed from its parameters (v.tables holds cost_params(KIND)
 // floats per slot) by gen_tile, the rest is the dense engine.
 template <int LT, int NT, bool PHI_LDS, bool FULL, bool TRACE, bool LDSU, bool PHI_FAR, int DEPTH = (LT <= 64 ? 2 : 1),
-          int KIND = kCostDense, int RULE = MPLPXX_RULE_H>
+          int KIND = kCostDense, int RULE = MPLPXX_RULE_H, bool SNAP = false>
 __device__ __forceinline__ bool mb_run(const MbView& v_in, int first_in, int stride_in, int iters_in,
                                        SmemMB<LT, NT>& sm, float* phi_lds, long long spin_limit, int* err) {
   using S = TileShape<float, LT, NT>;
@@ -1017,6 +1018,10 @@ __device__ __forceinline__ bool mb_run(const MbView& v_in, int first_in, int str
       if (outk) phi_w[(out_u ? 0 : L) + out_i] = omsg;
     } else {
       *(outk ? phi_w + (out_u ? 0 : L) + out_i : reinterpret_cast<float*>(v.sink + NT + (tid >> 6))) = omsg;
+    }
+    if (SNAP) {
+      float* row = v.snap + ((size_t)it * v.m + slot) * 2 * L;
+      *(outk ? row + (out_u ? 0 : L) + out_i : reinterpret_cast<float*>(v.sink + NT + (tid >> 6))) = omsg;
     }
     {
       const bool st = v.stamps && last_iter && tid == 0;

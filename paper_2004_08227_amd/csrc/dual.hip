@@ -40,25 +40,32 @@ __device__ __forceinline__ T table_at(const T* tables, int slot, int L, int s, i
   return tables[(size_t)slot * L * L + (size_t)s * L + t];
 }
 
-// out = sum(a[0..na)) + sum(b[0..nb)), fixed order, one workgroup
+// out = sum(a[0..na)) + sum(b[0..nb)), fixed order, one workgroup for each of
+// the grid's states (their terms one after another)
 __global__ void __launch_bounds__(1024) k_sum2(const double* __restrict__ a, int na, const double* __restrict__ b,
                                                int nb, double* __restrict__ out) {
   __shared__ double sh[1024];
+  a += (size_t)blockIdx.x * na;
+  b += (size_t)blockIdx.x * nb;
   double acc = 0.0;
   for (int i = threadIdx.x; i < na; i += 1024) acc += a[i];
   for (int i = threadIdx.x; i < nb; i += 1024) acc += b[i];
   acc = block_reduce<1024, false>(acc, sh);
-  if (threadIdx.x == 0) *out = acc;
+  if (threadIdx.x == 0) out[blockIdx.x] = acc;
 }
 
 // Node and edge terms of Eq. (3) in one launch (dual_terms.h): waves [0, n)
-// take a node each, the others a slot.
+// take a node each, the others a slot; grid y: the state, of `states` message
+// arrays one after another.
 template <typename T, int V>
 __global__ void __launch_bounds__(256) k_dual_terms(const T* __restrict__ unaries, const T* __restrict__ tables,
                                                     const T* __restrict__ phi, const int* __restrict__ node_ptr,
                                                     const int* __restrict__ inc, int n, int L, int m, int potts,
                                                     double* __restrict__ node_min, double* __restrict__ edge_min) {
   __shared__ T sh[4][2 * MPLPXX_MAX_LABELS];
+  phi += (size_t)blockIdx.y * m * 2 * L;
+  node_min += (size_t)blockIdx.y * n;
+  edge_min += (size_t)blockIdx.y * m;
   const int w = uni((int)(blockIdx.x * 4 + (threadIdx.x >> 6))), lane = threadIdx.x & 63;
   if (w < n) {
     const double mn = node_term(unaries + (size_t)w * L, phi, inc, uni(node_ptr[w]), uni(node_ptr[w + 1]), L);
@@ -73,8 +80,9 @@ __global__ void __launch_bounds__(256) k_dual_terms(const T* __restrict__ unarie
 
 template <typename T>
 hipError_t launch_dual(const T* unaries, const T* tables, const T* phi, const int* node_ptr, const int* inc, int n,
-                       int L, int m, double* node_min, double* edge_min, double* out, hipStream_t st, int potts) {
-  const dim3 grid((unsigned)((n + (size_t)m + 3) / 4));
+                       int L, int m, double* node_min, double* edge_min, double* out, hipStream_t st, int potts,
+                       int states) {
+  const dim3 grid((unsigned)((n + (size_t)m + 3) / 4), (unsigned)states);
   // (a vector of 16 bytes stays inside a row, and is aligned, where its width divides L)
   constexpr int V = 16 / sizeof(T);
   if (!potts && L % V == 0)
@@ -83,7 +91,7 @@ hipError_t launch_dual(const T* unaries, const T* tables, const T* phi, const in
   else
     hipLaunchKernelGGL((k_dual_terms<T, 1>), grid, dim3(256), 0, st, unaries, tables, phi, node_ptr, inc, n, L, m, potts,
                        node_min, edge_min);
-  hipLaunchKernelGGL(k_sum2, dim3(1), dim3(1024), 0, st, node_min, n, edge_min, m, out);
+  hipLaunchKernelGGL(k_sum2, dim3(states), dim3(1024), 0, st, node_min, n, edge_min, m, out);
   return hipGetLastError();
 }
 
@@ -199,6 +207,10 @@ hipError_t launch_trace_sum(double* trace_nodes, const float* trace_e, int m, in
 // Nodes are numbered by an arrival ticket, so a workgroup only waits for
 // workgroups that have started: the launch needs no co-residency.
 //
+// Several states of one model (one message array after another) are labelled
+// in one launch, the tickets taking node 0 of every state, then node 1 of
+// every state: their chains run side by side.
+//
 // Sums are in FP64 and in one order whatever the graph: wave w sums the
 // incidences w, w+16, ... of the node (lane = label), and the 16 partial sums
 // are added in wave order after the reparametrized unary.
@@ -218,8 +230,8 @@ template <typename T, int PER, int B>
 __global__ void __launch_bounds__(kDecW * 64) k_decode(const T* __restrict__ unaries, const T* __restrict__ tables,
                                                        const T* __restrict__ phi, const SlotInfo* __restrict__ slots,
                                                        const int* __restrict__ node_ptr, const int* __restrict__ inc,
-                                                       int L, int potts, int stage, int* __restrict__ labels,
-                                                       int* __restrict__ ticket, int* __restrict__ err,
+                                                       int n, int L, int m, int states, int potts, int stage,
+                                                       int* __restrict__ labels, int* __restrict__ ticket, int* __restrict__ err,
                                                        long long spin_limit) {
   static_assert(B <= 64, "one lane polls each incidence of a block");
   __shared__ double part[kDecW][64 * PER];
@@ -235,7 +247,10 @@ __global__ void __launch_bounds__(kDecW * 64) k_decode(const T* __restrict__ una
     s_near_slot = -1;
   }
   __syncthreads();
-  const int u = uni(s_u);
+  const int t = uni(s_u);
+  const int u = uni(t / states), state = t - u * states;
+  phi += (size_t)state * m * 2 * L;
+  labels += (size_t)state * n;
   const int k0 = uni(node_ptr[u]), k1 = uni(node_ptr[u + 1]);
   const int deg = k1 - k0;
   {
@@ -368,6 +383,9 @@ __global__ void __launch_bounds__(256) k_energy_terms(const T* __restrict__ unar
                                                       const int* __restrict__ labels, int n, int L, int m, int potts,
                                                       double* __restrict__ node_e, double* __restrict__ edge_e) {
   const int i = blockIdx.x * 256 + threadIdx.x;
+  labels += (size_t)blockIdx.y * n;
+  node_e += (size_t)blockIdx.y * n;
+  edge_e += (size_t)blockIdx.y * m;
   if (i < n) {
     node_e[i] = (double)unaries[(size_t)i * L + labels[i]];
   } else if (i - n < m) {
@@ -379,21 +397,22 @@ __global__ void __launch_bounds__(256) k_energy_terms(const T* __restrict__ unar
 template <typename T>
 hipError_t launch_decode(const T* unaries, const T* tables, const T* phi, const SlotInfo* slots, const int* node_ptr,
                          const int* inc, int n, int L, int m, int* labels, int* ticket, double* node_e, double* edge_e,
-                         double* energy, int* err, long long spin_limit, hipStream_t st, int potts) {
-  hipLaunchKernelGGL(k_decode_init, dim3((n + 255) / 256), dim3(256), 0, st, labels, n, ticket);
+                         double* energy, int* err, long long spin_limit, hipStream_t st, int potts, int states) {
+  const int all = n * states;
+  hipLaunchKernelGGL(k_decode_init, dim3((all + 255) / 256), dim3(256), 0, st, labels, all, ticket);
   const size_t tab = (size_t)L * L * sizeof(T);
   const int stage = !potts && m > 0 && tab <= kDecStage;
   const size_t dyn = L * sizeof(T) + (stage ? tab : 0);
   constexpr int B1 = sizeof(T) == 4 ? 16 : 8;
   if (L <= 64)
-    hipLaunchKernelGGL((k_decode<T, 1, B1>), dim3(n), dim3(kDecW * 64), dyn, st, unaries, tables, phi, slots, node_ptr,
-                       inc, L, potts, stage, labels, ticket, err, spin_limit);
+    hipLaunchKernelGGL((k_decode<T, 1, B1>), dim3(all), dim3(kDecW * 64), dyn, st, unaries, tables, phi, slots,
+                       node_ptr, inc, n, L, m, states, potts, stage, labels, ticket, err, spin_limit);
   else
-    hipLaunchKernelGGL((k_decode<T, 2, B1 / 2>), dim3(n), dim3(kDecW * 64), dyn, st, unaries, tables, phi, slots,
-                       node_ptr, inc, L, potts, stage, labels, ticket, err, spin_limit);
-  hipLaunchKernelGGL(k_energy_terms<T>, dim3((n + m + 255) / 256), dim3(256), 0, st, unaries, tables, slots, labels, n,
+    hipLaunchKernelGGL((k_decode<T, 2, B1 / 2>), dim3(all), dim3(kDecW * 64), dyn, st, unaries, tables, phi, slots,
+                       node_ptr, inc, n, L, m, states, potts, stage, labels, ticket, err, spin_limit);
+  hipLaunchKernelGGL(k_energy_terms<T>, dim3((n + m + 255) / 256, states), dim3(256), 0, st, unaries, tables, slots, labels, n,
                      L, m, potts, node_e, edge_e);
-  hipLaunchKernelGGL(k_sum2, dim3(1), dim3(1024), 0, st, node_e, n, edge_e, m, energy);
+  hipLaunchKernelGGL(k_sum2, dim3(states), dim3(1024), 0, st, node_e, n, edge_e, m, energy);
   return hipGetLastError();
 }
 
@@ -496,14 +515,14 @@ hipError_t launch_fill_int(int* p, int value, size_t count, hipStream_t st) {
 
 #define MPLPXX_INST(T)                                                                                              \
   template hipError_t launch_dual<T>(const T*, const T*, const T*, const int*, const int*, int, int, int, double*,  \
-                                     double*, double*, hipStream_t, int);                                         \
+                                     double*, double*, hipStream_t, int, int);                                    \
   template hipError_t launch_trace_nodes<T>(const T*, const T*, int, int, double*, hipStream_t);                             \
   template hipError_t launch_trace_edges<T>(const T*, const T*, int, int, float*, hipStream_t);               \
   template hipError_t launch_trace_sum<T>(double*, const float*, int, int, const T*, const int*, int, int, int,   \
                                           double*, hipStream_t);     \
   template hipError_t launch_decode<T>(const T*, const T*, const T*, const SlotInfo*, const int*, const int*, int, \
                                        int, int, int*, int*, double*, double*, double*, int*, long long,           \
-                                       hipStream_t, int);                                                          \
+                                       hipStream_t, int, int);                                                     \
   template hipError_t launch_phi_by_edge<T>(const T*, const int*, int, int, T*, hipStream_t);                      \
   template hipError_t launch_check_finite<T>(const T*, size_t, int*, hipStream_t);
 MPLPXX_INST(float)

@@ -21,7 +21,7 @@ hipError_t launch_mb_odd(const HsArgs<float>& a, unsigned long long* mb, int gri
                          size_t dyn_lds, hipStream_t st);
 
 template <int LT, int NT, bool PHI_LDS, bool FULL, bool TRACE, bool PHI_FAR, int DEPTH = (LT <= 64 ? 2 : 1),
-          int KIND = kCostDense, int RULE = MPLPXX_RULE_H>
+          int KIND = kCostDense, int RULE = MPLPXX_RULE_H, bool SNAP = false>
 __global__ void __launch_bounds__(NT + 128) k_persistent_mb(HsArgs<float> a, unsigned long long* __restrict__ mb,
                                                             int iters) {
   __shared__ SmemMB<LT, NT> sm;
@@ -37,9 +37,9 @@ __global__ void __launch_bounds__(NT + 128) k_persistent_mb(HsArgs<float> a, uns
   }
   __syncthreads();
   MbView v{a.tables, a.phi, mb, a.slots, a.deg, a.trace, a.trace_e, a.stamps, L, a.m, a.n, nullptr, nullptr,
-           a.sink + (size_t)blockIdx.x * (NT + 128), a.mbs};
-  if (!mb_run<LT, NT, PHI_LDS, FULL, TRACE, false, PHI_FAR, DEPTH, KIND, RULE>(v, blockIdx.x, G, iters, sm, phi_lds,
-                                                                         a.spin_limit, a.err))
+           a.sink + (size_t)blockIdx.x * (NT + 128), a.mbs, a.snap};
+  if (!mb_run<LT, NT, PHI_LDS, FULL, TRACE, false, PHI_FAR, DEPTH, KIND, RULE, SNAP>(v, blockIdx.x, G, iters, sm, phi_lds,
+                                                                               a.spin_limit, a.err))
     return;
   __syncthreads();
   if (PHI_LDS) {
