@@ -70,8 +70,9 @@ struct mplpxx_solver {
   int* d_inc = nullptr;
   double* d_node_min = nullptr;
   double* d_edge_min = nullptr;
-  double* d_scalar = nullptr;
+  double* d_scalar = nullptr;             // [4] and d_labels [n] lie behind the error words: one copy reads them all
   int* d_labels = nullptr;
+  char* pin = nullptr;                    // kPinBytes of pinned host memory that results arrive in
   double* d_trace_nodes = nullptr;
   double* d_trace_out = nullptr;
   float* d_trace_e = nullptr;            // FP32: [cap][m][8] edge terms of the trace
@@ -199,13 +200,17 @@ struct mplpxx_solver {
 
 namespace {
 
+constexpr size_t kReadHead = 8 * sizeof(int) + 4 * sizeof(double);  // error words and scalars
+constexpr size_t kPinBytes = 64 * 1024;
+
 void free_all(mplpxx_solver* h) {
   void* ptrs[] = {h->d_tables, h->d_phi, h->d_U, h->d_Ulo, h->d_adj, h->d_unaries, h->d_slots, h->d_deg, h->d_ver, h->d_err,
-                  h->d_node_ptr, h->d_inc, h->d_node_min, h->d_edge_min, h->d_scalar, h->d_labels,
+                  h->d_node_ptr, h->d_inc, h->d_node_min, h->d_edge_min,
                   h->d_trace_nodes, h->d_trace_out, h->d_trace_e, h->d_mb, h->d_sink, h->d_stamps, h->d_slot_of_edge, h->d_edge_flip, h->d_export, h->d_mb64, h->d_sink64,
                   h->d_gap};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
+  if (h->pin) (void)hipHostFree(h->pin);
   if (h->ev0) (void)hipEventDestroy(h->ev0);
   if (h->ev1) (void)hipEventDestroy(h->ev1);
   if (h->own_stream) (void)hipStreamDestroy(h->own_stream);
@@ -345,13 +350,13 @@ int create_impl(int32_t n, int32_t L, int64_t m, const int32_t* edges, const voi
   h->d_slots = dalloc<SlotInfo>(m, &ae); TRY(ae);
   h->d_deg = dalloc<int>(n, &ae); TRY(ae);
   h->d_ver = dalloc<int>(n, &ae); TRY(ae);
-  h->d_err = dalloc<int>(8, &ae); TRY(ae);
+  h->d_err = reinterpret_cast<int*>(dalloc<char>(kReadHead + (size_t)n * sizeof(int), &ae)); TRY(ae);
+  h->d_scalar = reinterpret_cast<double*>(h->d_err + 8);
+  h->d_labels = reinterpret_cast<int*>(h->d_scalar + 4);
   h->d_node_ptr = dalloc<int>(n + 1, &ae); TRY(ae);
   h->d_inc = dalloc<int>(2 * (size_t)m, &ae); TRY(ae);
   h->d_node_min = dalloc<double>(n, &ae); TRY(ae);
   h->d_edge_min = dalloc<double>(m, &ae); TRY(ae);
-  h->d_scalar = dalloc<double>(4, &ae); TRY(ae);
-  h->d_labels = dalloc<int>(n, &ae); TRY(ae);
   if (dtype == MPLPXX_F32) {
     h->d_mb = dalloc<unsigned long long>((size_t)n * mb_row_words(L), &ae);
     TRY(ae);
@@ -470,18 +475,75 @@ int create_impl(int32_t n, int32_t L, int64_t m, const int32_t* edges, const voi
   return MPLPXX_OK;
 }
 
-int sync_and_check(mplpxx_solver* h) {
-  HIP_TRY(hipStreamSynchronize(h->stream()));
+// Ends a call: waits for the handle's stream, checks the error words and
+// delivers results.  Error words, scalars and labels are read by one copy, the
+// others by one each, all into pinned memory and queued before the wait: a copy
+// to pageable memory after it took 11.5 us, a queued one takes 3.  (Microseconds
+// of a call on 8 nodes of 4 labels, before / after: no iterations 37 / 25, bound
+// 52 / 21, labelling 77 / 35, state 39 / 20.)
+struct Result {
+  const void* dev;
+  void* host;
+  size_t bytes;
+};
+bool ensure_pin(mplpxx_solver* h) {
+  if (!h->pin && hipHostMalloc(reinterpret_cast<void**>(&h->pin), kPinBytes, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    h->pin = nullptr;
+  }
+  return h->pin != nullptr;
+}
+// results that fit `room` bytes of pinned memory from `at` on; false: they are
+// copied one by one after the wait
+bool queue_results(mplpxx_solver* h, const Result* r, int count, size_t at, hipError_t* e) {
+  size_t total = at;
+  for (int i = 0; i < count; ++i) total += r[i].bytes;
+  if (total > kPinBytes) return false;
+  for (int i = 0; i < count && *e == hipSuccess; at += r[i++].bytes)
+    if (r[i].bytes) *e = hipMemcpyAsync(h->pin + at, r[i].dev, r[i].bytes, hipMemcpyDeviceToHost, h->stream());
+  return true;
+}
+void take_results(const mplpxx_solver* h, const Result* r, int count, size_t at) {
+  for (int i = 0; i < count; at += r[i++].bytes)
+    if (r[i].bytes) std::memcpy(r[i].host, h->pin + at, r[i].bytes);
+}
+// labels: wanted with the error words and scalars; scalars are then in `head`
+int finish(mplpxx_solver* h, int32_t* labels = nullptr, double* scalars = nullptr, const Result* r = nullptr, int count = 0) {
   int err[8] = {0};
-  HIP_TRY(hipMemcpy(err, h->d_err, 8 * sizeof(int), hipMemcpyDeviceToHost));
+  const size_t lab = labels ? (size_t)h->n * sizeof(int) : 0;
+  const bool pinned = ensure_pin(h);
+  const bool lab_pinned = pinned && kReadHead + lab <= kPinBytes;
+  const size_t head = lab_pinned ? kReadHead + lab : kReadHead;
+  bool extra = false;
+  if (pinned) {
+    HIP_TRY(hipMemcpyAsync(h->pin, h->d_err, head, hipMemcpyDeviceToHost, h->stream()));
+    hipError_t e = hipSuccess;
+    extra = queue_results(h, r, count, head, &e);
+    HIP_TRY(e);
+  }
+  HIP_TRY(hipStreamSynchronize(h->stream()));
+  if (pinned) std::memcpy(err, h->pin, sizeof(err));
+  else HIP_TRY(hipMemcpy(err, h->d_err, sizeof(err), hipMemcpyDeviceToHost));
   if (err[0] != 0) {
     (void)hipMemsetAsync(h->d_err, 0, 8 * sizeof(int), h->stream());
     (void)hipStreamSynchronize(h->stream());
     return fail(err[0], "device wait exceeded its bound (workgroup %d, slot %d, node %d, expected version %d, seen %d)",
                 err[1], err[2], err[3], err[4], err[5]);
   }
+  if (scalars) {
+    if (pinned) std::memcpy(scalars, h->pin + sizeof(err), 4 * sizeof(double));
+    else HIP_TRY(hipMemcpy(scalars, h->d_scalar, 4 * sizeof(double), hipMemcpyDeviceToHost));
+  }
+  if (lab) {
+    if (lab_pinned) std::memcpy(labels, h->pin + kReadHead, lab);
+    else HIP_TRY(hipMemcpy(labels, h->d_labels, lab, hipMemcpyDeviceToHost));
+  }
+  if (extra) take_results(h, r, count, head);
+  for (int i = 0; i < count && !extra; ++i)
+    if (r[i].bytes) HIP_TRY(hipMemcpy(r[i].host, r[i].dev, r[i].bytes, hipMemcpyDeviceToHost));
   return MPLPXX_OK;
 }
+int sync_and_check(mplpxx_solver* h) { return finish(h); }
 
 hipError_t ensure_slot_of_edge(mplpxx_solver* h) {
   if (h->d_slot_of_edge || !h->m) return hipSuccess;
@@ -686,13 +748,12 @@ template <typename T> int iterate_t(mplpxx_solver* h, int k, double* trace_host)
   const int rc = queue_iterate<T>(h, k, trace_host);
   if (rc != MPLPXX_OK) return rc;
   if (!h->user_stream || trace_host) {
-    int rc = sync_and_check(h);
+    const Result trace{h->d_trace_out, trace_host, trace_host && k > 0 ? (size_t)k * sizeof(double) : 0};
+    int rc = finish(h, nullptr, nullptr, &trace, 1);
     if (rc != MPLPXX_OK) return rc;
     float ms = 0.f;
     HIP_TRY(hipEventElapsedTime(&ms, h->ev0, h->ev1));
     h->last_ms = ms;
-    if (trace_host && k > 0)
-      HIP_TRY(hipMemcpy(trace_host, h->d_trace_out, (size_t)k * sizeof(double), hipMemcpyDeviceToHost));
   }
   return MPLPXX_OK;
 }
@@ -1126,20 +1187,19 @@ int mplpxx_adjoint_backward(mplpxx_solver* h, void* grad_unaries, void* grad_pai
 int mplpxx_dual_bound(mplpxx_solver* h, double* out) {
   if (!h || !out) return fail(MPLPXX_EINVAL, "NULL argument");
   HIP_TRY(queue_dual(h, h->d_scalar));
-  int rc = sync_and_check(h);
-  if (rc != MPLPXX_OK) return rc;
-  HIP_TRY(hipMemcpy(out, h->d_scalar, sizeof(double), hipMemcpyDeviceToHost));
-  return MPLPXX_OK;
+  double scalars[4];
+  const int rc = finish(h, nullptr, scalars);
+  if (rc == MPLPXX_OK) *out = scalars[0];
+  return rc;
 }
 
 int mplpxx_decode(mplpxx_solver* h, int32_t* labels, double* energy) {
   if (!h || !labels) return fail(MPLPXX_EINVAL, "NULL argument");
   HIP_TRY(queue_decode(h, h->d_labels, h->d_scalar + 1));
-  int rc = sync_and_check(h);
-  if (rc != MPLPXX_OK) return rc;
-  HIP_TRY(hipMemcpy(labels, h->d_labels, (size_t)h->n * sizeof(int), hipMemcpyDeviceToHost));
-  if (energy) HIP_TRY(hipMemcpy(energy, h->d_scalar + 1, sizeof(double), hipMemcpyDeviceToHost));
-  return MPLPXX_OK;
+  double scalars[4];
+  const int rc = finish(h, labels, scalars);
+  if (rc == MPLPXX_OK && energy) *energy = scalars[1];
+  return rc;
 }
 
 int mplpxx_iterate_gap(mplpxx_solver* h, int32_t k, double* dual, double* energy, int32_t* best_labels) {
@@ -1214,7 +1274,9 @@ int mplpxx_iterate_gap(mplpxx_solver* h, int32_t k, double* dual, double* energy
       return fail(MPLPXX_EDEVICE, "gap trace: %s", hipGetErrorString(e));
     }
   }
-  int rc = sync_and_check(h);
+  std::vector<double> buf((size_t)2 * k);
+  const Result gap{d_gap, buf.data(), buf.size() * sizeof(double)};
+  int rc = finish(h, nullptr, nullptr, &gap, 1);
   if (rc != MPLPXX_OK) {
     release();
     return rc;
@@ -1228,8 +1290,7 @@ int mplpxx_iterate_gap(mplpxx_solver* h, int32_t k, double* dual, double* energy
     }
     h->last_ms = ms / h->timed_calls;
   }
-  std::vector<double> buf((size_t)2 * k);
-  hipError_t e = hipMemcpy(buf.data(), d_gap, buf.size() * sizeof(double), hipMemcpyDeviceToHost);
+  hipError_t e = hipSuccess;
   int best = 0;
   for (int it = 0; it < k; ++it) {
     dual[it] = buf[it];
@@ -1307,8 +1368,29 @@ int mplpxx_schedule_kind(int32_t n, int64_t m, const int32_t* edges, int32_t sch
 
 int mplpxx_get_state(mplpxx_solver* h, void* U, void* phi, float* U_comp) {
   if (!h) return fail(MPLPXX_EINVAL, "handle is NULL");
-  HIP_TRY(hipStreamSynchronize(h->stream()));
   const size_t esz = h->esz, L = h->L;
+  {
+    // a small state: every copy queued before one wait (see finish)
+    const size_t nL = (size_t)h->n * L, row = 2 * L * esz;
+    const size_t bytes[3] = {U ? nL * esz : 0, U_comp && h->d_Ulo ? nL * sizeof(float) : 0, phi ? (size_t)h->m * row : 0};
+    if (bytes[0] + bytes[1] + bytes[2] <= kPinBytes && ensure_pin(h)) {
+      const void* src[3] = {h->d_U, h->d_Ulo, h->d_phi};
+      size_t at[4] = {0};
+      for (int i = 0; i < 3; ++i) {
+        if (bytes[i]) HIP_TRY(hipMemcpyAsync(h->pin + at[i], src[i], bytes[i], hipMemcpyDeviceToHost, h->stream()));
+        at[i + 1] = at[i] + bytes[i];
+      }
+      HIP_TRY(hipStreamSynchronize(h->stream()));
+      if (U) std::memcpy(U, h->pin, bytes[0]);
+      if (bytes[1]) std::memcpy(U_comp, h->pin + at[1], bytes[1]);
+      else if (U_comp) std::fill(U_comp, U_comp + nL, 0.0f);
+      if (phi)
+        for (int e = 0; e < h->m; ++e)
+          std::memcpy(static_cast<char*>(phi) + (size_t)e * row, h->pin + at[2] + (size_t)h->slot_of_edge[e] * row, row);
+      return MPLPXX_OK;
+    }
+  }
+  HIP_TRY(hipStreamSynchronize(h->stream()));
   if (U) HIP_TRY(hipMemcpy(U, h->d_U, (size_t)h->n * L * esz, hipMemcpyDeviceToHost));
   if (U_comp) {
     if (h->d_Ulo)
