@@ -15,9 +15,9 @@
 // Bound: the chain of dependent matchings, as in FP32.  Against the former
 // FP64 forward (argmins carried through every minimum, tables loaded after the
 // step that used the last ones, divergent stores), microseconds a matching:
-// n = 100, L = 16 1.72 -> 1.15, L = 32 2.49 -> 1.41, L = 64 4.82 -> 2.35;
-// traces, which ran on release and acquire fences, 4.62 -> 1.16, 5.39 -> 1.42,
-// 6.25 -> 2.32.  The records cost nothing at L = 32 (1.40 us with them): they
+// n = 100, L = 16 1.72 -> 1.14, L = 32 2.49 -> 1.33, L = 64 4.82 -> 2.08;
+// traces, which ran on release and acquire fences, 4.62 -> 1.13, 5.39 -> 1.33,
+// 6.25 -> 2.03.  The records cost nothing at L = 32: they
 // are made while the next workgroup of the chain works.
 //
 // Slots are owned statically: workgroup w runs slots w, w + G, ... in schedule
@@ -118,7 +118,7 @@ __device__ __forceinline__ void col4_min_store64(const double (&x)[BC], double* 
 }
 // lowest index over the 16 lanes of a row, and over the four row blocks
 template <int CTRL> __device__ __forceinline__ int dpp_i(int x) {
-  return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, false);
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, true);
 }
 __device__ __forceinline__ int row16_imin(int x) {
   x = min(x, dpp_i<0xB1>(x));
@@ -286,14 +286,16 @@ __device__ __forceinline__ void fwd64_role(const Fwd64Args& a, int first_in, int
 #pragma unroll
     for (int i = 0; i < S::BR; ++i)
 #pragma unroll
-      for (int jj = 0; jj < S::BC; ++jj) xc[i][jj] = row_real[i] && col_real[jj] ? xc[i][jj] : __builtin_inf();
+      for (int jj = 0; jj < S::BC; ++jj) {
+        xc[i][jj] = row_real[i] && col_real[jj] ? xc[i][jj] : __builtin_inf();
+        asm volatile("" : "+v"(xc[i][jj]));  // (here, not behind the barrier)
+      }
     __syncthreads();  // the step's nodes are in LDS
     if (owned == 1) load_phi64(slot, j);
     double au[S::BR], av[S::BC];
 #pragma unroll
     for (int jj = 0; jj < S::BC; ++jj) {
-      const double x = sm.hv[parity][col_real[jj] ? cb * S::BC + jj : L - 1] - pv[jj];
-      av[jj] = col_real[jj] ? x : 0.0;
+      av[jj] = sm.hv[parity][col_real[jj] ? cb * S::BC + jj : L - 1] - pv[jj];
     }
 #pragma unroll
     for (int i = 0; i < S::BR; ++i) au[i] = sm.hu[parity][row_real[i] ? rb * S::BR + i : L - 1] - pu[i];
