@@ -26,7 +26,8 @@ __global__ void __launch_bounds__(kF64NT + 128) k_adj_pair(Fwd64Args f, HsArgs<f
                                                            unsigned long long* __restrict__ mb, int grid32) {
   constexpr int NT = kF64NT;
   __shared__ SmemF64<LT> smf;
-  __shared__ SmemMB<LT, NT> sm;
+  constexpr int LT32 = LT <= 32 ? LT : 64;
+  __shared__ SmemMB<LT32, NT> sm;
   extern __shared__ __align__(16) double pair_lds[];
   const int tid = threadIdx.x;
   const int b = blockIdx.x;
@@ -44,7 +45,7 @@ __global__ void __launch_bounds__(kF64NT + 128) k_adj_pair(Fwd64Args f, HsArgs<f
   __syncthreads();
   MbView v{a.tables, a.phi, mb, a.slots, a.deg, nullptr, nullptr, nullptr, L, a.m, a.n, nullptr, nullptr,
            a.sink + (size_t)first * (NT + 128), a.mbs};
-  if (!mb_run<LT, NT, true, false, false, false, true, 2, kCostDense, MPLPXX_RULE_H>(v, first, grid32, f.iters, sm,
+  if (!mb_run<LT32, NT, true, false, false, false, true, 2, kCostDense, MPLPXX_RULE_H>(v, first, grid32, f.iters, sm,
                                                                                       phi_lds, a.spin_limit, a.err))
     return;
   __syncthreads();
@@ -77,6 +78,7 @@ hipError_t launch_adj_pair(const Fwd64Args& f, const HsArgs<float>& a, unsigned 
   const size_t lds = std::max(pair_lds64(f.m, f.L, f.grid), pair_lds32(f.m, f.L, grid32) + kPhiLdsTail);
   if (f.L <= 16) return adj_pair_one<16>(f, a, mb, grid32, lds, st);
   if (f.L <= 32) return adj_pair_one<32>(f, a, mb, grid32, lds, st);
+  if (f.L <= 48) return adj_pair_one<48>(f, a, mb, grid32, lds, st);
   return adj_pair_one<64>(f, a, mb, grid32, lds, st);
 }
 

@@ -101,19 +101,21 @@ __device__ __forceinline__ double join32_min(double a, double b) {
 template <int BC>
 __device__ __forceinline__ void col4_min_store64(const double (&x)[BC], double* red, int cb, int lane) {
   const int k = lane >> 4;
-  if constexpr (BC == 1) {
-    const double p = pair16_min(x[0], x[0]);
-    const double f = join32_min(p, p);
-    if (lane < 16) red[cb] = f;
-  } else if constexpr (BC == 2) {
-    const double p = pair16_min(x[0], x[1]);
-    const double f = join32_min(p, p);
-    if (lane < 32) red[cb * 2 + k] = f;
-  } else {
-    static_assert(BC % 4 == 0, "columns per lane");
+  constexpr int Q = BC / 4 * 4;  // columns in groups of four, then two, then one
 #pragma unroll
-    for (int g = 0; g < BC; g += 4)
-      red[cb * BC + g + k] = join32_min(pair16_min(x[g], x[g + 1]), pair16_min(x[g + 2], x[g + 3]));
+  for (int g = 0; g < Q; g += 4)
+    red[cb * BC + g + k] = join32_min(pair16_min(x[g], x[g + 1]), pair16_min(x[g + 2], x[g + 3]));
+  if constexpr (BC - Q == 3) {
+    const double f = join32_min(pair16_min(x[Q], x[Q + 1]), pair16_min(x[Q + 2], x[Q + 2]));
+    if (lane < 48) red[cb * BC + Q + k] = f;
+  } else if constexpr (BC - Q == 2) {
+    const double p = pair16_min(x[Q], x[Q + 1]);
+    const double f = join32_min(p, p);
+    if (lane < 32) red[cb * BC + Q + k] = f;
+  } else if constexpr (BC - Q == 1) {
+    const double p = pair16_min(x[Q], x[Q]);
+    const double f = join32_min(p, p);
+    if (lane < 16) red[cb * BC + Q] = f;
   }
 }
 // lowest index over the 16 lanes of a row, and over the four row blocks
@@ -257,13 +259,18 @@ __device__ __forceinline__ void fwd64_role(const Fwd64Args& a, int first_in, int
     for (int jj = 0; jj < S::BC; ++jj) pv[jj] = ph[L + (col_real[jj] ? cb * S::BC + jj : L - 1)];
     pvo = ph[L + out_ic];
   };
+  // tables are loaded two steps ahead, one where the argmins take the registers
+  // (with the candidates kept from the passes and two steps ahead, 142 registers
+  // were spilled at 64 labels: forward with records of 100 nodes 2.77 us a
+  // matching, 2.25 now, backward 4.10, 2.92 now)
+  constexpr int DEPTH = REC && LT == 64 ? 1 : 2;
   double t0[S::BR][S::BC], t1[S::BR][S::BC], t2[S::BR][S::BC];
   load_tile64(t0, first);
-  load_tile64(t1, first + (owned > 1 ? G : 0));
+  if (DEPTH == 2) load_tile64(t1, first + (owned > 1 ? G : 0));
   // (a workgroup that owns one slot reads back the messages it wrote at the
   // previous step: after the next step's first barrier)
   if (owned > 1) load_phi64(first, 0);
-  int parity = 0, it = 0, j = 0, jp = 2 % owned;
+  int parity = 0, it = 0, j = 0, jp = DEPTH % owned;
   SlotInfo si = ld_const(slots + first);
   unsigned char* rec_prev = nullptr;  // REC: the s2 record of the previous step
   auto finish_s2 = [&](int par) __attribute__((always_inline)) {
@@ -376,6 +383,14 @@ __device__ __forceinline__ void fwd64_role(const Fwd64Args& a, int first_in, int
     if constexpr (REC) {
       // argmins, after everything another workgroup waits for
       if (rec_prev) finish_s2(parity ^ 1);
+      if constexpr (LT > 32) {
+        // (the candidates are formed anew: kept from the passes, they would
+        // not fit the registers beside the tiles)
+#pragma unroll
+        for (int jj = 0; jj < S::BC; ++jj) asm volatile("" : "+v"(av[jj]), "+v"(qv[jj]));
+#pragma unroll
+        for (int i = 0; i < S::BR; ++i) asm volatile("" : "+v"(b[i]));
+      }
       int a1 = 255, a3 = 255;
 #pragma unroll
       for (int i = 0; i < S::BR; ++i) {
@@ -414,13 +429,21 @@ __device__ __forceinline__ void fwd64_role(const Fwd64Args& a, int first_in, int
     return true;
   };
   int q = 0;
-  for (; q + 3 <= total; q += 3) {
-    if (!step(t0, t2, q)) return;
-    if (!step(t1, t0, q + 1)) return;
-    if (!step(t2, t1, q + 2)) return;
+  if (DEPTH == 2) {
+    for (; q + 3 <= total; q += 3) {
+      if (!step(t0, t2, q)) return;
+      if (!step(t1, t0, q + 1)) return;
+      if (!step(t2, t1, q + 2)) return;
+    }
+    if (q < total && !step(t0, t2, q)) return;
+    if (q + 1 < total && !step(t1, t0, q + 1)) return;
+  } else {
+    for (; q + 2 <= total; q += 2) {
+      if (!step(t0, t1, q)) return;
+      if (!step(t1, t0, q + 1)) return;
+    }
+    if (q < total && !step(t0, t1, q)) return;
   }
-  if (q < total && !step(t0, t2, q)) return;
-  if (q + 1 < total && !step(t1, t0, q + 1)) return;
   if (REC) {
     __syncthreads();
     finish_s2(parity ^ 1);
