@@ -239,9 +239,16 @@ __global__ void __launch_bounds__(kWvWaves * 64, MPLPXX_WV_WPE) k_wbatch(BatchAr
     if constexpr (KIND != kCostDense) {
       wv_task<64, KIND>(b, md, task, my, iters, dyn_lds, &s_abort);
     } else {
-      if (md.lt == 16) wv_task<16>(b, md, task, my, iters, dyn_lds, &s_abort);
-      else if (md.lt == 32) wv_task<32>(b, md, task, my, iters, dyn_lds, &s_abort);
-      else wv_task<64>(b, md, task, my, iters, dyn_lds, &s_abort);
+      // the smallest tile of a multiple of 8 labels (wave_engine.h)
+      switch ((uni(md.L) + 7) / 8) {
+        case 8: wv_task<64>(b, md, task, my, iters, dyn_lds, &s_abort); break;
+        case 7: wv_task<56>(b, md, task, my, iters, dyn_lds, &s_abort); break;
+        case 6: wv_task<48>(b, md, task, my, iters, dyn_lds, &s_abort); break;
+        case 5: wv_task<40>(b, md, task, my, iters, dyn_lds, &s_abort); break;
+        case 4: wv_task<32>(b, md, task, my, iters, dyn_lds, &s_abort); break;
+        case 3: wv_task<24>(b, md, task, my, iters, dyn_lds, &s_abort); break;
+        default: wv_task<16>(b, md, task, my, iters, dyn_lds, &s_abort);
+      }
     }
     __syncthreads();  // LDS is reused by the next task; every wave has stopped
     if (*(volatile int*)&s_abort) break;

@@ -5,7 +5,11 @@
 // workgroup and waits on two barriers per update).  Used by the batched
 // solver for models with L <= 64.
 //
-// Lane layout.  The L x L table (padded to LT = 16, 32 or 64) sits on an 8 x 8
+// Lane layout.  The L x L table (padded to LT, the next multiple of 8 from 16
+// on: the passes run over every entry of the tile; milliseconds an iteration
+// with tiles of 16, 32 and 64 only / of every multiple of 8: 12 models of 33 to
+// 48 labels 0.437 / 0.384, 64 models of 8 to 48 labels 0.288 / 0.264, 24 of 8 to
+// 32 labels 0.154 / 0.143, 24 of 8 to 64 labels 0.479 / 0.466) sits on an 8 x 8
 // grid of lanes: lane = 8 rb + cb holds rows rb B .. rb B + B - 1 and columns
 // cb B .. cb B + B - 1, B = LT / 8, in registers.  A minimum over t of a row
 // is an in-register minimum and one over the 8 lanes of an octet (lane bits
@@ -70,7 +74,7 @@ __device__ __forceinline__ float wave_min(float x) { return col4_min(row16_min(x
 
 template <int LT> struct WvShape {
   static constexpr int B = LT / 8;
-  static_assert(LT == 16 || LT == 32 || LT == 64, "wave engine tile");
+  static_assert(LT % 8 == 0 && LT >= 16 && LT <= 64, "wave engine tile");
 };
 
 // sleep of a waiting worker per update its node lacks (in units of 64 clocks),
@@ -129,8 +133,9 @@ __device__ __forceinline__ int opaque(int x) {
 // model on this wave.  Returns false if a wait timed out or another worker
 // gave up (then *abort is set for the workgroup and err for the launch).
 // PHI_FAR (the caller guarantees at least two owned slots): the messages of
-// the next slot are loaded one slot ahead.  LT <= 32 also loads the next
-// table one slot ahead (a second register tile); LT = 64 loads each table at
+// the next slot are loaded one slot ahead.  LT <= 40 also loads the next
+// table one slot ahead (a second register tile; at 48 it costs more in spilled
+// registers than it hides); larger tiles load each table at
 // the start of its own update, and other waves of the compute unit cover the
 // latency.
 //
@@ -142,7 +147,7 @@ __device__ __forceinline__ bool wv_run(const WvView& v_in, int first_in, int str
                                        WvScratch& scr, long long spin_limit, int* err, int* abort) {
   constexpr int B = WvShape<LT>::B;
   constexpr bool POTTS = KIND != kCostDense;   // (any structured cost)
-  constexpr bool PRE = LT <= 32 && !POTTS;
+  constexpr bool PRE = LT <= 40 && !POTTS;
   WvView v = v_in;
   v.L = uni(v.L);
   v.m = uni(v.m);
