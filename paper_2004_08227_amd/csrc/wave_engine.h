@@ -38,6 +38,15 @@
 //    the unaries are in the tagged 64-bit mailbox words of the mailbox
 //    engine (value and version in one word), polled and written with
 //    device-scope atomic accesses.
+// What an update's latency is made of is instructions: everything that decides
+// where control goes is uniform (readfirstlane where it is loaded), so that
+// loops and positions stay scalar; column minima cross the wave four at a time;
+// addresses, the head of the unary update and the next loads are formed where
+// an LDS round trip or a wait covers them.  Before / after these (instructions
+// of a step at 64, 48 and 32 labels 893 / 753, 715 / 599, 600 / 451):
+// milliseconds an iteration of 24 models of 8 to 64 labels 0.466 / 0.433, 24 of
+// 8 to 32 0.143 / 0.131, 64 of 8 to 48 0.264 / 0.253, 12 of 33 to 48 0.384 /
+// 0.353.
 // The messages of a slot are read and written only by the worker that owns
 // the slot, each label by the same lane, so they need no synchronisation.
 #pragma once
@@ -63,14 +72,63 @@ template <int N> __device__ __forceinline__ void oct_min_n(float (&x)[N]) {
 #pragma unroll
   for (int k = 0; k < N; ++k) x[k] = vmin(x[k], dpp_f<0x141>(x[k]));  // the other quad of the octet
 }
+// the two halves of a swap of x and y, row by row of 16 lanes: rows 0, 2 of x
+// and y (swap16), rows 0, 1 of x and y (swap32); the others
+__device__ __forceinline__ void swap16(float& x, float& y) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  x = __uint_as_float(r[0]);
+  y = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap32(float& x, float& y) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  x = __uint_as_float(r[0]);
+  y = __uint_as_float(r[1]);
+}
+// minimum over lanes l, l ^ 16, l ^ 32, l ^ 48 in all four, of four values at
+// once: two swaps and minima leave value k in row k, two more swaps bring each
+// back to every row (12 instructions, 8 for one value alone)
+__device__ __forceinline__ void quad_min(float& a, float& b, float& c, float& d) {
+  swap16(a, b);
+  swap16(c, d);
+  a = vmin(a, b);
+  c = vmin(c, d);
+  swap32(a, c);
+  a = vmin(a, c);
+  b = a;
+  swap16(a, b);
+  c = a;
+  d = b;
+  swap32(a, c);
+  swap32(b, d);
+}
+__device__ __forceinline__ void pair_min(float& a, float& b) {
+  swap16(a, b);
+  a = vmin(a, b);
+  b = a;
+  swap32(a, b);
+  a = vmin(a, b);
+  b = a;
+  swap16(a, b);
+}
 // minimum over the 8 lanes with the same lane & 7 (lane bits 3..5)
 template <int N> __device__ __forceinline__ void stripe_min_n(float (&x)[N]) {
 #pragma unroll
   for (int k = 0; k < N; ++k) x[k] = vmin(x[k], dpp_f<0x128>(x[k]));  // row_ror:8 = lane ^ 8
+  constexpr int Q = N / 4 * 4;
 #pragma unroll
-  for (int k = 0; k < N; ++k) x[k] = col4_min(x[k]);                  // lanes ^ 16, ^ 32
+  for (int k = 0; k < Q; k += 4) quad_min(x[k], x[k + 1], x[k + 2], x[k + 3]);
+  if constexpr (N - Q >= 2) pair_min(x[Q], x[Q + 1]);
+  if constexpr (N % 2 == 1) x[N - 1] = col4_min(x[N - 1]);
 }
-__device__ __forceinline__ float wave_min(float x) { return col4_min(row16_min(x)); }
+// minima of two values over the wave
+__device__ __forceinline__ void wave_min2(float x, float y, float& mx, float& my) {
+  float a[2] = {x, y};
+  row16_min_n<2>(a);
+  const float p = pair16_min(a[0], a[1]);  // rows of lanes 0..15 and 32..47: x, the others: y
+  const float m = join32_min(p, p);
+  mx = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m), 0));
+  my = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m), 16));
+}
 
 template <int LT> struct WvShape {
   static constexpr int B = LT / 8;
@@ -204,18 +262,20 @@ __device__ __forceinline__ bool wv_run(const WvView& v_in, int first_in, int str
     }
     // LDS mode: the prefetches go out now (LDS polls do not wait on them);
     // mailbox mode: after the poll, so that the poll does not queue behind
-    // them in the in-order memory counter
+    // them in the in-order memory counter, and behind the update's first LDS
+    // writes, whose latency covers them
     if (LDSU) prefetch();
     // ---- wait for both nodes, read their unaries in label order ----
     float hu, lu, hv, lv;
+    unsigned long long *dst_u = nullptr, *dst_v = nullptr;
     {
       long long spins = 0;
       if (LDSU) {
         for (;;) {
-          const unsigned cu = (unsigned)__hip_atomic_load(v.lds_ver + si.u, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
-          const unsigned cv = (unsigned)__hip_atomic_load(v.lds_ver + si.v, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
+          const unsigned cu = (unsigned)uni(__hip_atomic_load(v.lds_ver + si.u, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
+          const unsigned cv = (unsigned)uni(__hip_atomic_load(v.lds_ver + si.v, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
           if (cu == want_u && cv == want_v) break;
-          if (++spins > spin_limit || ((spins & 63) == 0 && (*(volatile int*)abort != 0 || ld_dev(err) != 0))) {
+          if (++spins > spin_limit || ((spins & 63) == 0 && uni(*(volatile int*)abort | ld_dev(err)) != 0)) {
             if (lane == 0) {
               if (spins > spin_limit) report_timeout(err, slot, cu != want_u ? si.u : si.v, cu != want_u ? want_u : want_v,
                                                      cu != want_u ? cu : cv);
@@ -231,8 +291,11 @@ __device__ __forceinline__ bool wv_run(const WvView& v_in, int first_in, int str
         hv = v.lds_hi[(size_t)si.v * L + li];
         lv = __uint_as_float((unsigned)v.lds_lo[(size_t)si.v * L + li] << 16);
       } else {
-        const unsigned long long* pu = v.mb + (size_t)si.u * v.mbs + li;
-        const unsigned long long* pv = v.mb + (size_t)si.v * v.mbs + li;
+        unsigned long long* pu = v.mb + (size_t)si.u * v.mbs + li;
+        unsigned long long* pv = v.mb + (size_t)si.v * v.mbs + li;
+        dst_u = lout ? pu : v.sink + lane;
+        dst_v = lout ? pv : v.sink + 64 + lane;
+        asm volatile("" ::"v"(dst_u), "v"(dst_v));  // (formed here, not behind the passes)
         // A node that is ready stays as it is until this update, so only the
         // other one is read again.  A worker is several matchings ahead of
         // the chain; while a node lacks two or more updates it sleeps for
@@ -255,7 +318,7 @@ __device__ __forceinline__ bool wv_run(const WvView& v_in, int first_in, int str
           const unsigned lag_u = (want_u - (unsigned)__builtin_amdgcn_readfirstlane((int)mb_ver(wu))) & 0xFFFFu;
           const unsigned lag_v = (want_v - (unsigned)__builtin_amdgcn_readfirstlane((int)mb_ver(wv))) & 0xFFFFu;
           for (unsigned i = 1, lag = min(max(lag_u, lag_v), kPollLag); i < lag; ++i) __builtin_amdgcn_s_sleep(kPollSleep);
-          if (++spins > spin_limit || ((spins & 255) == 0 && (*(volatile int*)abort != 0 || ld_dev(err) != 0))) {
+          if (++spins > spin_limit || ((spins & 255) == 0 && uni(*(volatile int*)abort | ld_dev(err)) != 0)) {
             if (lane == 0) {
               if (spins > spin_limit) {
                 const bool bad_u = mb_ver(wu) != (want_u & 0xFFFFu);
@@ -271,22 +334,30 @@ __device__ __forceinline__ bool wv_run(const WvView& v_in, int first_in, int str
         lu = mb_lo(wu);
         hv = mb_hi(wv);
         lv = mb_lo(wv);
-        prefetch();
       }
     }
-    const float c_u = wave_min(lout ? hu : kInf);
-    const float c_v = wave_min(lout ? hv : kInf);
+    float c_u, c_v;
+    wave_min2(lout ? hu : kInf, lout ? hv : kInf, c_u, c_v);
     const float delta = 0.5f * (c_u - c_v);
     float phu, phv;
+    float cdu, ceu, cdv, cev;
     if constexpr (POTTS) {
       // centred a' in label order; the three passes by min_other
       const float au = ((hu - c_u) + lu) - fu;
       const float av = ((hv - c_v) + lv) - fv;
+      if (!LDSU) prefetch();
       structured_passes<KIND>(au, av, prm, lout, L, delta, phu, phv);
+      comp_update_head(hu, fu, cdu, ceu);
+      comp_update_head(hv, fv, cdv, cev);
     } else {
       // ---- centred a' in label order, then into the grid ----
       scr.au[lane] = lout ? ((hu - c_u) + lu) - fu : 0x1p127f;
       scr.av[lane] = lout ? ((hv - c_v) + lv) - fv : kPadBig;
+      if (!LDSU) prefetch();
+      // (the head of the unary update needs only the old value and message)
+      comp_update_head(hu, fu, cdu, ceu);
+      comp_update_head(hv, fv, cdv, cev);
+      asm volatile("" : "+v"(cdu), "+v"(ceu), "+v"(cdv), "+v"(cev));
       wave_sync();
       float au[B], av[B];
   #pragma unroll
@@ -331,6 +402,8 @@ __device__ __forceinline__ bool wv_run(const WvView& v_in, int first_in, int str
         r[i] = mn;
       }
       oct_min_n<B>(r);
+  #pragma unroll
+      for (int i = 0; i < B; ++i) asm volatile("" : "+v"(r[i]));  // (finished by every lane, not behind the mask below)
       // ---- results back to label order ----
       {
         // (every lane of an octet holds the same r, every lane of a stripe
@@ -349,8 +422,8 @@ __device__ __forceinline__ bool wv_run(const WvView& v_in, int first_in, int str
       phv = scr.qq[li] + delta;   // new message into v
     }
     float nhu, nlu, nhv, nlv;
-    comp_update(hu, lu, fu, phu, nhu, nlu);
-    comp_update(hv, lv, fv, phv, nhv, nlv);
+    comp_update_tail(cdu, ceu, lu, phu, nhu, nlu);
+    comp_update_tail(cdv, cev, lv, phv, nhv, nlv);
     // ---- publish (what other workers wait for first) ----
     // (every lane issues the same global stores; lanes without a label
     // write this wave's scratch words, so the count of memory operations in
@@ -369,8 +442,8 @@ __device__ __forceinline__ bool wv_run(const WvView& v_in, int first_in, int str
         __hip_atomic_store(v.lds_ver + si.v, (int)(want_v + 1), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     } else {
-      mb_store(lout ? v.mb + (size_t)si.u * v.mbs + lane : v.sink + lane, mb_pack(nhu, nlu, want_u + 1));
-      mb_store(lout ? v.mb + (size_t)si.v * v.mbs + lane : v.sink + 64 + lane, mb_pack(nhv, nlv, want_v + 1));
+      mb_store(dst_u, mb_pack(nhu, nlu, want_u + 1));
+      mb_store(dst_v, mb_pack(nhv, nlv, want_v + 1));
     }
     {
       float* pw = v.phi + (size_t)slot * 2 * L;
