@@ -101,7 +101,7 @@ struct mplpxx_batch {
   bool wave = false;           // the plan runs the wave engine
   double wv_edge_us[3] = {0.05, 0.08, 0.13};  // workgroup time per edge update besides its bytes, LT 16, 32, 64
   double wv_lat_lds_us = 2.4;  // latency of one update, unaries in LDS
-  double wv_lat_mb_us = 2.0;   // latency of one update through the mailboxes
+  double wv_lat_mb_us = 2.2;   // latency of one update through the mailboxes
   size_t wv_static = 0;        // static LDS of the wave kernel
   size_t wv_lds_limit = 0;     // dynamic LDS a workgroup of the wave kernel can have
   size_t wv_lds_cap = 0;       // dynamic LDS that keeps the kernel's register-limited occupancy
@@ -131,8 +131,13 @@ bool lds_fits(const mplpxx_batch* b, int i) {
 
 // Wave engine: a team of T workgroups is T * NW workers.  Per iteration a
 // model needs m / T edge updates of workgroup time, each t_w(LT) plus its
-// bytes at the workgroup's share of the achievable HBM bandwidth (about 3/4
-// of the nominal 8 TB/s), and S matchings one after another, each of
+// bytes at the rate a workgroup streams tables with, half of its share of the
+// nominal 8 TB/s (13 to 17 bytes a nanosecond were measured on teams of every
+// shape, a large copy reaches 19 a compute unit; planned with 23 the large
+// models got too few workgroups: milliseconds an iteration with 3/4 and 2.0 us
+// of latency / with these, 24 models of 20 to 160 nodes and 8 to 64 labels 0.44 /
+// 0.397, 8 up to 120 nodes 0.247 / 0.223, 256 of 20 to 80 nodes and 8 to 32
+// labels 0.310 / 0.286), and S matchings one after another, each of
 // ceil(max_step / (T NW)) rounds of one update latency.
 double wave_model_time(const mplpxx_batch* b, int i, int T, double bw_per_wg_bytes_us) {
   const ModelHost& h = b->mh[i];
@@ -141,7 +146,7 @@ double wave_model_time(const mplpxx_batch* b, int i, int T, double bw_per_wg_byt
   const double workers = (double)T * b->wv_waves;
   const double chain = h.S * std::ceil(h.max_step / workers) * lat;
   const double bytes = (h.potts ? 4.0 * cost_params(h.potts) : 4.0 * h.L * h.L) + 16.0 * h.L;
-  const double work = (double)h.m / T * (tw + bytes / (0.75 * bw_per_wg_bytes_us));
+  const double work = (double)h.m / T * (tw + bytes / (0.5 * bw_per_wg_bytes_us));
   return std::max(chain, work);
 }
 
