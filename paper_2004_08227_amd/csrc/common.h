@@ -62,6 +62,51 @@ struct SlotInfo {
 // 1.43; multiples of 16 the same.
 __host__ __device__ constexpr int mb_row_words(int L) { return (L + 15) / 16 * 16; }
 
+// ---------------------------------------------------------------------------
+// Which compute die a workgroup of the FP32 mailbox engine runs on.
+//
+// The dispatcher hands workgroups to the 8 dies (XCDs) in turn.  In the schedule
+// of a complete graph a node moves from one position of the matching to a
+// neighbouring one, so with positions dealt out like that every handoff crosses
+// dies; with blocks of neighbouring positions on one die only those at the
+// blocks' ends do (a handoff takes 0.31 to 0.35 us within a die, 0.40 to 0.54
+// between dies).  Positions are the slots of a matching; the map needs all
+// matchings to have the same number `ms` of them and G to be a multiple of it, and
+// leaves the slots that logical workgroup w owns (w, w + G, ...) as they are.
+// Workgroups beyond a die's last position leave at once.  Were workgroups dealt
+// out differently, only the gain would be lost.
+//
+// Microseconds a matching, in turn / in blocks, complete graphs of n nodes and L
+// labels: n = 40, L = 24 1.20 / 1.13; 61, 21 1.22 / 1.13; 100, 9 1.11 / 1.07; 100, 32
+// 1.19 / 1.08; 150, 50 1.40 / 1.33; 160, 64 1.33 / 1.28; 200, 16 1.09 / 1.06; 200, 56
+// 1.39 / 1.34; 120, 16 alone no gain, 1.075 / 1.088.  Tables beyond the 256 MB of the
+// last-level cache come from HBM in every iteration, and there the blocks are
+// slower: 200, 64 (326 MB) 1.342 / 1.363.  FP64 runs were within 1.5 % either way
+// and keep the plain order.
+// ---------------------------------------------------------------------------
+struct WgMap {
+  int G;       // logical workgroups
+  int launch;  // workgroups of the launch
+  int ms;      // positions of a matching (0: logical = launched)
+};
+constexpr int kDies = 8;
+constexpr size_t kLastLevelCache = (size_t)256 << 20;
+// even: all matchings have `ms` slots; cap: most workgroups of the launch
+inline WgMap wg_map(int G, int ms, bool even, size_t table_bytes, int cap) {
+  if (even && ms >= kDies && G % ms == 0 && table_bytes <= kLastLevelCache) {
+    const int launch = kDies * ((ms + kDies - 1) / kDies) * (G / ms);
+    if (launch <= cap) return WgMap{G, launch, ms};
+  }
+  return WgMap{G, G, 0};
+}
+// logical workgroup of launched workgroup b (G: none)
+__host__ __device__ inline int wg_logical(const WgMap& w, int b) {
+  if (w.ms == 0) return b;
+  const int d = w.G / w.ms, die = b % kDies, i = b / kDies;
+  const int p = die * w.ms / kDies + i / d;
+  return p < (die + 1) * w.ms / kDies ? i % d * w.ms + p : w.G;
+}
+
 template <typename T> struct HsArgs {
   const T* tables;        // [m][L][L] slot order, read-only (Potts models: [m] weights)
   T* phi;                 // [m][2][L] slot order
@@ -78,6 +123,7 @@ template <typename T> struct HsArgs {
   int L, m, n;
   int mbs;                // FP32 mailbox engine: words from one node's mailbox row to the next
   float* snap;            // [iters][m][2][L] messages of every iteration (launch_mb_snap)
+  WgMap wgs;              // FP32 mailbox engine: the launch's workgroups
   long long spin_limit;
 };
 

@@ -275,20 +275,20 @@ __global__ void __launch_bounds__(kPottsNT + 128) k_persistent_mb_potts(HsArgs<f
   extern __shared__ float phi_lds[];
   const int tid = threadIdx.x;
   const int L = a.L;
-  const int G = gridDim.x;
-  if ((int)blockIdx.x >= a.m) return;
+  const int G = a.wgs.G, wg = wg_logical(a.wgs, blockIdx.x);
+  if (wg >= G || wg >= a.m) return;
   if (tid == 0) sm.abort_flag = 0;
   if (PHI_LDS) {
-    for (int slot = blockIdx.x, j = 0; slot < a.m; slot += G, ++j)
+    for (int slot = wg, j = 0; slot < a.m; slot += G, ++j)
       for (int k = tid; k < 2 * L; k += kPottsNT + 128) phi_lds[j * 2 * L + k] = a.phi[(size_t)slot * 2 * L + k];
   }
   __syncthreads();
   MbView v{a.tables, a.phi, mb, a.slots, a.deg, nullptr, nullptr, a.stamps, L, a.m, a.n, nullptr, nullptr,
-           a.sink + (size_t)blockIdx.x * (kPottsNT + 128), a.mbs};
-  if (!mb_run_potts<PHI_LDS, KIND>(v, blockIdx.x, G, iters, sm, phi_lds, a.spin_limit, a.err)) return;
+           a.sink + (size_t)wg * (kPottsNT + 128), a.mbs};
+  if (!mb_run_potts<PHI_LDS, KIND>(v, wg, G, iters, sm, phi_lds, a.spin_limit, a.err)) return;
   __syncthreads();
   if (PHI_LDS) {
-    for (int slot = blockIdx.x, j = 0; slot < a.m; slot += G, ++j)
+    for (int slot = wg, j = 0; slot < a.m; slot += G, ++j)
       for (int k = tid; k < 2 * L; k += kPottsNT + 128) a.phi[(size_t)slot * 2 * L + k] = phi_lds[j * 2 * L + k];
   }
 }
@@ -367,7 +367,7 @@ static hipError_t launch_mb_one(const HsArgs<float>& a, unsigned long long* mb, 
       const bool far = (a.m / grid) >= (LT <= 64 ? 2 : 1) + 2;
       const void* f = rule == MPLPXX_RULE_M ? mb_rule_kernel<LT, MPLPXX_RULE_M>(phi_in_lds, a.L == LT, far)
                                             : mb_rule_kernel<LT, MPLPXX_RULE_U>(phi_in_lds, a.L == LT, far);
-      const hipError_t e = hipLaunchCooperativeKernel(f, dim3(grid), dim3(NT + 128), args, dyn_lds, st);
+      const hipError_t e = hipLaunchCooperativeKernel(f, dim3(a.wgs.launch), dim3(NT + 128), args, dyn_lds, st);
       if (e != hipSuccess) (void)hipGetLastError();
       return e;
     }
@@ -381,7 +381,7 @@ static hipError_t launch_mb_one(const HsArgs<float>& a, unsigned long long* mb, 
                       : kind == MPLPXX_COST_TRUNC_LINEAR
                           ? mb_gen_kernel<LT, NT, MPLPXX_COST_TRUNC_LINEAR>(phi_in_lds, a.L == LT, far)
                           : mb_gen_kernel<LT, NT, MPLPXX_COST_TRUNC_QUAD>(phi_in_lds, a.L == LT, far);
-      const hipError_t e = hipLaunchCooperativeKernel(f, dim3(grid), dim3(NT + 128), args, dyn_lds, st);
+      const hipError_t e = hipLaunchCooperativeKernel(f, dim3(a.wgs.launch), dim3(NT + 128), args, dyn_lds, st);
       if (e != hipSuccess) (void)hipGetLastError();
       return e;
     }
@@ -403,7 +403,7 @@ static hipError_t launch_mb_one(const HsArgs<float>& a, unsigned long long* mb, 
                   : depth == D0 ? (far ? MPLPXX_PICK(false, true, D0) : MPLPXX_PICK(false, false, D0))
                                 : (far ? MPLPXX_PICK(false, true, 1) : MPLPXX_PICK(false, false, 1));
 #undef MPLPXX_PICK
-  const hipError_t e = hipLaunchCooperativeKernel(f, dim3(grid), dim3(NT + 128), args, dyn_lds, st);
+  const hipError_t e = hipLaunchCooperativeKernel(f, dim3(a.wgs.launch), dim3(NT + 128), args, dyn_lds, st);
   // a refused launch returns its error here; clear the runtime's copy so
   // that it is not reported again by the next call's error check
   if (e != hipSuccess) (void)hipGetLastError();
@@ -492,7 +492,7 @@ hipError_t launch_persistent_mb_potts(const HsArgs<float>& a, unsigned long long
                                     : (const void*)k_persistent_mb_potts<false, MPLPXX_COST_TRUNC_LINEAR>)
                       : (phi_in_lds ? (const void*)k_persistent_mb_potts<true, MPLPXX_COST_POTTS>
                                     : (const void*)k_persistent_mb_potts<false, MPLPXX_COST_POTTS>);
-  const hipError_t e = hipLaunchCooperativeKernel(f, dim3(grid), dim3(kPottsNT + 128), args, dyn_lds, st);
+  const hipError_t e = hipLaunchCooperativeKernel(f, dim3(a.wgs.launch), dim3(kPottsNT + 128), args, dyn_lds, st);
   if (e != hipSuccess) (void)hipGetLastError();  // (see launch_mb_one)
   return e;
 }

@@ -16,7 +16,7 @@ constexpr size_t kPhiLdsTail = 128 * sizeof(float);
 // 2.34 / 2.00, 112 2.33 / 1.92.  (A tile of 48 gains nothing over 64: at 40
 // labels 1.41 / 1.57, at 48 1.41 / 1.39.)
 constexpr bool mb_odd_tile(int L) { return L > 64 && L <= 112; }
-// (four compute waves, dense tables, (H), no trace)
+// (four compute waves, dense tables, (H), no trace; a.wgs is set)
 hipError_t launch_mb_odd(const HsArgs<float>& a, unsigned long long* mb, int grid, int iters, int phi_in_lds,
                          size_t dyn_lds, hipStream_t st);
 
@@ -28,22 +28,22 @@ __global__ void __launch_bounds__(NT + 128) k_persistent_mb(HsArgs<float> a, uns
   extern __shared__ float phi_lds[];
   const int tid = threadIdx.x;
   const int L = FULL ? LT : a.L;
-  const int G = gridDim.x;
-  if ((int)blockIdx.x >= a.m) return;
+  const int G = a.wgs.G, wg = wg_logical(a.wgs, blockIdx.x);
+  if (wg >= G || wg >= a.m) return;
   if (tid == 0) sm.abort_flag = 0;
   if (PHI_LDS) {
-    for (int slot = blockIdx.x, j = 0; slot < a.m; slot += G, ++j)
+    for (int slot = wg, j = 0; slot < a.m; slot += G, ++j)
       for (int k = tid; k < 2 * L; k += NT + 128) phi_lds[j * 2 * L + k] = a.phi[(size_t)slot * 2 * L + k];
   }
   __syncthreads();
   MbView v{a.tables, a.phi, mb, a.slots, a.deg, a.trace, a.trace_e, a.stamps, L, a.m, a.n, nullptr, nullptr,
-           a.sink + (size_t)blockIdx.x * (NT + 128), a.mbs, a.snap};
-  if (!mb_run<LT, NT, PHI_LDS, FULL, TRACE, false, PHI_FAR, DEPTH, KIND, RULE, SNAP>(v, blockIdx.x, G, iters, sm, phi_lds,
+           a.sink + (size_t)wg * (NT + 128), a.mbs, a.snap};
+  if (!mb_run<LT, NT, PHI_LDS, FULL, TRACE, false, PHI_FAR, DEPTH, KIND, RULE, SNAP>(v, wg, G, iters, sm, phi_lds,
                                                                                a.spin_limit, a.err))
     return;
   __syncthreads();
   if (PHI_LDS) {
-    for (int slot = blockIdx.x, j = 0; slot < a.m; slot += G, ++j)
+    for (int slot = wg, j = 0; slot < a.m; slot += G, ++j)
       for (int k = tid; k < 2 * L; k += NT + 128) a.phi[(size_t)slot * 2 * L + k] = phi_lds[j * 2 * L + k];
   }
 }

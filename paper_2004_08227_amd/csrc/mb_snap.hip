@@ -21,7 +21,7 @@ static hipError_t mb_snap_one(const HsArgs<float>& a, unsigned long long* mb, in
       a.L == LT ? (const void*)k_persistent_mb<LT, 256, true, true, false, true, 2, kCostDense, MPLPXX_RULE_H, true>
                 : (const void*)k_persistent_mb<LT, 256, true, false, false, true, 2, kCostDense, MPLPXX_RULE_H, true>;
   const hipError_t e =
-      hipLaunchCooperativeKernel(f, dim3(grid), dim3(256 + 128), args, snap_lds(a.m, a.L, grid) + kPhiLdsTail, st);
+      hipLaunchCooperativeKernel(f, dim3(a.wgs.launch), dim3(256 + 128), args, snap_lds(a.m, a.L, grid) + kPhiLdsTail, st);
   if (e != hipSuccess) (void)hipGetLastError();  // (a refused launch: not left for a later launch check)
   return e;
 }

@@ -21,7 +21,7 @@ static hipError_t mb_odd_one(const HsArgs<float>& a, unsigned long long* mb, int
                              : (full ? (far ? MPLPXX_G(false, true, true) : MPLPXX_G(false, true, false))
                                      : (far ? MPLPXX_G(false, false, true) : MPLPXX_G(false, false, false)));
 #undef MPLPXX_G
-  const hipError_t e = hipLaunchCooperativeKernel(f, dim3(grid), dim3(256 + 128), args, dyn_lds, st);
+  const hipError_t e = hipLaunchCooperativeKernel(f, dim3(a.wgs.launch), dim3(256 + 128), args, dyn_lds, st);
   if (e != hipSuccess) (void)hipGetLastError();  // (a refused launch: not left for a later launch check)
   return e;
 }

@@ -207,6 +207,7 @@ extern "C" int mplpxx_solve_noalloc(int32_t n, int32_t L, int64_t m, const int32
     a.n = n;
     a.mbs = mbs;
     a.spin_limit = 1ll << 22;
+    a.wgs = wg_map(G, max_step, (long long)g.S * max_step == m, mLL * sizeof(float), cus);
     if (solo_fits(n, L, (int)m, g.S, max_step, sizeof(float), false)) {
       const SoloArgs<float> s{d_tab, d_phi, U_dev, d_ulo, d_slots, nullptr, nullptr, L, (int)m, n, g.S};
       HIP_TRY(launch_solo<float>(s, max_step, iters, st));

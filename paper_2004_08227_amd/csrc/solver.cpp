@@ -164,6 +164,10 @@ struct mplpxx_solver {
   }
   int max_deg = 0;
   int max_step = 1;  // edges of the largest matching
+  WgMap wg_map(int G) const {
+    const size_t table = potts ? (size_t)m * cost_params(potts) : (size_t)m * L * L;
+    return mplpxx::wg_map(G, max_step, (long long)S * max_step == m, table * esz, num_cus);
+  }
   int engine() const {
     // FP32 mailboxes carry 16-bit versions: degrees must stay below 2^16
     if (dtype == MPLPXX_F32 && max_deg >= 65536) return ENGINE_STEP;
@@ -705,6 +709,7 @@ template <typename T> int queue_iterate(mplpxx_solver* h, int k, double* trace_h
       HIP_TRY(ensure_sink(h, (size_t)G * (NT + 128)));
       a.sink = h->d_sink;
       a.mbs = mb_row_words(h->L);
+      a.wgs = h->wg_map(G);
       const size_t owned = ((size_t)h->m + G - 1) / G;
       const size_t phi_bytes = owned * 2 * h->L * sizeof(float);
       // (more than one workgroup per compute unit: messages in HBM, so that
@@ -774,6 +779,7 @@ int queue_snapshots(mplpxx_solver* h, int c, float* snap) {
   HsArgs<float> a = hs_args<float>(h, nullptr);
   a.sink = h->d_sink;
   a.mbs = mb_row_words(h->L);
+  a.wgs = h->wg_map(G);
   a.snap = snap;
   HIP_TRY(hipEventRecord(h->ev0, st));
   HIP_TRY(launch_mb_init(static_cast<const float*>(h->d_U), h->d_Ulo, h->d_mb, h->n, h->L, a.mbs, st));
