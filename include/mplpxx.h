@@ -224,8 +224,10 @@ int mplpxx_decode(mplpxx_solver* h, int32_t* labels, double* energy);
  * labelling of the lowest energy seen (the earliest on ties).  Every
  * energy[i] >= every dual[j] (weak duality), so min energy - max dual is a
  * certified bound on the distance of both to the optimum.  All three are
- * HOST buffers (dual, energy: k doubles; best_labels: n int32).  Costs one
- * dual and one rounding per iteration on top of the iteration itself.
+ * HOST buffers (dual, energy: k doubles; best_labels: n int32).  Bounds and
+ * roundings are taken from copies of the messages, of as many iterations
+ * together as fit 64 MiB (a workspace that stays with the handle), behind
+ * those iterations.
  * Errors: MPLPXX_EINVAL (k < 1, NULL dual or energy), MPLPXX_ENOMEM, and
  * those of mplpxx_iterate. */
 int mplpxx_iterate_gap(mplpxx_solver* h, int32_t k, double* dual, double* energy, int32_t* best_labels);
