@@ -805,7 +805,7 @@ template <typename T> bool adjoint_persistent(const mplpxx_solver* h) {
   return sizeof(T) == 8 && h->L <= 64 && h->m > 0 && h->engine() != ENGINE_STEP;
 }
 // `seg` iterations of an FP64 handle on the persistent forward, the
-// unaries through the mailboxes; rec: with argmin records
+// unaries through the mailboxes, queued; rec: with argmin records
 int fwd64_segment(mplpxx_solver* h, int seg, unsigned char* rec) {
   hipStream_t st = h->stream();
   if (!rec && h->solo(false)) {
@@ -818,9 +818,7 @@ int fwd64_segment(mplpxx_solver* h, int seg, unsigned char* rec) {
     HIP_TRY(rec ? launch_adj64(f, Rev64Args{}, nullptr, st) : launch_fwd64(f, st));
     HIP_TRY(launch_mb64_fini(static_cast<double*>(h->d_U), h->d_mb64, h->n, h->L, nullptr, st));
   }
-  const int rc = sync_and_check(h);
-  if (rc == MPLPXX_OK) h->iterations += seg;
-  return rc;
+  return MPLPXX_OK;
 }
 
 // The FP32 run of `h` beside its FP64 twin's in one launch (adj_pair.hip),
@@ -844,7 +842,7 @@ hipError_t clear_state32(mplpxx_solver* h, hipStream_t st) {
   if (e == hipSuccess) e = hipMemsetAsync(h->d_Ulo, 0, nL * sizeof(float), st);
   return e;
 }
-// `seg` iterations of both, on the twin's stream
+// `seg` iterations of both, queued on the twin's stream
 int pair_segment(mplpxx_solver* h, mplpxx_solver* h32, int seg, unsigned char* rec) {
   hipStream_t st = h->stream();
   Fwd64Args f{};
@@ -861,14 +859,7 @@ int pair_segment(mplpxx_solver* h, mplpxx_solver* h32, int seg, unsigned char* r
   HIP_TRY(launch_adj_pair(f, a, h32->d_mb, G, st));
   HIP_TRY(launch_mb64_fini(static_cast<double*>(h->d_U), h->d_mb64, h->n, h->L, nullptr, st));
   HIP_TRY(launch_mb_fini(static_cast<float*>(h32->d_U), h32->d_Ulo, h32->d_mb, h32->n, h32->L, a.mbs, nullptr, st));
-  int rc = sync_and_check(h);
-  const int rc32 = sync_and_check(h32);  // (clears its error words, whatever the other run ended with)
-  if (rc == MPLPXX_OK) rc = rc32;
-  if (rc == MPLPXX_OK) {
-    h->iterations += seg;
-    h32->iterations += seg;
-  }
-  return rc;
+  return MPLPXX_OK;
 }
 
 // beside: the FP32 handle whose own run of K iterations from phi = 0 goes along
@@ -944,9 +935,17 @@ int adjoint_forward_t(mplpxx_solver* h, int K, int every, double* loss, mplpxx_s
                           : iterate_t<T>(h, seg, nullptr);
     if (rc != MPLPXX_OK) return rc;
   }
+  if (beside) HIP_TRY(hipEventRecord(beside->ev1, st));
+  if (pers) {
+    // (one check behind all segments: those after a timed-out one end at once)
+    int rc = sync_and_check(h);
+    const int rc32 = beside ? sync_and_check(beside) : MPLPXX_OK;  // (clears its error words, whatever the other run ended with)
+    if (rc == MPLPXX_OK) rc = rc32;
+    if (rc != MPLPXX_OK) return rc;
+    h->iterations = K;
+  }
   if (beside) {
-    HIP_TRY(hipEventRecord(beside->ev1, st));
-    HIP_TRY(hipEventSynchronize(beside->ev1));
+    beside->iterations = K;
     float ms = 0.f;
     HIP_TRY(hipEventElapsedTime(&ms, beside->ev0, beside->ev1));
     beside->last_ms = ms;
@@ -1031,9 +1030,9 @@ template <typename T, typename O> int adjoint_backward_t(mplpxx_solver* h, O* gr
                         rev ? fwd64_grid(h, cap) : 0};
       HIP_TRY(launch_adj64(f, r, static_cast<double*>(h->d_thb), st));
       if (rev) HIP_TRY(launch_mb64_fini(static_cast<double*>(h->d_Ub), mb_rev, h->n, h->L, nullptr, st));
-      const int rc = sync_and_check(h);
-      if (rc != MPLPXX_OK) return rc;
     }
+    const int rc = sync_and_check(h);  // (before the caller's buffers are written)
+    if (rc != MPLPXX_OK) return rc;
     // (recomputed segments have taken the buffers of the recorded ones)
     if (h->adj_rec_from > 0) h->adj_rec_from = nck;
   }
