@@ -31,12 +31,12 @@ __global__ void __launch_bounds__(kF64NT + 128) k_adj_pair(Fwd64Args f, HsArgs<f
   extern __shared__ __align__(16) double pair_lds[];
   const int tid = threadIdx.x;
   const int b = blockIdx.x;
-  if (tid == 0) smf.abort_flag = sm.abort_flag = 0;
   if (b < f.grid) {
-    __syncthreads();
+    if (failed_before(f.err, smf.abort_flag)) return;
     fwd64_role<LT, true, REC, false>(f, b, f.grid, smf, pair_lds);
     return;
   }
+  if (failed_before(a.err, sm.abort_flag)) return;
   const int first = b - f.grid;
   const int L = a.L;
   float* phi_lds = reinterpret_cast<float*>(pair_lds);

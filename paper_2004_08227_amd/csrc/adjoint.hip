@@ -478,6 +478,10 @@ __device__ __forceinline__ void rev64_role(const Rev64Args& a, int first_in, int
 // the recording forward of `f.iters` iterations of another: they share no
 // data, so they run side by side on the device.  Each workgroup has kF64NT +
 // 128 threads; the reverse uses wave 0 and the two sync waves.
+// Segments are queued behind one another without a check between them, and a
+// segment whose recording timed out has left records that nobody wrote: the
+// launches behind it end at once (failed_before) instead of taking such bytes
+// for labels.
 template <int LT, bool PHI_LDS>
 __global__ void __launch_bounds__(kF64NT + 128) k_adj64(Fwd64Args f, Rev64Args r) {
   __shared__ SmemF64<LT> smf;
@@ -485,15 +489,11 @@ __global__ void __launch_bounds__(kF64NT + 128) k_adj64(Fwd64Args f, Rev64Args r
   extern __shared__ __align__(16) double phi_lds64[];
   const int b = blockIdx.x;
   if (b < r.grid) {
-    if (b >= r.m || r.seg <= 0) return;
-    if (threadIdx.x == 0) smr.abort_flag = 0;
-    __syncthreads();
+    if (b >= r.m || r.seg <= 0 || failed_before(r.err, smr.abort_flag)) return;
     rev64_role<LT>(r, b, r.grid, smr);
   } else {
     const int first = b - r.grid;
-    if (first >= f.m || f.iters <= 0) return;
-    if (threadIdx.x == 0) smf.abort_flag = 0;
-    __syncthreads();
+    if (first >= f.m || f.iters <= 0 || failed_before(f.err, smf.abort_flag)) return;
     fwd64_role<LT, PHI_LDS, true, false>(f, first, f.grid, smf, phi_lds64);
   }
 }
@@ -501,9 +501,7 @@ template <int LT, bool PHI_LDS, bool TRACE>
 __global__ void __launch_bounds__(kF64NT + 128) k_fwd64(Fwd64Args f) {
   __shared__ SmemF64<LT> smf;
   extern __shared__ __align__(16) double phi_lds64[];
-  if ((int)blockIdx.x >= f.m) return;
-  if (threadIdx.x == 0) smf.abort_flag = 0;
-  __syncthreads();
+  if ((int)blockIdx.x >= f.m || failed_before(f.err, smf.abort_flag)) return;
   fwd64_role<LT, PHI_LDS, false, TRACE>(f, blockIdx.x, f.grid, smf, phi_lds64);
 }
 
@@ -511,11 +509,13 @@ __global__ void __launch_bounds__(kF64NT + 128) k_fwd64(Fwd64Args f) {
 // iterations descending, within each r (thb(s, t3(s)) += rb(s)), then q
 // (thb(s2(t), t) += q-bar(t)), then p (thb(s, t1(s)) += p-bar(s)): the
 // order of the per-matching reverse.  One workgroup per slot, the slot's
-// table adjoint in LDS.
+// table adjoint in LDS.  (After a failed launch there may be no records.)
 template <int LT>
 __global__ void __launch_bounds__(256) k_thb_acc(double* __restrict__ thb, const unsigned char* __restrict__ rec,
-                                                 const double* __restrict__ contrib, int L, int m, int seg) {
+                                                 const double* __restrict__ contrib, int L, int m, int seg,
+                                                 const int* __restrict__ err) {
   __shared__ double g[LT * LT];
+  if (ld_dev(err) != 0) return;
   const int slot = blockIdx.x;
   const int tid = threadIdx.x;
   double* gt = thb + (size_t)slot * L * L;
@@ -587,7 +587,8 @@ static hipError_t adj64_one(const Fwd64Args& f, const Rev64Args& r, double* thb,
   const hipError_t e = coop(fn, grid, args, lds, st);
   if (e != hipSuccess) return e;
   if (r.grid > 0 && r.seg > 0 && r.m > 0) {
-    hipLaunchKernelGGL(k_thb_acc<LT>, dim3(r.m), dim3(256), 0, st, thb, r.rec, r.contrib, r.L, r.m, r.seg);
+    hipLaunchKernelGGL(k_thb_acc<LT>, dim3(r.m), dim3(256), 0, st, thb, r.rec, r.contrib, r.L, r.m, r.seg,
+                       r.err);
     return hipGetLastError();
   }
   return hipSuccess;

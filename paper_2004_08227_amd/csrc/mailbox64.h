@@ -77,6 +77,14 @@ __device__ __forceinline__ bool mb64_gather(const unsigned long long* __restrict
 
 constexpr int kF64NT = 256;  // compute threads of the FP64 mailbox forward
 
+// Start of a workgroup: clears its abort flag; true in every thread if an earlier
+// launch has already failed (steps that abort set the flag to 1 or more)
+__device__ __forceinline__ bool failed_before(const int* err, int& abort_flag) {
+  if (threadIdx.x == 0) abort_flag = ld_dev(err) != 0 ? -1 : 0;
+  __syncthreads();
+  return abort_flag == -1;
+}
+
 template <int LT> struct SmemF64 {
   double hu[2][LT];   // the step's nodes from the sync waves (double buffered)
   double hv[2][LT];

@@ -1,0 +1,34 @@
+"""An adjoint whose waits give up: no wait may be taken for a result, neither by the launches
+queued behind it nor by a later call."""
+import numpy as np
+import pytest
+
+import paper_2004_08227_amd as M
+from paper_2004_08227_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+ETIMEOUT = -4
+
+
+def _backward_fails(s):
+    s.set_option(M.OPT_SPIN_LIMIT, 1)  # (from the host: every wait gives up at once and every kernel ends)
+    with pytest.raises(M.MplpError) as e:
+        s.adjoint_backward()
+    assert e.value.code == ETIMEOUT
+    s.set_option(M.OPT_SPIN_LIMIT, 0)
+
+
+# one-workgroup forwards keep no records: every segment's are made by the backward, the last
+# one's shorter than the buffer, in tiles of 16 and 32 labels and with the records of one
+# segment only
+@pytest.mark.parametrize("n,L,K,every", [(8, 4, 7, 3), (5, 27, 11, 4), (8, 16, 3, 5)])
+def test_segments_behind_a_failed_recomputation(n, L, K, every):
+    print("CASE", n, L, K, every, flush=True)
+    model = W.uniform(n, L, seed=n + L, dtype=np.float64)
+    with M.Solver.from_model(model) as s, M.Solver.from_model(model) as ref:
+        ref.adjoint_forward(K, every)
+        want = ref.adjoint_backward()
+        s.adjoint_forward(K, every)
+        _backward_fails(s)
+        for x, y in zip(s.adjoint_backward(), want):
+            assert np.array_equal(x, y)
