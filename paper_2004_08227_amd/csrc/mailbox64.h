@@ -154,6 +154,9 @@ __device__ __forceinline__ int col4_imin(int x) {
 // index whose candidate equals the minimum; s2 needs the waves' row ranges
 // joined, which the next step's barriers do for free (its record is written
 // one step later).
+// Costs near the largest double overflow to infinities and their differences to
+// NaN, and then no candidate, or only a padded one, equals the minimum: a record
+// is at most L - 1 all the same (the reverse takes it for a label).
 template <int LT, bool PHI_LDS, bool REC, bool TRACE>
 __device__ __forceinline__ void fwd64_role(const Fwd64Args& a, int first_in, int G_in, SmemF64<LT>& sm, double* phi_lds) {
   constexpr int NT = kF64NT;
@@ -285,7 +288,7 @@ __device__ __forceinline__ void fwd64_role(const Fwd64Args& a, int first_in, int
     int s2 = sm.redi[par][0][out_ic];
 #pragma unroll
     for (int w = 1; w < S::W; ++w) s2 = min(s2, sm.redi[par][w][out_ic]);
-    *(outk && !out_u ? rec_prev + out_i : reinterpret_cast<unsigned char*>(sink)) = (unsigned char)s2;
+    *(outk && !out_u ? rec_prev + out_i : reinterpret_cast<unsigned char*>(sink)) = (unsigned char)min(s2, L - 1);
   };
   auto step = [&](double (&xc)[S::BR][S::BC], double (&xp)[S::BR][S::BC], int q) __attribute__((always_inline)) -> bool {
     const int slot = first + j * G;
@@ -424,8 +427,8 @@ __device__ __forceinline__ void fwd64_role(const Fwd64Args& a, int first_in, int
       }
       unsigned char* rc = a.rec + (size_t)it * rec_it + (size_t)slot * 3 * L;
       unsigned char* sk = reinterpret_cast<unsigned char*>(sink + 16);
-      *(outk && out_u ? rc + out_i : sk) = (unsigned char)a1;
-      *(outk && out_u ? rc + 2 * L + out_i : sk) = (unsigned char)a3;
+      *(outk && out_u ? rc + out_i : sk) = (unsigned char)min(a1, L - 1);
+      *(outk && out_u ? rc + 2 * L + out_i : sk) = (unsigned char)min(a3, L - 1);
       rec_prev = rc + L;
     }
     if (!PHI_LDS && owned > 1 && q + 1 < total) load_phi64(nxt, nj);

@@ -32,3 +32,26 @@ def test_segments_behind_a_failed_recomputation(n, L, K, every):
         _backward_fails(s)
         for x, y in zip(s.adjoint_backward(), want):
             assert np.array_equal(x, y)
+
+
+# finite costs whose sums overflow: no argmin may leave the labels.  Whatever labels the
+# records name, an update's reverse keeps the sum of its two nodes' adjoints (rows and
+# columns of the table included), so the unary gradient sums to the number of nodes that
+# seeded it (one each; a node whose values are all NaN may or may not).
+@pytest.mark.parametrize("n,L", [(8, 7), (40, 20), (40, 33), (30, 64)])
+def test_records_name_labels_whatever_overflows(n, L):
+    print("CASE", n, L, flush=True)
+    model = W.uniform(n, L, seed=L, dtype=np.float64)
+    rng = np.random.default_rng(n)
+    model.unaries[:] = 1e308 * rng.uniform(-1, 1, model.unaries.shape)
+    model.pairwise[:] = 1.7e308 * rng.uniform(-1, 1, model.pairwise.shape)
+    with M.Solver.from_model(model) as s:
+        s.adjoint_forward(5, 2)
+        U = s.get_state()[0]
+        gu, gp = s.adjoint_backward()
+        again = s.adjoint_backward()
+    assert np.isfinite(gu).all() and np.isfinite(gp).all()
+    seeds = round(float(gu.sum()))
+    assert (U < np.inf).any(1).sum() <= seeds <= n
+    assert abs(gu.sum() - seeds) <= 1e-12 * gu.size * max(1.0, np.abs(gu).max())
+    assert np.array_equal(gu, again[0]) and np.array_equal(gp, again[1])
