@@ -999,6 +999,10 @@ template <typename T, typename O> int adjoint_backward_t(mplpxx_solver* h, O* gr
     HIP_TRY(hipMemsetAsync(h->d_thb, 0, (size_t)h->m * h->L * h->L * esz, st));
   }
   const bool pers = adjoint_persistent<T>(h) && h->d_contrib;
+  // Recomputed segments take the buffers of the recorded ones: from here on the
+  // checkpoints alone count, however this call ends.
+  const int rec_from = h->adj_rec_from;
+  if (rec_from > 0 || !pers) h->adj_rec_from = nck;
   if (pers) {
     // Persistent pipeline: launch c runs the reverse of segment c beside the
     // recomputation (with argmin records) of segment c - 1, which needs only
@@ -1016,7 +1020,7 @@ template <typename T, typename O> int adjoint_backward_t(mplpxx_solver* h, O* gr
       return e;
     };
     for (int c = nck; c >= 0; --c) {
-      const bool rev = c < nck, fwd = c >= 1 && c - 1 < h->adj_rec_from;
+      const bool rev = c < nck, fwd = c >= 1 && c - 1 < rec_from;
       if (!rev && !fwd) continue;
       if (fwd) HIP_TRY(restore(c - 1));
       if (rev) HIP_TRY(launch_mb64_init(static_cast<const double*>(h->d_Ub), mb_rev, h->n, h->L, st));
@@ -1033,8 +1037,6 @@ template <typename T, typename O> int adjoint_backward_t(mplpxx_solver* h, O* gr
     }
     const int rc = sync_and_check(h);  // (before the caller's buffers are written)
     if (rc != MPLPXX_OK) return rc;
-    // (recomputed segments have taken the buffers of the recorded ones)
-    if (h->adj_rec_from > 0) h->adj_rec_from = nck;
   }
   for (int c = nck - 1; c >= 0 && h->m > 0 && !pers; --c) {
     const int seg = std::min(every, K - c * every);

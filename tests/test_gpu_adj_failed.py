@@ -55,3 +55,32 @@ def test_records_name_labels_whatever_overflows(n, L):
     assert (U < np.inf).any(1).sum() <= seeds <= n
     assert abs(gu.sum() - seeds) <= 1e-12 * gu.size * max(1.0, np.abs(gu).max())
     assert np.array_equal(gu, again[0]) and np.array_equal(gp, again[1])
+
+
+# a backward that fails, or one on the other engine, has overwritten what the forward
+# recorded: the next one starts from the checkpoints
+@pytest.mark.parametrize("K,every", [(3, 3), (6, 3), (8, 3), (9, 2)])
+def test_backward_after_a_failed_one(K, every):
+    print("CASE", K, every, flush=True)
+    model = W.uniform(40, 20, seed=K, dtype=np.float64)
+    with M.Solver.from_model(model) as s, M.Solver.from_model(model) as ref:
+        ref.adjoint_forward(K, every)
+        want = ref.adjoint_backward()
+        s.adjoint_forward(K, every)
+        _backward_fails(s)
+        for x, y in zip(s.adjoint_backward(), want):
+            assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("K,every", [(3, 3), (6, 3), (8, 3), (9, 2)])
+def test_backward_on_both_engines(K, every):
+    print("CASE", K, every, flush=True)
+    model = W.uniform(40, 20, seed=K, dtype=np.float64)
+    with M.Solver.from_model(model) as s:
+        s.adjoint_forward(K, every)
+        got = []
+        for engine in (M.ENGINE_STEP, 0, M.ENGINE_STEP, 0, 0):
+            s.set_option(M.OPT_ENGINE, engine)
+            got.append(s.adjoint_backward())
+    for g in got[1:]:
+        assert np.array_equal(g[0], got[0][0]) and np.array_equal(g[1], got[0][1])
