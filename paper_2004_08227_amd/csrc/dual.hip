@@ -216,6 +216,8 @@ hipError_t launch_trace_sum(double* trace_nodes, const float* trace_e, int m, in
 // are added in wave order after the reparametrized unary.
 // ---------------------------------------------------------------------------
 constexpr int kDecW = 16;               // waves per node = partial sums
+// nodes of a launch (the threads of one are a 32-bit number: 2^22 - 1 nodes at most)
+constexpr int kDecodeLaunch = 1 << 21;
 constexpr size_t kDecStage = 44 * 1024;  // largest table copied to LDS (with the partial sums within 64 KB)
 
 __global__ void k_decode_init(int* __restrict__ labels, int n, int* __restrict__ ticket) {
@@ -382,14 +384,14 @@ __global__ void __launch_bounds__(256) k_energy_terms(const T* __restrict__ unar
                                                       const SlotInfo* __restrict__ slots,
                                                       const int* __restrict__ labels, int n, int L, int m, int potts,
                                                       double* __restrict__ node_e, double* __restrict__ edge_e) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   labels += (size_t)blockIdx.y * n;
   node_e += (size_t)blockIdx.y * n;
   edge_e += (size_t)blockIdx.y * m;
-  if (i < n) {
-    node_e[i] = (double)unaries[(size_t)i * L + labels[i]];
-  } else if (i - n < m) {
-    const int slot = i - n;
+  if (i < (size_t)n) {
+    node_e[i] = (double)unaries[i * L + labels[i]];
+  } else if (i - n < (size_t)m) {
+    const int slot = (int)(i - n);
     edge_e[slot] = (double)table_at(tables, slot, L, labels[slots[slot].u], labels[slots[slot].v], potts);
   }
 }
@@ -399,19 +401,23 @@ hipError_t launch_decode(const T* unaries, const T* tables, const T* phi, const 
                          const int* inc, int n, int L, int m, int* labels, int* ticket, double* node_e, double* edge_e,
                          double* energy, int* err, long long spin_limit, hipStream_t st, int potts, int states) {
   const int all = n * states;
-  hipLaunchKernelGGL(k_decode_init, dim3((all + 255) / 256), dim3(256), 0, st, labels, all, ticket);
+  hipLaunchKernelGGL(k_decode_init, dim3((unsigned)(((size_t)all + 255) / 256)), dim3(256), 0, st, labels, all, ticket);
   const size_t tab = (size_t)L * L * sizeof(T);
   const int stage = !potts && m > 0 && tab <= kDecStage;
   const size_t dyn = L * sizeof(T) + (stage ? tab : 0);
   constexpr int B1 = sizeof(T) == 4 ? 16 : 8;
-  if (L <= 64)
-    hipLaunchKernelGGL((k_decode<T, 1, B1>), dim3(all), dim3(kDecW * 64), dyn, st, unaries, tables, phi, slots,
-                       node_ptr, inc, n, L, m, states, potts, stage, labels, ticket, err, spin_limit);
-  else
-    hipLaunchKernelGGL((k_decode<T, 2, B1 / 2>), dim3(all), dim3(kDecW * 64), dyn, st, unaries, tables, phi, slots,
-                       node_ptr, inc, n, L, m, states, potts, stage, labels, ticket, err, spin_limit);
-  hipLaunchKernelGGL(k_energy_terms<T>, dim3((n + m + 255) / 256, states), dim3(256), 0, st, unaries, tables, slots, labels, n,
-                     L, m, potts, node_e, edge_e);
+  // (the tickets run on from one launch to the next)
+  for (int left = all; left > 0; left -= kDecodeLaunch) {
+    const dim3 grid(std::min(left, kDecodeLaunch));
+    if (L <= 64)
+      hipLaunchKernelGGL((k_decode<T, 1, B1>), grid, dim3(kDecW * 64), dyn, st, unaries, tables, phi, slots,
+                         node_ptr, inc, n, L, m, states, potts, stage, labels, ticket, err, spin_limit);
+    else
+      hipLaunchKernelGGL((k_decode<T, 2, B1 / 2>), grid, dim3(kDecW * 64), dyn, st, unaries, tables, phi, slots,
+                         node_ptr, inc, n, L, m, states, potts, stage, labels, ticket, err, spin_limit);
+  }
+  hipLaunchKernelGGL(k_energy_terms<T>, dim3((unsigned)(((size_t)n + m + 255) / 256), states), dim3(256), 0, st, unaries,
+                     tables, slots, labels, n, L, m, potts, node_e, edge_e);
   hipLaunchKernelGGL(k_sum2, dim3(states), dim3(1024), 0, st, node_e, n, edge_e, m, energy);
   return hipGetLastError();
 }

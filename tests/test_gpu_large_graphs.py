@@ -1,0 +1,44 @@
+"""Graphs whose nodes or edges outnumber what one launch can hold (its threads are a 32-bit
+number)."""
+import numpy as np
+import pytest
+
+import paper_2004_08227_amd as M
+
+pytestmark = pytest.mark.gpu
+
+
+def test_rounding_beyond_a_launch():
+    """2^22 nodes and more: rounded in several launches, edges within and across them."""
+    n, rng = (1 << 22) + 5, np.random.default_rng(0)
+    un = rng.integers(0, 8, (n, 2)).astype(np.float32)
+    at = [0, 1, (1 << 20) - 1, (1 << 21) - 1, 1 << 21, (1 << 22) - 2, (1 << 22) - 1, 1 << 22, n - 2, n - 1]
+    edges = np.array(list(zip(at, at[1:])) + [(0, n - 1), (5, 1 << 21)], dtype=np.int32)
+    pw = rng.integers(-9, 9, (len(edges), 2, 2)).astype(np.float32)
+    print("CASE", n, flush=True)
+    with M.Solver(n, 2, edges, un, pw) as s:
+        labels, energy = s.decode()
+    x = un.argmin(1)
+    for u in sorted(set(edges.ravel().tolist())):
+        c = un[u] + sum(pw[k, x[a]] for k, (a, b) in enumerate(edges.tolist()) if b == u)
+        x[u] = int(c.argmin())
+    assert np.array_equal(labels, x)
+    assert energy == un[np.arange(n), x].sum(dtype=np.float64) + sum(float(pw[k, x[a], x[b]]) for k, (a, b) in enumerate(edges.tolist()))
+
+
+def test_gap_states_beyond_a_launch():
+    """300 labellings of 16369 nodes at once."""
+    n, k, rng = 16369, 300, np.random.default_rng(1)
+    un = rng.random((n, 3)).astype(np.float32)
+    edges = np.array([[0, n - 1], [3, 4]], dtype=np.int32)
+    pw = rng.random((2, 3, 3)).astype(np.float32)
+    print("CASE", n, k, flush=True)
+    with M.Solver(n, 3, edges, un, pw) as s, M.Solver(n, 3, edges, un, pw) as t:
+        dual, energy, best = s.iterate_gap(k)
+        for i in range(3):
+            t.iterate(1)
+            assert dual[i] == t.dual_bound() and energy[i] == t.decode()[1]
+        t.iterate(k - 3)
+        labels, e = t.decode()
+        assert dual[-1] == t.dual_bound() and energy[-1] == e
+        assert np.array_equal(best, labels) or energy.min() < e
