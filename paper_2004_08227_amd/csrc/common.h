@@ -7,6 +7,12 @@
 
 namespace mplpxx {
 
+// Workgroups of a launch over `count` items that takes them at a grid stride: a
+// launch's threads are a 32-bit number, and 2^20 workgroups are far more than run
+// at once.
+constexpr unsigned kMaxBlocks = 1u << 20;
+inline unsigned stride_blocks(size_t count) { return count < kMaxBlocks ? (unsigned)count : kMaxBlocks; }
+
 enum { ENGINE_AUTO = 0, ENGINE_STEP = 1, ENGINE_PERSISTENT = 2 };
 
 // Pairwise cost of a model: a dense L x L table per edge, or a structured

@@ -473,16 +473,17 @@ template hipError_t launch_pack_tables<double, float>(const double*, float*, con
 // messages in the caller's edge order from slot order
 template <typename T>
 __global__ void __launch_bounds__(128) k_phi_by_edge(const T* __restrict__ phi_slot, const int* __restrict__ slot_of_edge,
-                                                     int row, T* __restrict__ out) {
-  const size_t e = blockIdx.x;
-  const T* src = phi_slot + (size_t)slot_of_edge[e] * row;
-  for (int i = threadIdx.x; i < row; i += 128) out[e * row + i] = src[i];
+                                                     int m, int row, T* __restrict__ out) {
+  for (size_t e = blockIdx.x; e < (size_t)m; e += gridDim.x) {
+    const T* src = phi_slot + (size_t)slot_of_edge[e] * row;
+    for (int i = threadIdx.x; i < row; i += 128) out[e * row + i] = src[i];
+  }
 }
 
 template <typename T>
 hipError_t launch_phi_by_edge(const T* phi_slot, const int* slot_of_edge, int m, int L, T* out, hipStream_t st) {
   if (m <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_phi_by_edge<T>, dim3((unsigned)m), dim3(128), 0, st, phi_slot, slot_of_edge, 2 * L, out);
+  hipLaunchKernelGGL(k_phi_by_edge<T>, dim3(stride_blocks(m)), dim3(128), 0, st, phi_slot, slot_of_edge, m, 2 * L, out);
   return hipGetLastError();
 }
 

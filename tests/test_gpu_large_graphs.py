@@ -42,3 +42,18 @@ def test_gap_states_beyond_a_launch():
         labels, e = t.decode()
         assert dual[-1] == t.dual_bound() and energy[-1] == e
         assert np.array_equal(best, labels) or energy.min() < e
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_messages_of_more_edges_than_workgroups(dtype):
+    """More than 2^20 edges put into the caller's order at a grid stride."""
+    m, rng = (1 << 20) + 3, np.random.default_rng(2)
+    perm = rng.permutation(2 * m).astype(np.int32).reshape(m, 2)  # one matching, in any order and orientation
+    un = rng.random((2 * m, 1)).astype(dtype)
+    pw = rng.random((m, 1, 1)).astype(dtype)
+    phi = rng.random((m, 2, 1)).astype(dtype)
+    print("CASE", m, dtype.__name__, flush=True)
+    with M.Solver(2 * m, 1, perm, un, pw) as s:
+        s.set_state(un, phi)
+        U, got = s.get_state()
+    assert np.array_equal(U, un) and np.array_equal(got, phi)
