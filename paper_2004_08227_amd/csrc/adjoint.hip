@@ -265,31 +265,33 @@ hipError_t launch_adj_seed(const T* U, const T* Ulo, int n, int L, T* Ub, double
 // adjoints in a second set of mailboxes.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(64) k_mb64_init(const double* __restrict__ x, unsigned long long* __restrict__ mb,
-                                                  int L) {
-  const size_t u = blockIdx.x;
-  for (int s = threadIdx.x; s < L; s += 64) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(x[u * L + s]);
-    unsigned long long* w = mb + u * mb64_row_words(L) + 2 * s;
-    w[0] = b & 0xffffffffull;
-    w[1] = b >> 32;
+                                                  int n, int L) {
+  for (size_t u = blockIdx.x; u < (size_t)n; u += gridDim.x) {
+    for (int s = threadIdx.x; s < L; s += 64) {
+      const unsigned long long b = (unsigned long long)__double_as_longlong(x[u * L + s]);
+      unsigned long long* w = mb + u * mb64_row_words(L) + 2 * s;
+      w[0] = b & 0xffffffffull;
+      w[1] = b >> 32;
+    }
   }
 }
 // values back; trace_row: their minimum per node
 __global__ void __launch_bounds__(64) k_mb64_fini(double* __restrict__ x, const unsigned long long* __restrict__ mb,
-                                                  int L, double* __restrict__ trace_row) {
-  const size_t u = blockIdx.x;
-  double mn = __builtin_inf();
-  for (int s = threadIdx.x; s < L; s += 64) {
-    const unsigned long long* w = mb + u * mb64_row_words(L) + 2 * s;
-    const double v = __longlong_as_double((long long)((w[0] & 0xffffffffull) | (w[1] << 32)));
-    x[u * L + s] = v;
-    mn = vmin(mn, v);
-  }
-  if (trace_row) {
-    mn = row16_min(mn);
-    mn = pair16_min(mn, mn);
-    mn = join32_min(mn, mn);
-    if (threadIdx.x == 0) trace_row[u] = mn;
+                                                  int n, int L, double* __restrict__ trace_row) {
+  for (size_t u = blockIdx.x; u < (size_t)n; u += gridDim.x) {
+    double mn = __builtin_inf();
+    for (int s = threadIdx.x; s < L; s += 64) {
+      const unsigned long long* w = mb + u * mb64_row_words(L) + 2 * s;
+      const double v = __longlong_as_double((long long)((w[0] & 0xffffffffull) | (w[1] << 32)));
+      x[u * L + s] = v;
+      mn = vmin(mn, v);
+    }
+    if (trace_row) {
+      mn = row16_min(mn);
+      mn = pair16_min(mn, mn);
+      mn = join32_min(mn, mn);
+      if (threadIdx.x == 0) trace_row[u] = mn;
+    }
   }
 }
 
@@ -536,11 +538,11 @@ __global__ void __launch_bounds__(256) k_thb_acc(double* __restrict__ thb, const
 }
 
 hipError_t launch_mb64_init(const double* x, unsigned long long* mb, int n, int L, hipStream_t st) {
-  hipLaunchKernelGGL(k_mb64_init, dim3(n), dim3(64), 0, st, x, mb, L);
+  hipLaunchKernelGGL(k_mb64_init, dim3(stride_blocks(n)), dim3(64), 0, st, x, mb, n, L);
   return hipGetLastError();
 }
 hipError_t launch_mb64_fini(double* x, const unsigned long long* mb, int n, int L, double* trace_row, hipStream_t st) {
-  hipLaunchKernelGGL(k_mb64_fini, dim3(n), dim3(64), 0, st, x, mb, L, trace_row);
+  hipLaunchKernelGGL(k_mb64_fini, dim3(stride_blocks(n)), dim3(64), 0, st, x, mb, n, L, trace_row);
   return hipGetLastError();
 }
 

@@ -310,35 +310,41 @@ size_t wbatch_lds_limit(size_t* static_bytes, int kind) {
 __global__ void __launch_bounds__(64) k_u_to_mb(const float* __restrict__ U, const float* __restrict__ Ulo,
                                                 unsigned long long* __restrict__ mb,
                                                 const BatchModel* __restrict__ models,
-                                                const int* __restrict__ node_model) {
-  const BatchModel& md = models[node_model[blockIdx.x]];
-  const int u = blockIdx.x - md.node_off;
-  for (int s = threadIdx.x; s < md.L; s += 64) {
-    const size_t i = md.u_off + (size_t)u * md.L + s;
-    mb[md.mb_off + (size_t)u * mb_row_words(md.L) + s] = mb_pack(U[i], Ulo[i], 0u);
+                                                const int* __restrict__ node_model, int total_nodes) {
+  for (size_t g = blockIdx.x; g < (size_t)total_nodes; g += gridDim.x) {
+    const BatchModel& md = models[node_model[g]];
+    const size_t u = g - md.node_off;
+    for (int s = threadIdx.x; s < md.L; s += 64) {
+      const size_t i = md.u_off + u * md.L + s;
+      mb[md.mb_off + u * mb_row_words(md.L) + s] = mb_pack(U[i], Ulo[i], 0u);
+    }
   }
 }
 __global__ void __launch_bounds__(64) k_mb_to_u(float* __restrict__ U, float* __restrict__ Ulo,
                                                 const unsigned long long* __restrict__ mb,
                                                 const BatchModel* __restrict__ models,
-                                                const int* __restrict__ node_model) {
-  const BatchModel& md = models[node_model[blockIdx.x]];
-  const int u = blockIdx.x - md.node_off;
-  for (int s = threadIdx.x; s < md.L; s += 64) {
-    const size_t i = md.u_off + (size_t)u * md.L + s;
-    const unsigned long long w = mb[md.mb_off + (size_t)u * mb_row_words(md.L) + s];
-    U[i] = mb_hi(w);
-    Ulo[i] = mb_lo(w);
+                                                const int* __restrict__ node_model, int total_nodes) {
+  for (size_t g = blockIdx.x; g < (size_t)total_nodes; g += gridDim.x) {
+    const BatchModel& md = models[node_model[g]];
+    const size_t u = g - md.node_off;
+    for (int s = threadIdx.x; s < md.L; s += 64) {
+      const size_t i = md.u_off + u * md.L + s;
+      const unsigned long long w = mb[md.mb_off + u * mb_row_words(md.L) + s];
+      U[i] = mb_hi(w);
+      Ulo[i] = mb_lo(w);
+    }
   }
 }
 hipError_t launch_u_to_mb(const float* U, const float* Ulo, unsigned long long* mb, const BatchModel* models,
                           const int* node_model, int total_nodes, hipStream_t st) {
-  hipLaunchKernelGGL(k_u_to_mb, dim3(total_nodes), dim3(64), 0, st, U, Ulo, mb, models, node_model);
+  hipLaunchKernelGGL(k_u_to_mb, dim3(stride_blocks(total_nodes)), dim3(64), 0, st, U, Ulo, mb, models, node_model,
+                     total_nodes);
   return hipGetLastError();
 }
 hipError_t launch_mb_to_u(float* U, float* Ulo, const unsigned long long* mb, const BatchModel* models,
                           const int* node_model, int total_nodes, hipStream_t st) {
-  hipLaunchKernelGGL(k_mb_to_u, dim3(total_nodes), dim3(64), 0, st, U, Ulo, mb, models, node_model);
+  hipLaunchKernelGGL(k_mb_to_u, dim3(stride_blocks(total_nodes)), dim3(64), 0, st, U, Ulo, mb, models, node_model,
+                     total_nodes);
   return hipGetLastError();
 }
 

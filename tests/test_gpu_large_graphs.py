@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 import paper_2004_08227_amd as M
+from paper_2004_08227_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +58,26 @@ def test_messages_of_more_edges_than_workgroups(dtype):
         s.set_state(un, phi)
         U, got = s.get_state()
     assert np.array_equal(U, un) and np.array_equal(got, phi)
+
+
+def test_mailboxes_of_more_nodes_than_workgroups():
+    """More than 2^20 nodes into the mailboxes and back: those of an FP64 model, whose first
+    and last nodes have edges, and those of a batch."""
+    n, rng = (1 << 20) + 3, np.random.default_rng(3)
+    edges = np.array([[0, n - 1], [1, n - 1], [0, 2], [n - 2, n - 3]], dtype=np.int32)
+    un, pw = rng.random((n, 2)), rng.random((4, 2, 2))
+    small = np.array([0, 1, 2, n - 3, n - 2, n - 1])
+    near = np.searchsorted(small, edges).astype(np.int32)
+    print("CASE", n, flush=True)
+    with M.Solver(n, 2, edges, un, pw) as s, M.Solver(6, 2, near, un[small], pw) as t:
+        assert np.isclose(s.iterate_trace(3)[-1] - t.iterate_trace(3)[-1], np.delete(un, small, 0).min(1).sum(), rtol=1e-12)
+        (U, phi), (V, psi) = s.get_state(), t.get_state()
+    assert np.array_equal(U[small], V) and np.array_equal(phi, psi)
+    assert np.array_equal(np.delete(U, small, 0), np.delete(un, small, 0))
+    un, pw = un.astype(np.float32), pw.astype(np.float32)
+    one, two = W.Model(n, 2, edges, un, pw), W.Model(6, 2, near, un[small], pw)
+    with M.Batch([one, two]) as b:
+        b.iterate(3)
+        (U, phi), (V, psi) = b.get_state(0)[:2], b.get_state(1)[:2]
+    assert np.array_equal(U[small], V) and np.array_equal(phi, psi)
+    assert np.array_equal(np.delete(U, small, 0), np.delete(un, small, 0))
