@@ -321,7 +321,7 @@ int mplpxx_iterate_trace(mplpxx_solver* h, int32_t k, double* trace);
 #define MPLPXX_OPT_THREADS 2     /* threads per workgroup: 0 auto, 256, 512, 1024; 64 (one compute
                                     wave, FP32 persistent engine) up to 32 labels */
 #define MPLPXX_OPT_GRID 3        /* workgroups of the persistent engine (0 auto) */
-#define MPLPXX_OPT_SPIN_LIMIT 4  /* device wait bound in polls (0 default) */
+#define MPLPXX_OPT_SPIN_LIMIT 4  /* bound in polls of the device waits of iterations and adjoints (0 default) */
 #define MPLPXX_OPT_PROFILE 5     /* 1: record per-slot timestamps (persistent FP32 engine) */
 #define MPLPXX_OPT_ADJOINT_F64 6 /* FP32 handles: 1 (default) differentiate an FP64 run on the same costs
                                     (exactly widened); 0: differentiate the FP32 run itself */

@@ -596,16 +596,24 @@ hipError_t queue_dual(mplpxx_solver* h, double* out) {
 // the rounding of Eq. (5) into the device array `labels`, its energy into
 // the device double `energy` (d_node_min, d_edge_min and the third scalar
 // are scratch)
+//
+// A node's workgroup may start long before its neighbours are labelled (hundreds
+// of nodes are in flight, 1.7 us apart where each waits for the last one), so a
+// limit that suits the handoffs of an iteration would end a rounding that makes
+// progress: OPT_SPIN_LIMIT does not count here where it is smaller than this.
+// (Every wait ends anyway: a node waits for nodes that have started before it.)
+constexpr long long kDecodeSpin = 1ll << 26;
 hipError_t queue_decode(mplpxx_solver* h, int* labels, double* energy, const void* phi, double* node_e, double* edge_e,
                         int states) {
   int* ticket = reinterpret_cast<int*>(h->d_scalar + 2);
+  const long long spins = std::max(h->spin_limit, kDecodeSpin);
   if (h->dtype == MPLPXX_F32)
     return launch_decode<float>((const float*)h->d_unaries, (const float*)h->d_tables, (const float*)phi, h->d_slots,
                                 h->d_node_ptr, h->d_inc, h->n, h->L, h->m, labels, ticket, node_e, edge_e, energy,
-                                h->d_err, h->spin_limit, h->stream(), h->potts, states);
+                                h->d_err, spins, h->stream(), h->potts, states);
   return launch_decode<double>((const double*)h->d_unaries, (const double*)h->d_tables, (const double*)phi,
                                h->d_slots, h->d_node_ptr, h->d_inc, h->n, h->L, h->m, labels, ticket, node_e, edge_e,
-                               energy, h->d_err, h->spin_limit, h->stream(), 0, states);
+                               energy, h->d_err, spins, h->stream(), 0, states);
 }
 hipError_t queue_decode(mplpxx_solver* h, int* labels, double* energy) {
   return queue_decode(h, labels, energy, h->d_phi, h->d_node_min, h->d_edge_min, 1);
