@@ -377,7 +377,9 @@ int mplpxx_get_step_profile(mplpxx_solver* h, int64_t* stamps);
 
 /* Average duration in milliseconds of the device work of the last iterate
  * call, measured with HIP events on the handle's stream around the launch
- * (0 if none). */
+ * (0 if none).  mplpxx_iterate_gap: of one of its iterations.
+ * mplpxx_adjoint_forward of an FP32 handle: of its FP32 run, also where that
+ * shares a launch with the FP64 run (then by the device's clock). */
 int mplpxx_last_iterate_ms(mplpxx_solver* h, double* ms);
 
 /* ------------------------------------------------------------------------

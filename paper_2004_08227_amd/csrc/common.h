@@ -235,11 +235,11 @@ hipError_t launch_adj64(const Fwd64Args& f, const Rev64Args& r, double* thb, hip
 
 // one launch: f.iters iterations of the FP64 forward beside as many of the FP32
 // mailbox engine on `grid32` workgroups (adj_pair.hip); adj_pair_fits: whether
-// these grids can be launched so
+// these grids can be launched so; clk: two zeroed words that give the FP32 run's time
 constexpr int kPairNT = 256;  // compute threads of each role
 bool adj_pair_fits(int m, int L, int grid64, int grid32);
 hipError_t launch_adj_pair(const Fwd64Args& f, const HsArgs<float>& a, unsigned long long* mb, int grid32,
-                           hipStream_t st);
+                           unsigned long long* clk, hipStream_t st);
 
 int max_blocks_per_cu_mb(int LT, int NT);
 // the (M) and (U) updates on the per-matching engine (rules.hip); rule 1 = M, 2 = U

@@ -851,7 +851,7 @@ hipError_t clear_state32(mplpxx_solver* h, hipStream_t st) {
   return e;
 }
 // `seg` iterations of both, queued on the twin's stream
-int pair_segment(mplpxx_solver* h, mplpxx_solver* h32, int seg, unsigned char* rec) {
+int pair_segment(mplpxx_solver* h, mplpxx_solver* h32, int seg, unsigned char* rec, unsigned long long* clk) {
   hipStream_t st = h->stream();
   Fwd64Args f{};
   HIP_TRY(fwd64_args(h, seg, &f));
@@ -864,7 +864,7 @@ int pair_segment(mplpxx_solver* h, mplpxx_solver* h32, int seg, unsigned char* r
   a.mbs = mb_row_words(h32->L);
   HIP_TRY(launch_mb64_init(static_cast<const double*>(h->d_U), h->d_mb64, h->n, h->L, st));
   HIP_TRY(launch_mb_init(static_cast<const float*>(h32->d_U), h32->d_Ulo, h32->d_mb, h32->n, h32->L, a.mbs, st));
-  HIP_TRY(launch_adj_pair(f, a, h32->d_mb, G, st));
+  HIP_TRY(launch_adj_pair(f, a, h32->d_mb, G, clk, st));
   HIP_TRY(launch_mb64_fini(static_cast<double*>(h->d_U), h->d_mb64, h->n, h->L, nullptr, st));
   HIP_TRY(launch_mb_fini(static_cast<float*>(h32->d_U), h32->d_Ulo, h32->d_mb, h32->n, h32->L, a.mbs, nullptr, st));
   return MPLPXX_OK;
@@ -891,7 +891,8 @@ int adjoint_forward_t(mplpxx_solver* h, int K, int every, double* loss, mplpxx_s
   const size_t o_U = part((nck + 1) * nL * esz), o_lo = part(h->d_Ulo ? (nck + 1) * nL * sizeof(float) : 0),
                o_phi = part((nck + 1) * mp * esz), o_rec = part(rec_bytes), o_Ub = part(nL * esz), o_pb = part(mp * esz),
                o_thb = part((size_t)h->m * h->L * h->L * esz),
-               o_contrib = part(pers ? (size_t)every * h->m * 3 * h->L * sizeof(double) : 0);
+               o_contrib = part(pers ? (size_t)every * h->m * 3 * h->L * sizeof(double) : 0),
+               o_clk = part(beside ? (size_t)nck * 2 * sizeof(unsigned long long) : 0);
   if (h->adj_size != used || !h->d_adj) {
     if (h->d_adj) (void)hipFree(h->d_adj);
     h->d_adj = nullptr;
@@ -915,6 +916,7 @@ int adjoint_forward_t(mplpxx_solver* h, int K, int every, double* loss, mplpxx_s
     HIP_TRY(hipMalloc(&h->d_edge_flip, h->m * sizeof(int)));
     HIP_TRY(hipMemcpyAsync(h->d_edge_flip, h->flip.data(), h->m * sizeof(int), hipMemcpyHostToDevice, st));
   }
+  auto* clk = reinterpret_cast<unsigned long long*>(h->d_adj + o_clk);  // [nck][2] the FP32 run's segments on the device's clock
   // start from phi = 0, U = theta_u
   HIP_TRY(hipStreamSynchronize(st));
   HIP_TRY(hipMemsetAsync(h->d_phi, 0, mp * esz, st));
@@ -925,7 +927,7 @@ int adjoint_forward_t(mplpxx_solver* h, int K, int every, double* loss, mplpxx_s
     HIP_TRY(hipStreamSynchronize(beside->stream()));
     HIP_TRY(clear_state32(beside, st));
     beside->iterations = 0;
-    HIP_TRY(hipEventRecord(beside->ev0, st));
+    HIP_TRY(hipMemsetAsync(clk, 0, (size_t)nck * 2 * sizeof(unsigned long long), st));
   }
   for (int c = 0; c < nck; ++c) {
     HIP_TRY(hipMemcpyAsync((char*)h->d_ck_U + c * nL * esz, h->d_U, nL * esz, hipMemcpyDeviceToDevice, st));
@@ -938,27 +940,29 @@ int adjoint_forward_t(mplpxx_solver* h, int K, int every, double* loss, mplpxx_s
     // workgroup, without records)
     const bool record = pers && c >= nck - 2 && !h->solo(false);
     unsigned char* rec = record ? h->d_rec + (size_t)(c & 1) * every * h->m * 3 * h->L : nullptr;
-    const int rc = beside ? pair_segment(h, beside, seg, rec)
+    const int rc = beside ? pair_segment(h, beside, seg, rec, clk + 2 * (size_t)c)
                    : pers ? fwd64_segment(h, seg, rec)
                           : iterate_t<T>(h, seg, nullptr);
     if (rc != MPLPXX_OK) return rc;
   }
-  if (beside) HIP_TRY(hipEventRecord(beside->ev1, st));
+  std::vector<unsigned long long> ticks(beside ? 2 * (size_t)nck : 0);
   if (pers) {
     // (one check behind all segments: those after a timed-out one end at once)
     int rc = sync_and_check(h);
-    const int rc32 = beside ? sync_and_check(beside) : MPLPXX_OK;  // (clears its error words, whatever the other run ended with)
-    if (rc == MPLPXX_OK) rc = rc32;
+    if (beside) {  // (clears its error words, whatever the other run ended with)
+      const Result r{clk, ticks.data(), ticks.size() * sizeof(unsigned long long)};
+      const int rc32 = finish(beside, nullptr, nullptr, &r, 1);
+      if (rc == MPLPXX_OK) rc = rc32;
+    }
     if (rc != MPLPXX_OK) return rc;
     h->iterations = K;
   }
   if (beside) {
     beside->iterations = K;
-    float ms = 0.f;
-    HIP_TRY(hipEventElapsedTime(&ms, beside->ev0, beside->ev1));
-    beside->last_ms = ms;
-    beside->timed = true;
-    beside->timed_calls = 1;
+    beside->last_ms = 0.0;
+    for (int c = 0; c < nck; ++c)
+      beside->last_ms += (double)(ticks[2 * c + 1] - ~ticks[2 * c]) / beside->wallclock_khz;
+    beside->timed = false;  // (not between the two events)
   }
   HIP_TRY(hipMemcpyAsync((char*)h->d_ck_U + nck * nL * esz, h->d_U, nL * esz, hipMemcpyDeviceToDevice, st));
   if (h->d_Ulo)
