@@ -104,6 +104,20 @@ inline int mb_default_grid(int max_step, int num_cus, long long m, int L, const 
   return (int)std::min<long long>(num_cus, std::max<long long>(2ll * max_step, fit));
 }
 
+// `k` iterations of a mailbox engine on `grid` workgroups, f(done, c) for the next
+// c of them: in as few launches as a workgroup can count its updates of in 31 bits
+// (a state passes from one launch to the next bit for bit).
+template <typename F> inline hipError_t in_launches(int k, long long m, int grid, const F& f) {
+  const long long owned = (m + grid - 1) / grid;
+  const int most = (int)std::max(1ll, (1ll << 30) / std::max(1ll, owned));
+  hipError_t e = hipSuccess;
+  for (int done = 0, c; done < k && e == hipSuccess; done += c) {
+    c = std::min(most, k - done);
+    e = f(done, c);
+  }
+  return e;
+}
+
 // messages of at least this size are put into the caller's edge order on the
 // device when a state is read (figures at mplpxx_get_state)
 constexpr size_t kExportOnDevice = 1 << 20;

@@ -708,11 +708,8 @@ template <typename T> int queue_iterate(mplpxx_solver* h, int k, double* trace_h
       }
     } else if (sizeof(T) == 4) {
       // FP32: tagged mailboxes; messages stay in LDS when they fit
-      HsArgs<float> a = hs_args<float>(h, trace_host ? h->d_trace_nodes : nullptr);
-      if (trace_host) {
-        a.trace_e = h->d_trace_e;
-        trace_w = NT / 64;
-      }
+      HsArgs<float> a = hs_args<float>(h, nullptr);
+      if (trace_host) trace_w = NT / 64;
       const int G = h->grid();
       HIP_TRY(ensure_sink(h, (size_t)G * (NT + 128)));
       a.sink = h->d_sink;
@@ -723,23 +720,35 @@ template <typename T> int queue_iterate(mplpxx_solver* h, int k, double* trace_h
       // (more than one workgroup per compute unit: messages in HBM, so that
       // the workgroups' LDS never limits how many fit)
       const int in_lds = phi_bytes <= kPhiLdsBudget && G <= h->num_cus && h->phi_opt != 2 ? 1 : 0;
-      HIP_TRY(launch_mb_init(static_cast<const float*>(h->d_U), h->d_Ulo, h->d_mb, h->n, h->L, a.mbs, st));
-      if (h->potts && !h->gen_tiles())
-        HIP_TRY(launch_persistent_mb_potts(a, h->d_mb, G, k, in_lds, in_lds ? phi_bytes : 0, st, h->potts));
-      else
-        HIP_TRY(launch_persistent_mb(a, h->d_mb, LT, NT, G, k, in_lds, in_lds ? phi_bytes : 0, st, h->prefetch_opt,
-                                     h->gen_tiles() ? h->potts : 0, rule_mb ? h->rule : MPLPXX_RULE_H));
-      HIP_TRY(launch_mb_fini(static_cast<float*>(h->d_U), h->d_Ulo, h->d_mb, h->n, h->L, a.mbs,
-                             trace_host ? h->d_trace_nodes + (size_t)(k - 1) * h->n : nullptr, st));
+      HIP_TRY(in_launches(k, h->m, G, [&](int done, int c) -> hipError_t {
+        if (trace_host) {
+          a.trace = h->d_trace_nodes + (size_t)done * h->n;
+          a.trace_e = h->d_trace_e + (size_t)done * h->m * trace_w;
+        }
+        hipError_t e = launch_mb_init(static_cast<const float*>(h->d_U), h->d_Ulo, h->d_mb, h->n, h->L, a.mbs, st);
+        if (e != hipSuccess) return e;
+        if (h->potts && !h->gen_tiles())
+          e = launch_persistent_mb_potts(a, h->d_mb, G, c, in_lds, in_lds ? phi_bytes : 0, st, h->potts);
+        else
+          e = launch_persistent_mb(a, h->d_mb, LT, NT, G, c, in_lds, in_lds ? phi_bytes : 0, st, h->prefetch_opt,
+                                   h->gen_tiles() ? h->potts : 0, rule_mb ? h->rule : MPLPXX_RULE_H);
+        if (e != hipSuccess) return e;
+        return launch_mb_fini(static_cast<float*>(h->d_U), h->d_Ulo, h->d_mb, h->n, h->L, a.mbs,
+                              trace_host ? a.trace + (size_t)(c - 1) * h->n : nullptr, st);
+      }));
     } else if (h->L <= 64) {
       // FP64: the mailbox forward (two tagged words per label, no fences)
       Fwd64Args f{};
       HIP_TRY(fwd64_args(h, k, &f));
-      f.trace = trace_host ? h->d_trace_nodes : nullptr;
-      HIP_TRY(launch_mb64_init(static_cast<const double*>(h->d_U), h->d_mb64, h->n, h->L, st));
-      HIP_TRY(launch_fwd64(f, st));
-      HIP_TRY(launch_mb64_fini(static_cast<double*>(h->d_U), h->d_mb64, h->n, h->L,
-                               trace_host ? h->d_trace_nodes + (size_t)(k - 1) * h->n : nullptr, st));
+      HIP_TRY(in_launches(k, h->m, f.grid, [&](int done, int c) -> hipError_t {
+        f.iters = c;
+        f.trace = trace_host ? h->d_trace_nodes + (size_t)done * h->n : nullptr;
+        hipError_t e = launch_mb64_init(static_cast<const double*>(h->d_U), h->d_mb64, h->n, h->L, st);
+        if (e == hipSuccess) e = launch_fwd64(f, st);
+        if (e != hipSuccess) return e;
+        return launch_mb64_fini(static_cast<double*>(h->d_U), h->d_mb64, h->n, h->L,
+                                trace_host ? f.trace + (size_t)(c - 1) * h->n : nullptr, st);
+      }));
     } else {
       HsArgs<T> a = hs_args<T>(h, trace_host ? h->d_trace_nodes : nullptr);
       HIP_TRY(launch_fill_int(h->d_ver, 0, h->n, st));

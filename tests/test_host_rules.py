@@ -30,3 +30,24 @@ def test_strided_launches_hold_any_count(run):
     const size_t b = stride_blocks(c);
     CHECK(b <= c && (c == 0 || b > 0) && b * 1024 < ((size_t)1 << 32));
   }""")
+
+
+def test_iterations_of_a_launch_are_counted_in_31_bits(run):
+    run("""
+  for (int k : {0, 1, 7, 130000, 2147483647})
+    for (long long m : {1ll, 2ll, 4950ll, 4498500ll, 0x3fffffffll})
+      for (int grid : {1, 2, 100, 256, 1024}) {
+        const long long owned = (m + grid - 1) / grid;
+        if (owned > 1000000 && k > 130000) continue;
+        int sum = 0, calls = 0;
+        CHECK(in_launches(k, m, grid, [&](int done, int c) {
+          CHECK(done == sum && c >= 1 && owned * c <= (c == 1 ? owned : 1ll << 30));
+          sum += c;
+          ++calls;
+          return hipSuccess;
+        }) == hipSuccess);
+        CHECK(sum == k && (owned * k > (1ll << 30) || calls == (k > 0)));
+      }
+  int calls = 0;
+  CHECK(in_launches(5, 1ll << 40, 1, [&](int, int) { return ++calls == 2 ? hipErrorUnknown : hipSuccess; }) == hipErrorUnknown);
+  CHECK(calls == 2);""")
