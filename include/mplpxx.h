@@ -319,8 +319,10 @@ int mplpxx_iterate_trace(mplpxx_solver* h, int32_t k, double* trace);
                                     (FP32 handles with a node of degree >= 65536
                                     always run one launch per matching) */
 #define MPLPXX_OPT_THREADS 2     /* threads per workgroup: 0 auto, 256, 512, 1024; 64 (one compute
-                                    wave, FP32 persistent engine) up to 32 labels */
-#define MPLPXX_OPT_GRID 3        /* workgroups of the persistent engine (0 auto) */
+                                    wave, FP32 persistent engine) up to 32 labels.  The persistent
+                                    engine runs FP64 models up to 64 labels on 256 whatever this says */
+#define MPLPXX_OPT_GRID 3        /* workgroups of the persistent engine (0 auto; FP64 up to 64 labels:
+                                    at most one per compute unit is used) */
 #define MPLPXX_OPT_SPIN_LIMIT 4  /* bound in polls of the device waits of iterations and adjoints (0 default) */
 #define MPLPXX_OPT_PROFILE 5     /* 1: record per-slot timestamps (persistent FP32 engine) */
 #define MPLPXX_OPT_ADJOINT_F64 6 /* FP32 handles: 1 (default) differentiate an FP64 run on the same costs
@@ -358,7 +360,8 @@ int mplpxx_set_option(mplpxx_solver* h, int32_t key, int64_t value);
 #define MPLPXX_INFO_STEPS 4
 #define MPLPXX_INFO_DTYPE 5
 #define MPLPXX_INFO_ENGINE 6     /* engine the next iterate call will use */
-#define MPLPXX_INFO_GRID 7       /* workgroups of the persistent engine */
+#define MPLPXX_INFO_GRID 7       /* workgroups of the persistent engine's mailbox kernels (a small model on
+                                    one workgroup: those it would have there) */
 #define MPLPXX_INFO_THREADS 8    /* threads per workgroup */
 #define MPLPXX_INFO_ITERATIONS 9 /* iterations run since create / set_state */
 #define MPLPXX_INFO_WALLCLOCK_KHZ 10 /* device wall-clock rate of the timestamps */

@@ -183,6 +183,9 @@ struct mplpxx_solver {
            (threads_opt == 0 || threads_opt == 256);
   }
   bool mb_engine() const { return dtype == MPLPXX_F32 && engine() == ENGINE_PERSISTENT; }
+  // the FP64 mailbox engine (mailbox64.h): 256 compute threads, at most one
+  // workgroup per compute unit
+  bool mb64_engine() const { return dtype == MPLPXX_F64 && L <= 64 && engine() == ENGINE_PERSISTENT; }
   // no option asks for one of the engines' ways
   bool plain() const {
     return rule == MPLPXX_RULE_H && !potts && engine_opt == ENGINE_AUTO && threads_opt == 0 && grid_opt == 0 &&
@@ -192,6 +195,9 @@ struct mplpxx_solver {
   bool solo(bool trace) const { return plain() && solo_fits(n, L, m, S, max_step, esz, trace); }
   int grid() const {
     int g = grid_opt > 0 ? grid_opt : num_cus;
+    if (mb64_engine())
+      g = grid_opt > 0 ? std::min(grid_opt, num_cus)
+                       : mb_default_grid(std::min(max_step, num_cus), num_cus, m, L, [] { return 1; }, sizeof(double));
     if (grid_opt == 0 && (mb_engine() || rule_mailbox()))
       g = mb_default_grid(max_step, num_cus, m, L, [&] {
         return potts && !gen_tiles() ? max_blocks_per_cu_mb_potts() : max_blocks_per_cu_mb(LT(), NT());
@@ -740,6 +746,7 @@ template <typename T> int queue_iterate(mplpxx_solver* h, int k, double* trace_h
       // FP64: the mailbox forward (two tagged words per label, no fences)
       Fwd64Args f{};
       HIP_TRY(fwd64_args(h, k, &f));
+      f.grid = h->grid();
       HIP_TRY(in_launches(k, h->m, f.grid, [&](int done, int c) -> hipError_t {
         f.iters = c;
         f.trace = trace_host ? h->d_trace_nodes + (size_t)done * h->n : nullptr;
@@ -1518,6 +1525,9 @@ int mplpxx_set_option(mplpxx_solver* h, int32_t key, int64_t value) {
       if (value < 0) return fail(MPLPXX_EINVAL, "grid must be >= 0");
       const int nb = h->potts && !h->gen_tiles() ? max_blocks_per_cu_mb_potts()
                      : h->mb_engine() ? max_blocks_per_cu_mb(h->LT(), h->NT())
+                     // (FP64 up to 64 labels: what the workgroups of NT() threads that ran it
+                     // without mailboxes allowed; more than one per compute unit counts as one)
+                     : h->dtype == MPLPXX_F64 && h->L <= 64 ? (h->L <= 32 ? 1792 : 1024) / h->NT()
                      : h->dtype == MPLPXX_F32 ? max_blocks_per_cu<float>(ENGINE_PERSISTENT, h->LT(), h->NT())
                                               : max_blocks_per_cu<double>(ENGINE_PERSISTENT, h->LT(), h->NT());
       if (value > (int64_t)nb * h->num_cus) return fail(MPLPXX_EINVAL, "grid %lld exceeds co-resident limit %d", (long long)value, nb * h->num_cus);
