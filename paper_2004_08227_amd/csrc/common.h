@@ -248,7 +248,7 @@ hipError_t launch_step_rule(const HsArgs<T>& a, int rule, int LT, int NT, int sl
 template <typename T>
 hipError_t launch_handshake(const HsArgs<T>& a, int engine, int LT, int NT, int slot_begin, int count, int grid,
                             int iters, hipStream_t st);
-template <typename T> int max_blocks_per_cu(int engine, int LT, int NT);
+template <typename T> int max_blocks_per_cu(int LT, int NT);
 // FP32 persistent engine with tagged mailboxes
 // prefetch: steps the tables are loaded ahead (0 the default: 2 for tiles up
 // to 64, 1 for 128; 1: one step, for tiles up to 64 without a trace)

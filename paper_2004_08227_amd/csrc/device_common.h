@@ -106,64 +106,9 @@ __device__ __forceinline__ void col4_min_store(const float (&x)[BC], float* red,
   }
 }
 
-// lowest-index minimum of (v, i) pairs: the other pair wins if smaller, or
-// equal with a smaller index (its bits are kept, as a scan in index order
-// keeps the first of equal values).  Written as selects: no branch.
-__device__ __forceinline__ void argmin_merge(double& v, int& i, double ov, int oi) {
-  const bool take = (ov < v) | ((ov == v) & (oi < i));
-  v = take ? ov : v;
-  i = take ? oi : i;
-}
-// the same when the other index is known to be the larger (a scan in index
-// order): strictly smaller values win
-__device__ __forceinline__ void argmin_next(double& v, int& i, double ov, int oi) {
-  const bool take = ov < v;
-  v = take ? ov : v;
-  i = take ? oi : i;
-}
-template <int CTRL> __device__ __forceinline__ void argmin_dpp(double& v, int& i) {
-  const double ov = dpp_f<CTRL>(v);
-  const int oi = __builtin_amdgcn_update_dpp(0, i, CTRL, 0xF, 0xF, false);
-  argmin_merge(v, i, ov, oi);
-}
-// over the 16 lanes of a row
-__device__ __forceinline__ void row16_argmin(double& v, int& i) {
-  argmin_dpp<0xB1>(v, i);
-  argmin_dpp<0x4E>(v, i);
-  argmin_dpp<0x141>(v, i);
-  argmin_dpp<0x140>(v, i);
-}
-// over lanes l, l^16, l^32, l^48 (gfx950 permlane swaps of the two halves
-// and the index: each lane gets its partner's values)
+// a double from its halves
 __device__ __forceinline__ double dbl_of(unsigned lo, unsigned hi) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-__device__ __forceinline__ void col4_argmin(double& v, int& i) {
-  {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
-    const auto ix = __builtin_amdgcn_permlane16_swap((unsigned)i, (unsigned)i, false, false);
-    // each swap leaves this lane's own value in one half and the partner's
-    // in the other; which is which is the same for all three
-    const double a0 = dbl_of(lo[0], hi[0]), a1 = dbl_of(lo[1], hi[1]);
-    double w = a0;
-    int k = (int)ix[0];
-    argmin_merge(w, k, a1, (int)ix[1]);
-    v = w;
-    i = k;
-  }
-  {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
-    const auto ix = __builtin_amdgcn_permlane32_swap((unsigned)i, (unsigned)i, false, false);
-    double w = dbl_of(lo[0], hi[0]);
-    int k = (int)ix[0];
-    argmin_merge(w, k, dbl_of(lo[1], hi[1]), (int)ix[1]);
-    v = w;
-    i = k;
-  }
 }
 
 // the value of x in lane addr / 4

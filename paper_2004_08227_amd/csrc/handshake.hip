@@ -186,7 +186,8 @@ __global__ void __launch_bounds__(NT) k_step(HsArgs<T> a, int slot_begin) {
 }
 
 // ---------------------------------------------------------------------------
-// Engine 2: persistent.  Workgroup w owns the slots w, w+G, w+2G, ... (a
+// Engine 2: persistent on version counters (FP64 above 64 labels; the others run on
+// mailboxes).  Workgroup w owns the slots w, w+G, w+2G, ... (a
 // static map, so an edge's messages never leave one workgroup) and visits
 // them in schedule order for every iteration.  Before updating edge (u, v) it
 // waits until u and v have seen exactly the updates that precede this one in
@@ -319,6 +320,10 @@ __global__ void k_mb_fini(float* __restrict__ U, float* __restrict__ Ulo, const 
 // ---------------------------------------------------------------------------
 // Launchers.
 // ---------------------------------------------------------------------------
+// models that run persistently on version counters: FP64 above 64 labels (all
+// others run on tagged mailboxes)
+template <typename T, int LT> constexpr bool kOnVersions = sizeof(T) == 8 && LT > 64;
+
 template <typename T, int LT, int NT>
 static hipError_t launch_one(const HsArgs<T>& a, int engine, int slot_begin, int count, int grid, int iters,
                              hipStream_t st) {
@@ -327,10 +332,13 @@ static hipError_t launch_one(const HsArgs<T>& a, int engine, int slot_begin, int
     hipLaunchKernelGGL((k_step<T, LT, NT>), dim3(count), dim3(NT), 0, st, a, slot_begin);
     return hipGetLastError();
   }
-  void* args[] = {(void*)&a, (void*)&iters};
-  const hipError_t e = hipLaunchCooperativeKernel((const void*)k_persistent<T, LT, NT>, dim3(grid), dim3(NT), args, 0, st);
-  if (e != hipSuccess) (void)hipGetLastError();  // (see launch_mb_one)
-  return e;
+  if constexpr (kOnVersions<T, LT>) {
+    void* args[] = {(void*)&a, (void*)&iters};
+    const hipError_t e = hipLaunchCooperativeKernel((const void*)k_persistent<T, LT, NT>, dim3(grid), dim3(NT), args, 0, st);
+    if (e != hipSuccess) (void)hipGetLastError();  // (see launch_mb_one)
+    return e;
+  }
+  return hipErrorInvalidValue;
 }
 
 // structured costs on the dense mailbox engine, the tiles formed from the
@@ -527,16 +535,18 @@ hipError_t launch_handshake(const HsArgs<T>& a, int engine, int LT, int NT, int 
   return hipErrorInvalidValue;
 }
 
+// workgroups of the version-counter kernel that fit on one compute unit
 template <typename T>
-int max_blocks_per_cu(int engine, int LT, int NT) {
+int max_blocks_per_cu(int LT, int NT) {
   int nb = 0;
   hipError_t e = hipErrorInvalidValue;
-#define MPLPXX_CASE(lt, nt)                                                                           \
-  if (LT == lt && NT == nt) {                                                                         \
-    const void* f = engine == ENGINE_STEP ? (const void*)k_step<T, lt, nt> : (const void*)k_persistent<T, lt, nt>; \
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, nt, 0);                                  \
-    if (e == hipSuccess && engine != ENGINE_STEP) nb = placeable_per_cu(f, nt, nb);                   \
-  }
+#define MPLPXX_CASE(lt, nt)                                                     \
+  if constexpr (sizeof(T) == 4 || kOnVersions<T, lt>)                           \
+    if (LT == lt && NT == nt) {                                                 \
+      const void* f = (const void*)k_persistent<T, lt, nt>;                     \
+      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, nt, 0);          \
+      if (e == hipSuccess) nb = placeable_per_cu(f, nt, nb);                    \
+    }
   MPLPXX_CASE(16, 256)
   MPLPXX_CASE(32, 256)
   MPLPXX_CASE(32, 512)
@@ -552,7 +562,7 @@ int max_blocks_per_cu(int engine, int LT, int NT) {
 
 template hipError_t launch_handshake<float>(const HsArgs<float>&, int, int, int, int, int, int, int, hipStream_t);
 template hipError_t launch_handshake<double>(const HsArgs<double>&, int, int, int, int, int, int, int, hipStream_t);
-template int max_blocks_per_cu<float>(int, int, int);
-template int max_blocks_per_cu<double>(int, int, int);
+template int max_blocks_per_cu<float>(int, int);
+template int max_blocks_per_cu<double>(int, int);
 
 }  // namespace mplpxx

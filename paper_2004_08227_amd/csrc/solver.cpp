@@ -1528,8 +1528,8 @@ int mplpxx_set_option(mplpxx_solver* h, int32_t key, int64_t value) {
                      // (FP64 up to 64 labels: what the workgroups of NT() threads that ran it
                      // without mailboxes allowed; more than one per compute unit counts as one)
                      : h->dtype == MPLPXX_F64 && h->L <= 64 ? (h->L <= 32 ? 1792 : 1024) / h->NT()
-                     : h->dtype == MPLPXX_F32 ? max_blocks_per_cu<float>(ENGINE_PERSISTENT, h->LT(), h->NT())
-                                              : max_blocks_per_cu<double>(ENGINE_PERSISTENT, h->LT(), h->NT());
+                     : h->dtype == MPLPXX_F32 ? max_blocks_per_cu<float>(h->LT(), h->NT())
+                                              : max_blocks_per_cu<double>(h->LT(), h->NT());
       if (value > (int64_t)nb * h->num_cus) return fail(MPLPXX_EINVAL, "grid %lld exceeds co-resident limit %d", (long long)value, nb * h->num_cus);
       h->grid_opt = (int)value;
       return MPLPXX_OK;
