@@ -438,8 +438,9 @@ static int placeable_per_cu(const void* f, int threads, int nb) {
 }
 
 // workgroups of the FP32 mailbox kernel that fit on one compute unit (no
-// dynamic LDS)
-int max_blocks_per_cu_mb(int LT, int NT) {
+// dynamic LDS); where L labels may run on a tile of their own multiple of 16,
+// of either kernel
+int max_blocks_per_cu_mb(int LT, int NT, int L) {
   int nb = 0;
   hipError_t e = hipErrorInvalidValue;
 #define MPLPXX_CASE(lt, nt)                                                                                  \
@@ -458,6 +459,11 @@ int max_blocks_per_cu_mb(int LT, int NT) {
   MPLPXX_CASE(128, 256)
   MPLPXX_CASE(128, 512)
 #undef MPLPXX_CASE
+  if (e == hipSuccess && NT == 256 && mb_odd_tile(L)) {
+    int own = 0;
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&own, mb_odd_kernel(L), NT + 128, 0);
+    if (e == hipSuccess) nb = std::min(nb, placeable_per_cu(mb_odd_kernel(L), NT + 128, own));
+  }
   return e == hipSuccess ? nb : 0;
 }
 

@@ -16,6 +16,8 @@ constexpr size_t kPhiLdsTail = 128 * sizeof(float);
 // 2.34 / 2.00, 112 2.33 / 1.92.  (A tile of 48 gains nothing over 64: at 40
 // labels 1.41 / 1.57, at 48 1.41 / 1.39.)
 constexpr bool mb_odd_tile(int L) { return L > 64 && L <= 112; }
+// the kernel of such a tile, for occupancy queries
+const void* mb_odd_kernel(int L);
 // (four compute waves, dense tables, (H), no trace; a.wgs is set)
 hipError_t launch_mb_odd(const HsArgs<float>& a, unsigned long long* mb, int grid, int iters, int phi_in_lds,
                          size_t dyn_lds, hipStream_t st);

@@ -26,6 +26,14 @@ static hipError_t mb_odd_one(const HsArgs<float>& a, unsigned long long* mb, int
   return e;
 }
 
+const void* mb_odd_kernel(int L) {
+  switch ((L + 15) / 16) {
+    case 5: return (const void*)k_persistent_mb<80, 256, false, false, false, true, odd_depth<80>()>;
+    case 6: return (const void*)k_persistent_mb<96, 256, false, false, false, true, odd_depth<96>()>;
+    default: return (const void*)k_persistent_mb<112, 256, false, false, false, true, odd_depth<112>()>;
+  }
+}
+
 hipError_t launch_mb_odd(const HsArgs<float>& a, unsigned long long* mb, int grid, int iters, int phi_in_lds,
                          size_t dyn_lds, hipStream_t st) {
   switch ((a.L + 15) / 16) {

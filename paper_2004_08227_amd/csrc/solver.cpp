@@ -200,7 +200,7 @@ struct mplpxx_solver {
                        : mb_default_grid(std::min(max_step, num_cus), num_cus, m, L, [] { return 1; }, sizeof(double));
     if (grid_opt == 0 && (mb_engine() || rule_mailbox()))
       g = mb_default_grid(max_step, num_cus, m, L, [&] {
-        return potts && !gen_tiles() ? max_blocks_per_cu_mb_potts() : max_blocks_per_cu_mb(LT(), NT());
+        return potts && !gen_tiles() ? max_blocks_per_cu_mb_potts() : max_blocks_per_cu_mb(LT(), NT(), L);
       });
     if (g > m) g = m;
     if (g < 1) g = 1;
@@ -1524,7 +1524,7 @@ int mplpxx_set_option(mplpxx_solver* h, int32_t key, int64_t value) {
     case MPLPXX_OPT_GRID: {
       if (value < 0) return fail(MPLPXX_EINVAL, "grid must be >= 0");
       const int nb = h->potts && !h->gen_tiles() ? max_blocks_per_cu_mb_potts()
-                     : h->mb_engine() ? max_blocks_per_cu_mb(h->LT(), h->NT())
+                     : h->mb_engine() ? max_blocks_per_cu_mb(h->LT(), h->NT(), h->L)
                      // (FP64 up to 64 labels: what the workgroups of NT() threads that ran it
                      // without mailboxes allowed; more than one per compute unit counts as one)
                      : h->dtype == MPLPXX_F64 && h->L <= 64 ? (h->L <= 32 ? 1792 : 1024) / h->NT()

@@ -51,3 +51,41 @@ def test_iterations_of_a_launch_are_counted_in_31_bits(run):
   int calls = 0;
   CHECK(in_launches(5, 1ll << 40, 1, [&](int, int) { return ++calls == 2 ? hipErrorUnknown : hipSuccess; }) == hipErrorUnknown);
   CHECK(calls == 2);""")
+
+
+def test_workgroups_on_dies(run):
+    """Every logical workgroup once, positions of one matching in blocks on the dies, and the
+    plain order wherever the mapped launch would not fit or the sizes do not suit it."""
+    run("""
+  int mapped = 0, beyond = 0;
+  for (int ms = 1; ms <= 300; ++ms)
+    for (int d = 1; d <= 5; ++d)
+      for (int cap : {64, 256, 512}) {
+        const int G = ms * d, launch = kDies * ((ms + kDies - 1) / kDies) * d;
+        const WgMap w = wg_map(G, ms, true, 1 << 20, cap);
+        CHECK(w.G == G);
+        if (ms < kDies || launch > cap) {
+          beyond += ms >= kDies;
+          CHECK(w.ms == 0 && w.launch == G);
+          for (int b = 0; b < G; ++b) CHECK(wg_logical(w, b) == b);
+          continue;
+        }
+        ++mapped;
+        CHECK(w.ms == ms && w.launch == launch && launch <= cap);
+        std::vector<int> seen(G, 0);
+        for (int b = 0; b < launch; ++b) {
+          const int g = wg_logical(w, b);
+          CHECK(g >= 0 && g <= G);
+          if (g == G) continue;
+          ++seen[g];
+          const int die = b % kDies, p = g % ms;  // the die's block of neighbouring positions
+          CHECK(p >= die * ms / kDies && p < (die + 1) * ms / kDies);
+        }
+        for (int x : seen) CHECK(x == 1);
+      }
+  CHECK(mapped > 300 && beyond > 300);
+  CHECK(wg_map(243, 81, true, 1 << 20, 256).ms == 0);                  // 264 workgroups
+  CHECK(wg_map(20, 10, false, 1 << 20, 256).ms == 0);                  // unequal matchings
+  CHECK(wg_map(21, 10, true, 1 << 20, 256).ms == 0);                   // no multiple
+  CHECK(wg_map(20, 10, true, kLastLevelCache, 256).ms == 10);
+  CHECK(wg_map(20, 10, true, kLastLevelCache + 1, 256).ms == 0);""")
