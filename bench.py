@@ -10,7 +10,9 @@ The JSON line reports edge-block updates/s (``value``), the HBM roofline of
 the dominant kernel from its algorithmic bytes (4 L^2 table bytes + 16 L
 message bytes per edge update), the oracle's CPU throughput on a bounded
 sample, and time to reach the dual bound within epsilon of the best value
-against the plain FP64 oracle.
+against the plain FP64 oracle.  Further sections (batches, sparsification, the
+adjoint, the other updates, structured costs) are summarised in it; their
+details go to stderr, one JSON object a line.
 """
 from __future__ import annotations
 
@@ -464,8 +466,7 @@ def bench_trunc_linear(M, W, iters=50, mix_count=64, tau=8.0, kind=None):
 
 
 def summary(result):
-    """The headline numbers of every section, short enough to survive the
-    end of a long line."""
+    """The headline numbers of every section."""
     sm = {"c1_ms_per_iter": result.get("ms_per_step"), "c1_hbm_frac": result.get("hbm_frac")}
     b = result.get("batched")
     if b:
@@ -811,23 +812,25 @@ def main():
                                               "library's plain HIP read kernel over 4 GiB (median and best of 5); "
                                               "frac_of_measured_read uses the larger median read rate; the "
                                               "roofline peak stays the published 8 TB/s")
-    if not args.no_batch:
-        result["batched"] = bench_batched(M, W, per_problem=not args.no_per_problem)
-    if not args.no_c2:
-        result["c2"] = bench_c2(M, W, with_cpu=not args.no_cpu)
-    if not args.no_adjoint:
-        result["adjoint"] = bench_adjoint(M, W)
-    if not args.no_rules:
-        result["rules"] = bench_rules(M, W)
-    if not args.no_gap:
-        result["gap"] = bench_gap(M, W)
-    if not args.no_potts:
-        result["potts"] = bench_potts(M, W)
-    if not args.no_trunc_linear:
-        result["trunc_linear"] = bench_trunc_linear(M, W)
-    if not args.no_trunc_quad:
-        result["trunc_quad"] = bench_trunc_linear(M, W, kind=M.COST_TRUNC_QUAD, tau=64.0)
-    result["summary"] = summary(result)
+    # the sections' details go to stderr, one JSON object a line; the result line
+    # holds their summary (a line with all of them is longer than a log's end)
+    sections = [("batched", args.no_batch, lambda: bench_batched(M, W, per_problem=not args.no_per_problem)),
+                ("c2", args.no_c2, lambda: bench_c2(M, W, with_cpu=not args.no_cpu)),
+                ("adjoint", args.no_adjoint, lambda: bench_adjoint(M, W)),
+                ("rules", args.no_rules, lambda: bench_rules(M, W)),
+                ("gap", args.no_gap, lambda: bench_gap(M, W)),
+                ("potts", args.no_potts, lambda: bench_potts(M, W)),
+                ("trunc_linear", args.no_trunc_linear, lambda: bench_trunc_linear(M, W)),
+                ("trunc_quad", args.no_trunc_quad, lambda: bench_trunc_linear(M, W, kind=M.COST_TRUNC_QUAD, tau=64.0))]
+    print_result(result, [(name, run) for name, skip, run in sections if not skip])
+
+
+def print_result(result, sections):
+    details = dict(result)
+    for name, run in sections:
+        details[name] = run()
+        print(json.dumps({name: details[name]}), file=sys.stderr, flush=True)
+    result["summary"] = summary(details)
     print(json.dumps(result))
 
 
