@@ -178,10 +178,10 @@ def tune_solver(model, iters=20, make=None, log=None, gain=0.97, repeats=2):
 # ---------------------------------------------------------------------------
 # batches
 # ---------------------------------------------------------------------------
-BATCH_DEFAULTS = {"engine": 0, "lds": 1, "queue": 1, "one_per_model": 0, "wave_lat_mb_us": 2.0,
+BATCH_DEFAULTS = {"engine": 0, "lds": 1, "queue": 1, "one_per_model": 0, "wave_lat_mb_us": 2.2,
                   "wave_lat_lds_us": 2.4, "wave_edge16_us": 0.05, "wave_edge32_us": 0.08, "wave_edge64_us": 0.13}
 BATCH_CHOICES = {"engine": [0, 1, 2], "lds": [1, 0], "queue": [1, 0], "one_per_model": [0, 1],
-                 "wave_lat_mb_us": [1.0, 2.0, 4.0], "wave_lat_lds_us": [1.2, 2.4, 4.8],
+                 "wave_lat_mb_us": [1.1, 2.2, 4.4], "wave_lat_lds_us": [1.2, 2.4, 4.8],
                  "wave_edge16_us": [0.025, 0.05, 0.1], "wave_edge32_us": [0.04, 0.08, 0.16],
                  "wave_edge64_us": [0.08, 0.13, 0.2]}
 
