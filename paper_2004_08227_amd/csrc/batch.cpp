@@ -80,6 +80,7 @@ struct mplpxx_batch {
   double* d_duals = nullptr;
   int* d_slot_of_edge = nullptr;         // all models', for get_state
   float* d_export = nullptr;             // the largest model's messages in edge order
+  size_t export_bytes = 0;
   // plan
   int grid = 0;
   int grid_opt = 0;
@@ -376,7 +377,8 @@ hipError_t ensure_export(mplpxx_batch* b) {
       return e;
     }
   }
-  return hipMalloc(&b->d_export, std::max<size_t>(1, most) * sizeof(float));
+  b->export_bytes = std::max<size_t>(1, most) * sizeof(float);
+  return hipMalloc(&b->d_export, b->export_bytes);
 }
 
 hipError_t enqueue(mplpxx_batch* b, int k) {
@@ -685,9 +687,13 @@ int mplpxx_batch_get_state(mplpxx_batch* b, int32_t model, float* U, float* phi,
       on_device = false;
     }
     if (on_device) {
-      HIP_TRY(launch_phi_by_edge<float>(b->d_phi + d.phi_off, b->d_slot_of_edge + d.slot_off, h.m, h.L, b->d_export, b->stream));
-      HIP_TRY(hipMemcpyAsync(phi, b->d_export, (size_t)h.m * 2 * h.L * sizeof(float), hipMemcpyDeviceToHost, b->stream));
-      HIP_TRY(hipStreamSynchronize(b->stream));
+      hipError_t e = launch_phi_by_edge<float>(b->d_phi + d.phi_off, b->d_slot_of_edge + d.slot_off, h.m, h.L, b->d_export,
+                                               b->stream);
+      if (e == hipSuccess)
+        e = hipMemcpyAsync(phi, b->d_export, (size_t)h.m * 2 * h.L * sizeof(float), hipMemcpyDeviceToHost, b->stream);
+      if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
+      give_back_large(b->d_export, b->export_bytes);
+      HIP_TRY(e);
       return MPLPXX_OK;
     }
     std::vector<float> tmp((size_t)h.m * 2 * h.L);

@@ -122,6 +122,15 @@ template <typename F> inline hipError_t in_launches(int k, long long m, int grid
 // device when a state is read (figures at mplpxx_get_state)
 constexpr size_t kExportOnDevice = 1 << 20;
 
+// device workspaces of calls on a handle stay with it up to this size, larger ones
+// are given back when the call ends
+constexpr size_t kKeepWorkspace = (size_t)96 << 20;
+template <typename T> inline void give_back_large(T*& p, size_t bytes) {
+  if (!p || bytes <= kKeepWorkspace) return;
+  (void)hipFree(p);
+  p = nullptr;
+}
+
 // smallest register tile (16, 32, 64, 128) holding L labels
 inline int next_tile(int L) {
   int lt = 16;

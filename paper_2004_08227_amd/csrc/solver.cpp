@@ -128,7 +128,7 @@ struct mplpxx_solver {
   double last_ms = 0.0;
   bool timed = false;
   int timed_calls = 1;  // iterations of iterate_gap between the two events (1: one iterate call)
-  char* d_gap = nullptr;  // iterate_gap's workspace, kept up to kGapKeep
+  char* d_gap = nullptr;  // iterate_gap's workspace, kept up to kKeepWorkspace
   size_t gap_size = 0;
 
   hipStream_t stream() const { return user_stream ? user_stream : own_stream; }
@@ -794,7 +794,6 @@ template <typename T> int iterate_t(mplpxx_solver* h, int k, double* trace_host)
 // ---------------------------------------------------------------------------
 namespace {
 constexpr size_t kGapStates = (size_t)64 << 20;  // copies of the messages held at once
-constexpr size_t kGapKeep = (size_t)96 << 20;    // a larger workspace is given back when the call ends
 
 int queue_snapshots(mplpxx_solver* h, int c, float* snap) {
   hipStream_t st = h->stream();
@@ -1276,11 +1275,8 @@ int mplpxx_iterate_gap(mplpxx_solver* h, int32_t k, double* dual, double* energy
   int* d_lab = reinterpret_cast<int*>(C > 1 ? edge_t + (size_t)C * h->m : d_gap + 2 * (size_t)k);  // [k][n] labellings
   auto release = [&]() {
     (void)hipStreamSynchronize(st);
-    if (h->gap_size > kGapKeep) {
-      (void)hipFree(h->d_gap);
-      h->d_gap = nullptr;
-      h->gap_size = 0;
-    }
+    give_back_large(h->d_gap, h->gap_size);
+    if (!h->d_gap) h->gap_size = 0;
   };
   const bool one_launch = C > 1 && h->dtype == MPLPXX_F32 && h->plain() && h->m > 0 && !h->solo(false) &&
                           h->NT() == 256 && h->grid() <= h->num_cus && mb_snap_fits(h->m, h->L, h->grid());
@@ -1450,13 +1446,15 @@ int mplpxx_get_state(mplpxx_solver* h, void* U, void* phi, float* U_comp) {
       }
     }
     if (on_device) {
-      HIP_TRY(h->dtype == MPLPXX_F32
-                  ? launch_phi_by_edge<float>(static_cast<const float*>(h->d_phi), h->d_slot_of_edge, h->m, h->L,
-                                              static_cast<float*>(h->d_export), h->stream())
-                  : launch_phi_by_edge<double>(static_cast<const double*>(h->d_phi), h->d_slot_of_edge, h->m, h->L,
-                                               static_cast<double*>(h->d_export), h->stream()));
-      HIP_TRY(hipMemcpyAsync(phi, h->d_export, bytes, hipMemcpyDeviceToHost, h->stream()));
-      HIP_TRY(hipStreamSynchronize(h->stream()));
+      hipError_t e = h->dtype == MPLPXX_F32
+                         ? launch_phi_by_edge<float>(static_cast<const float*>(h->d_phi), h->d_slot_of_edge, h->m, h->L,
+                                                     static_cast<float*>(h->d_export), h->stream())
+                         : launch_phi_by_edge<double>(static_cast<const double*>(h->d_phi), h->d_slot_of_edge, h->m, h->L,
+                                                      static_cast<double*>(h->d_export), h->stream());
+      if (e == hipSuccess) e = hipMemcpyAsync(phi, h->d_export, bytes, hipMemcpyDeviceToHost, h->stream());
+      if (e == hipSuccess) e = hipStreamSynchronize(h->stream());
+      give_back_large(h->d_export, bytes);
+      HIP_TRY(e);
       return MPLPXX_OK;
     }
     std::vector<char> tmp(bytes);
