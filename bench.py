@@ -39,7 +39,8 @@ TRAFFIC = {"src_sha": "8c57154f050dfbd2", "fetch_kib_per_iter": 3768204.6875 / 2
            "write_kib_per_iter": 457708.0 / 20, "write_scale": 1.0}
 TRAFFIC_SRCS = ("paper_2004_08227_amd/csrc/common.h", "paper_2004_08227_amd/csrc/device_common.h",
                 "paper_2004_08227_amd/csrc/step_common.h", "paper_2004_08227_amd/csrc/potts_passes.h",
-                "paper_2004_08227_amd/csrc/potts_mb.h", "paper_2004_08227_amd/csrc/handshake.hip")
+                "paper_2004_08227_amd/csrc/potts_mb.h", "paper_2004_08227_amd/csrc/mb_kernel.h",
+                "paper_2004_08227_amd/csrc/handshake.hip")
 
 
 def kernel_src_sha():

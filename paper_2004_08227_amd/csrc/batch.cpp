@@ -100,7 +100,7 @@ struct mplpxx_batch {
   // wave engine (one wave per edge update; models with L <= 64)
   int engine_opt = 0;          // 0 auto, 1 workgroup (mailbox) engine, 2 wave engine
   bool wave = false;           // the plan runs the wave engine
-  double wv_edge_us[3] = {0.05, 0.08, 0.13};  // workgroup time per edge update besides its bytes, LT 16, 32, 64
+  double wv_edge_us[3] = {0.05, 0.08, 0.13};  // workgroup time per edge update besides its bytes, L <= 16, 32, 64
   double wv_lat_lds_us = 2.4;  // latency of one update, unaries in LDS
   double wv_lat_mb_us = 2.2;   // latency of one update through the mailboxes
   size_t wv_static = 0;        // static LDS of the wave kernel
@@ -131,8 +131,9 @@ bool lds_fits(const mplpxx_batch* b, int i) {
 }
 
 // Wave engine: a team of T workgroups is T * NW workers.  Per iteration a
-// model needs m / T edge updates of workgroup time, each t_w(LT) plus its
-// bytes at the rate a workgroup streams tables with, half of its share of the
+// model needs m / T edge updates of workgroup time, each t_w (of the classes
+// up to 16, 32 and 64 labels; the kernel's tiles are finer, so 17 to 24 labels
+// are priced as 32 and 33 to 56 as 64) plus its bytes at the rate a workgroup streams tables with, half of its share of the
 // nominal 8 TB/s (13 to 17 bytes a nanosecond were measured on teams of every
 // shape, a large copy reaches 19 a compute unit; planned with 23 the large
 // models got too few workgroups: milliseconds an iteration with 3/4 and 2.0 us

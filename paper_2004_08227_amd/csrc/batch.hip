@@ -88,8 +88,9 @@ __device__ __forceinline__ bool next_queued(const BatchArgs& b, int& s_q, int& t
   return true;
 }
 
-// at least two waves per SIMD: one 6-wave workgroup per compute unit, with
-// registers for every tile size without spills
+// at least two waves per SIMD: one 6-wave workgroup per compute unit (256
+// registers; the kernel with the tile of 128 labels spills 134 all the same, the
+// others none)
 template <int NT, int MAXLT>
 __global__ void __launch_bounds__(NT + 128, 2) k_batch(BatchArgs b, int iters) {
   __shared__ BatchSmem<NT, MAXLT> sm;
@@ -167,10 +168,12 @@ size_t batch_lds_limit(int max_lt) {
 // deals its slots to the NW waves round-robin.
 // ---------------------------------------------------------------------------
 // twelve workers per compute unit: one 12-wave workgroup at three waves per
-// SIMD (168 registers hold the 64-label tile and its working vectors).
-// Measured on the batched pose mix, this beats 8 waves at two per SIMD and
-// two workgroups per compute unit (6 waves each, or 8 at four per SIMD,
-// which spills the 64-label path).
+// SIMD, 168 registers each.  With the tiles of all multiples of 8 labels in one
+// kernel the compiler spills 19 of them (80 bytes of scratch a lane; 6 and 28
+// bytes with tiles of 16, 32 and 64 only), which is faster than padding to 64 all
+// the same (wave_engine.h).  Measured on the batched pose mix with the three tiles,
+// this beat 8 waves at two per SIMD and two workgroups per compute unit (6 waves
+// each, or 8 at four per SIMD, which spills far more of the 64-label path).
 #ifndef MPLPXX_WV_WAVES
 #define MPLPXX_WV_WAVES 12
 #endif

@@ -271,9 +271,10 @@ __device__ __forceinline__ void fwd64_role(const Fwd64Args& a, int first_in, int
     pvo = ph[L + out_ic];
   };
   // tables are loaded two steps ahead, one where the argmins take the registers
-  // (with the candidates kept from the passes and two steps ahead, 142 registers
-  // were spilled at 64 labels: forward with records of 100 nodes 2.77 us a
-  // matching, 2.25 now, backward 4.10, 2.92 now)
+  // (k_adj64 at 64 labels: 5 registers spilled where messages stay in memory, none
+  // in LDS; with the candidates kept from the passes and two steps ahead, 142:
+  // forward with records of 100 nodes 2.77 us a matching, 2.25 now, backward 4.10,
+  // 2.92 now)
   constexpr int DEPTH = REC && LT == 64 ? 1 : 2;
   double t0[S::BR][S::BC], t1[S::BR][S::BC], t2[S::BR][S::BC];
   load_tile64(t0, first);

@@ -368,9 +368,10 @@ __global__ void __launch_bounds__(64 * solo_max_waves(LT)) k_solo(SoloArgs<T> a,
 // the lower (side 0) or upper (side 1) node, and shuffled into the tile's rows
 // and columns and back.  Two more LDS round trips a step, but fewer instructions
 // where a lane has several rows and FP32 has the references and corrections of
-// each: the better way in FP32 above 8 labels from two waves a SIMD on
-// (microseconds a matching at 4, 8 and 16 edges, 16 labels: 0.56, 0.66 and 0.99
-// here, 0.51, 0.73 and 1.13 above; 32 labels, 2 edges: 0.86 and 0.95).
+// each.  FP32 above 8 labels runs here for every number of edges: it is the
+// better way from two waves a SIMD on, and with fewer a little behind the one
+// above (microseconds a matching at 4, 8 and 16 edges, 16 labels: 0.56, 0.66 and
+// 0.99 here, 0.51, 0.73 and 1.13 above; 32 labels, 2 edges: 0.86 and 0.95).
 // the lower and the upper half wave's value of x, in the lanes of both
 __device__ __forceinline__ void halves(float x, float& lo, float& hi) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
