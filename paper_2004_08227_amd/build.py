@@ -35,7 +35,9 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-Wno-unused-comman
 
 # The handshake kernels see no NaN: inputs are validated finite (FP32:
 # |cost| <= 1e18), padded tile entries are +inf or 2^126, padded labels of the structured passes
-# +inf, and no pass can form inf - inf.  Telling the compiler so lets min
+# +inf, and no pass can form inf - inf (but for FP64 costs near the largest
+# double, whose sums overflow: their values mean nothing, and no index made from
+# them leaves its array).  Telling the compiler so lets min
 # reductions skip the quieting of their operands and fold into DPP forms;
 # on non-NaN operands the results are bitwise the same.
 EXTRA = {"handshake.hip": ["-fno-honor-nans"], "batch.hip": ["-fno-honor-nans"], "rules.hip": ["-fno-honor-nans"],
