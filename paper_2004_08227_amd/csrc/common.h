@@ -241,7 +241,7 @@ bool adj_pair_fits(int m, int L, int grid64, int grid32);
 hipError_t launch_adj_pair(const Fwd64Args& f, const HsArgs<float>& a, unsigned long long* mb, int grid32,
                            unsigned long long* clk, hipStream_t st);
 
-int max_blocks_per_cu_mb(int LT, int NT, int L);
+int max_blocks_per_cu_mb(int LT, int NT, int L, bool traces);
 // the (M) and (U) updates on the per-matching engine (rules.hip); rule 1 = M, 2 = U
 template <typename T>
 hipError_t launch_step_rule(const HsArgs<T>& a, int rule, int LT, int NT, int slot_begin, int count, hipStream_t st);

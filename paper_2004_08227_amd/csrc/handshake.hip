@@ -438,16 +438,24 @@ static int placeable_per_cu(const void* f, int threads, int nb) {
 }
 
 // workgroups of the FP32 mailbox kernel that fit on one compute unit (no
-// dynamic LDS); where L labels may run on a tile of their own multiple of 16,
-// of either kernel
-int max_blocks_per_cu_mb(int LT, int NT, int L) {
-  int nb = 0;
+// dynamic LDS): of the instance with the most registers (ragged labels, messages
+// prefetched), with traces of the two that run (16 labels and 256 threads: 64
+// registers, four workgroups, without a trace, 67 and three with); where L labels
+// may run on a tile of their own multiple of 16, of that kernel too
+static hipError_t fit_per_cu(const void* f, int threads, int& nb) {
+  int own = 0;
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&own, f, threads, 0);
+  if (e == hipSuccess) nb = std::min(nb, placeable_per_cu(f, threads, own));
+  return e;
+}
+int max_blocks_per_cu_mb(int LT, int NT, int L, bool traces) {
+  int nb = 1 << 20;
   hipError_t e = hipErrorInvalidValue;
-#define MPLPXX_CASE(lt, nt)                                                                                  \
-  if (LT == lt && NT == nt) {                                                                                \
-    const void* f = (const void*)k_persistent_mb<lt, nt, false, false, false, true>;                         \
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, nt + 128, 0);                                   \
-    if (e == hipSuccess) nb = placeable_per_cu(f, nt + 128, nb);                                             \
+#define MPLPXX_CASE(lt, nt)                                                                                     \
+  if (LT == lt && NT == nt) {                                                                                   \
+    e = fit_per_cu((const void*)k_persistent_mb<lt, nt, false, false, false, true>, nt + 128, nb);              \
+    if (e == hipSuccess && traces)                                                                              \
+      e = fit_per_cu((const void*)k_persistent_mb<lt, nt, false, false, true, true>, nt + 128, nb);             \
   }
   MPLPXX_CASE(16, 64)
   MPLPXX_CASE(16, 256)
@@ -459,11 +467,7 @@ int max_blocks_per_cu_mb(int LT, int NT, int L) {
   MPLPXX_CASE(128, 256)
   MPLPXX_CASE(128, 512)
 #undef MPLPXX_CASE
-  if (e == hipSuccess && NT == 256 && mb_odd_tile(L)) {
-    int own = 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&own, mb_odd_kernel(L), NT + 128, 0);
-    if (e == hipSuccess) nb = std::min(nb, placeable_per_cu(mb_odd_kernel(L), NT + 128, own));
-  }
+  if (e == hipSuccess && NT == 256 && mb_odd_tile(L)) e = fit_per_cu(mb_odd_kernel(L), NT + 128, nb);
   return e == hipSuccess ? nb : 0;
 }
 

@@ -101,7 +101,7 @@ extern "C" int mplpxx_solve_noalloc(int32_t n, int32_t L, int64_t m, const int32
   HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   const int LT = next_tile(L), NT = 256;
   const int G = std::max(
-      1, std::min<int>(mb_default_grid(max_step, cus, m, L, [&] { return max_blocks_per_cu_mb(LT, NT, L); }),
+      1, std::min<int>(mb_default_grid(max_step, cus, m, L, [&] { return max_blocks_per_cu_mb(LT, NT, L, false); }),
                        (int)std::max<int64_t>(m, 1)));
   const size_t nL = (size_t)n * L, mLL = (size_t)m * L * L;
   const size_t owned = ((size_t)m + G - 1) / G;

@@ -193,6 +193,17 @@ struct mplpxx_solver {
   }
   // small models on one workgroup (solo.h)
   bool solo(bool trace) const { return plain() && solo_fits(n, L, m, S, max_step, esz, trace); }
+  // workgroups of the FP32 mailbox kernels on a compute unit, asked for once per
+  // number of threads
+  mutable int fit_key = -1, fit = 0;
+  int fit_per_cu() const {
+    const int key = 2 * NT() + (potts && !gen_tiles());
+    if (fit_key != key) {
+      fit = potts && !gen_tiles() ? max_blocks_per_cu_mb_potts() : max_blocks_per_cu_mb(LT(), NT(), L, true);
+      fit_key = key;
+    }
+    return fit;
+  }
   int grid() const {
     int g = grid_opt > 0 ? grid_opt : num_cus;
     if (mb64_engine())
@@ -200,7 +211,7 @@ struct mplpxx_solver {
                        : mb_default_grid(std::min(max_step, num_cus), num_cus, m, L, [] { return 1; }, sizeof(double));
     if (grid_opt == 0 && (mb_engine() || rule_mailbox()))
       g = mb_default_grid(max_step, num_cus, m, L, [&] {
-        return potts && !gen_tiles() ? max_blocks_per_cu_mb_potts() : max_blocks_per_cu_mb(LT(), NT(), L);
+        return fit_per_cu();
       });
     if (g > m) g = m;
     if (g < 1) g = 1;
@@ -726,7 +737,7 @@ template <typename T> int queue_iterate(mplpxx_solver* h, int k, double* trace_h
       // (more than one workgroup per compute unit: messages in HBM, so that
       // the workgroups' LDS never limits how many fit)
       const int in_lds = phi_bytes <= kPhiLdsBudget && G <= h->num_cus && h->phi_opt != 2 ? 1 : 0;
-      HIP_TRY(in_launches(k, h->m, G, [&](int done, int c) -> hipError_t {
+      const hipError_t launched = in_launches(k, h->m, G, [&](int done, int c) -> hipError_t {
         if (trace_host) {
           a.trace = h->d_trace_nodes + (size_t)done * h->n;
           a.trace_e = h->d_trace_e + (size_t)done * h->m * trace_w;
@@ -741,13 +752,14 @@ template <typename T> int queue_iterate(mplpxx_solver* h, int k, double* trace_h
         if (e != hipSuccess) return e;
         return launch_mb_fini(static_cast<float*>(h->d_U), h->d_Ulo, h->d_mb, h->n, h->L, a.mbs,
                               trace_host ? a.trace + (size_t)(c - 1) * h->n : nullptr, st);
-      }));
+      });
+      HIP_TRY(launched);
     } else if (h->L <= 64) {
       // FP64: the mailbox forward (two tagged words per label, no fences)
       Fwd64Args f{};
       HIP_TRY(fwd64_args(h, k, &f));
       f.grid = h->grid();
-      HIP_TRY(in_launches(k, h->m, f.grid, [&](int done, int c) -> hipError_t {
+      const hipError_t launched = in_launches(k, h->m, f.grid, [&](int done, int c) -> hipError_t {
         f.iters = c;
         f.trace = trace_host ? h->d_trace_nodes + (size_t)done * h->n : nullptr;
         hipError_t e = launch_mb64_init(static_cast<const double*>(h->d_U), h->d_mb64, h->n, h->L, st);
@@ -755,7 +767,8 @@ template <typename T> int queue_iterate(mplpxx_solver* h, int k, double* trace_h
         if (e != hipSuccess) return e;
         return launch_mb64_fini(static_cast<double*>(h->d_U), h->d_mb64, h->n, h->L,
                                 trace_host ? f.trace + (size_t)(c - 1) * h->n : nullptr, st);
-      }));
+      });
+      HIP_TRY(launched);
     } else {
       HsArgs<T> a = hs_args<T>(h, trace_host ? h->d_trace_nodes : nullptr);
       HIP_TRY(launch_fill_int(h->d_ver, 0, h->n, st));
@@ -1522,7 +1535,7 @@ int mplpxx_set_option(mplpxx_solver* h, int32_t key, int64_t value) {
     case MPLPXX_OPT_GRID: {
       if (value < 0) return fail(MPLPXX_EINVAL, "grid must be >= 0");
       const int nb = h->potts && !h->gen_tiles() ? max_blocks_per_cu_mb_potts()
-                     : h->mb_engine() ? max_blocks_per_cu_mb(h->LT(), h->NT(), h->L)
+                     : h->mb_engine() ? max_blocks_per_cu_mb(h->LT(), h->NT(), h->L, true)
                      // (FP64 up to 64 labels: what the workgroups of NT() threads that ran it
                      // without mailboxes allowed; more than one per compute unit counts as one)
                      : h->dtype == MPLPXX_F64 && h->L <= 64 ? (h->L <= 32 ? 1792 : 1024) / h->NT()

@@ -33,3 +33,50 @@ def test_more_edges_than_compute_units(L):
 
 def test_mapped_launch_beyond_the_chip():
     _same(W.uniform(162, 6, seed=1), 243)  # 81 positions, three workgroups each: 264 mapped
+
+
+@pytest.mark.parametrize("L,threads", [(13, 256), (16, 256), (13, 64), (20, 64), (29, 256)])
+def test_traces_at_the_largest_grid(L, threads):
+    """The largest grid that is accepted, and the default of a matching that fills it, fit the
+    chip in every kernel that may run there; traces need more registers than iterations."""
+    m, rng = 1500, np.random.default_rng(L)
+    pairs = rng.permutation(2 * m).reshape(m, 2)
+    edges = np.concatenate([pairs, np.stack([pairs[:-1, 0], pairs[1:, 1]], 1)]).astype(np.int32)
+    n = 2 * m
+    model = W.Model(n, L, edges, rng.random((n, L), dtype=np.float32), rng.random((len(edges), L, L), dtype=np.float32))
+    most, got = 0, []
+    for grid in (None, 0):
+        with M.Solver.from_model(model) as s:
+            s.set_option(M.OPT_THREADS, threads)
+            s.set_option(M.OPT_SPIN_LIMIT, 1 << 20)
+            if grid is None:
+                for per_cu in range(1, 17):
+                    try:
+                        s.set_option(M.OPT_GRID, 256 * per_cu)
+                        most = 256 * per_cu
+                    except M.MplpError:
+                        break
+            assert s.info("grid") <= most
+            print("CASE", L, threads, "grid", s.info("grid"), "largest", most, flush=True)
+            t = s.iterate_trace(3)
+            s.iterate(2)
+            for rule in (M.RULE_M, M.RULE_U):
+                if threads == 256:
+                    s.set_option(M.OPT_RULE, rule)
+                    s.iterate(2)
+            got.append([t, *s.get_state(comp=True)])
+    with M.Solver.from_model(model) as s:
+        s.set_option(M.OPT_ENGINE, M.ENGINE_STEP)
+        s.iterate_trace(3)
+        s.iterate(2)
+        for rule in (M.RULE_M, M.RULE_U):
+            if threads == 256:
+                s.set_option(M.OPT_RULE, rule)
+                s.iterate(2)
+        want = s.get_state(comp=True)
+    for g in got:
+        assert np.array_equal(g[0], got[0][0])
+        for x, y in zip(g[1:], want):
+            assert x.tobytes() == y.tobytes()
+    if (L, threads) == (13, 256):  # 67 registers: seven waves a SIMD, two of them of every workgroup
+        assert most == 3 * 256
