@@ -259,7 +259,7 @@ hipError_t launch_persistent_mb(const HsArgs<float>& a, unsigned long long* mb, 
                                 int phi_in_lds, size_t dyn_lds, hipStream_t st, int prefetch = 0, int kind = 0,
                                 int rule = 0);
 // the same for Potts models (one weight per slot, L <= 64; potts_mb.h)
-int max_blocks_per_cu_mb_potts();
+int max_blocks_per_cu_mb_potts(int kind);
 hipError_t launch_persistent_mb_potts(const HsArgs<float>& a, unsigned long long* mb, int grid, int iters,
                                       int phi_in_lds, size_t dyn_lds, hipStream_t st, int kind = MPLPXX_COST_POTTS);
 // the same on `grid` workgroups, the messages of every iteration kept in a.snap

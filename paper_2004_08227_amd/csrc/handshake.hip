@@ -491,11 +491,12 @@ hipError_t launch_persistent_mb(const HsArgs<float>& a, unsigned long long* mb, 
   return hipErrorInvalidValue;
 }
 
-int max_blocks_per_cu_mb_potts() {
-  int nb = 0;
-  const void* f = (const void*)k_persistent_mb_potts<false, MPLPXX_COST_POTTS>;
-  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, kPottsNT + 128, 0);
-  return e == hipSuccess ? placeable_per_cu(f, kPottsNT + 128, nb) : 0;
+int max_blocks_per_cu_mb_potts(int kind) {
+  int nb = 1 << 20;
+  const void* f = kind == MPLPXX_COST_TRUNC_QUAD     ? (const void*)k_persistent_mb_potts<false, MPLPXX_COST_TRUNC_QUAD>
+                  : kind == MPLPXX_COST_TRUNC_LINEAR ? (const void*)k_persistent_mb_potts<false, MPLPXX_COST_TRUNC_LINEAR>
+                                                     : (const void*)k_persistent_mb_potts<false, MPLPXX_COST_POTTS>;
+  return fit_per_cu(f, kPottsNT + 128, nb) == hipSuccess ? nb : 0;
 }
 
 hipError_t launch_persistent_mb_potts(const HsArgs<float>& a, unsigned long long* mb, int grid, int iters,

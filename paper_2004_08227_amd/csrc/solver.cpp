@@ -199,7 +199,7 @@ struct mplpxx_solver {
   int fit_per_cu() const {
     const int key = 2 * NT() + (potts && !gen_tiles());
     if (fit_key != key) {
-      fit = potts && !gen_tiles() ? max_blocks_per_cu_mb_potts() : max_blocks_per_cu_mb(LT(), NT(), L, true);
+      fit = potts && !gen_tiles() ? max_blocks_per_cu_mb_potts(potts) : max_blocks_per_cu_mb(LT(), NT(), L, true);
       fit_key = key;
     }
     return fit;
@@ -1534,7 +1534,7 @@ int mplpxx_set_option(mplpxx_solver* h, int32_t key, int64_t value) {
       return MPLPXX_OK;
     case MPLPXX_OPT_GRID: {
       if (value < 0) return fail(MPLPXX_EINVAL, "grid must be >= 0");
-      const int nb = h->potts && !h->gen_tiles() ? max_blocks_per_cu_mb_potts()
+      const int nb = h->potts && !h->gen_tiles() ? max_blocks_per_cu_mb_potts(MPLPXX_COST_POTTS)
                      : h->mb_engine() ? max_blocks_per_cu_mb(h->LT(), h->NT(), h->L, true)
                      // (FP64 up to 64 labels: what the workgroups of NT() threads that ran it
                      // without mailboxes allowed; more than one per compute unit counts as one)

@@ -80,3 +80,25 @@ def test_traces_at_the_largest_grid(L, threads):
             assert x.tobytes() == y.tobytes()
     if (L, threads) == (13, 256):  # 67 registers: seven waves a SIMD, two of them of every workgroup
         assert most == 3 * 256
+
+
+@pytest.mark.parametrize("kind", [M.COST_POTTS, M.COST_TRUNC_LINEAR, M.COST_TRUNC_QUAD])
+def test_structured_costs_in_label_order(kind):
+    """700 edges a matching on one compute wave in label order: the quadratic kind's kernel has
+    room for two workgroups on a compute unit, the others' for eight."""
+    n, L, rng = 1400, 9, np.random.default_rng(kind)
+    ring = np.array([(u, u + 1) for u in range(n - 1)] + [(0, n - 1)], dtype=np.int32)
+    prm = rng.random((n, M.COST_PARAMS[kind]), dtype=np.float32)
+    if kind != M.COST_POTTS:
+        prm[:, 1] = rng.integers(1, 2 * L, n)
+    model, got = W.Model(n, L, ring, rng.random((n, L), dtype=np.float32), prm), []
+    for threads in (64, 256):
+        with M.Solver.from_structured(model, kind) as s:
+            s.set_option(M.OPT_THREADS, threads)
+            print("CASE", kind, threads, "grid", s.info("grid"), flush=True)
+            s.iterate(3)
+            got.append((*s.get_state(comp=True), s.dual_bound()))
+    if kind == M.COST_TRUNC_LINEAR:  # (other sums: FP32 rounding of costs up to 1 a few updates long)
+        assert np.abs(got[0][0] - got[1][0]).max() <= 1e-5
+    else:
+        assert all(np.array_equal(x, y) for x, y in zip(*got))
