@@ -321,8 +321,9 @@ int mplpxx_iterate_trace(mplpxx_solver* h, int32_t k, double* trace);
 #define MPLPXX_OPT_THREADS 2     /* threads per workgroup: 0 auto, 256, 512, 1024; 64 (one compute
                                     wave, FP32 persistent engine) up to 32 labels.  The persistent
                                     engine runs FP64 models up to 64 labels on 256 whatever this says */
-#define MPLPXX_OPT_GRID 3        /* workgroups of the persistent engine (0 auto; FP64 up to 64 labels:
-                                    at most one per compute unit is used) */
+#define MPLPXX_OPT_GRID 3        /* workgroups of the persistent engine (0 auto).  At most as many run as
+                                    fit the device together under the other options (FP64 up to 64
+                                    labels: one per compute unit) */
 #define MPLPXX_OPT_SPIN_LIMIT 4  /* bound in polls of the device waits of iterations and adjoints (0 default) */
 #define MPLPXX_OPT_PROFILE 5     /* 1: record per-slot timestamps (persistent FP32 engine) */
 #define MPLPXX_OPT_ADJOINT_F64 6 /* FP32 handles: 1 (default) differentiate an FP64 run on the same costs

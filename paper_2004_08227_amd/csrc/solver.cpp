@@ -214,6 +214,9 @@ struct mplpxx_solver {
         return fit_per_cu();
       });
     if (g > m) g = m;
+    // (a grid that was set under other threads, costs or updates: no more
+    // workgroups than are certain of a place together)
+    if (g > num_cus && (mb_engine() || rule_mailbox())) g = std::min(g, std::max(1, fit_per_cu()) * num_cus);
     if (g < 1) g = 1;
     return g;
   }

@@ -102,3 +102,35 @@ def test_structured_costs_in_label_order(kind):
         assert np.abs(got[0][0] - got[1][0]).max() <= 1e-5
     else:
         assert all(np.array_equal(x, y) for x, y in zip(*got))
+
+
+OPTIONS = [
+    ("threads after the grid", 13, [(M.OPT_THREADS, 64), (M.OPT_GRID, 1280), (M.OPT_THREADS, 256)]),
+    ("(M), then the grid", 48, [(M.OPT_RULE, M.RULE_M), (M.OPT_GRID, 512)]),
+    ("(U), then the grid", 17, [(M.OPT_RULE, M.RULE_U), (M.OPT_GRID, 700)]),
+    ("(M), large tile", 113, [(M.OPT_RULE, M.RULE_M), (M.OPT_GRID, 300)]),
+    ("per matching, then the grid", 40, [(M.OPT_ENGINE, M.ENGINE_STEP), (M.OPT_GRID, 512), (M.OPT_ENGINE, 0)]),
+]
+
+
+@pytest.mark.parametrize("name,L,options", OPTIONS, ids=[o[0] for o in OPTIONS])
+def test_grids_set_under_other_options(name, L, options):
+    m, rng = (1300, np.random.default_rng(L)) if L <= 64 else (400, np.random.default_rng(L))
+    edges = rng.permutation(2 * m).reshape(m, 2).astype(np.int32)
+    model = W.Model(2 * m, L, edges, rng.random((2 * m, L), dtype=np.float32), rng.random((m, L, L), dtype=np.float32))
+    got = []
+    for engine in (None, M.ENGINE_STEP):
+        with M.Solver.from_model(model) as s:
+            s.set_option(M.OPT_SPIN_LIMIT, 1 << 20)
+            for key, value in options:
+                try:
+                    s.set_option(key, value)
+                except M.MplpError:  # (a limit of these options: nothing larger runs then)
+                    assert key == M.OPT_GRID
+            if engine is not None:
+                s.set_option(M.OPT_ENGINE, engine)
+            print("CASE", name, s.info("grid"), flush=True)
+            s.iterate(3)
+            got.append(s.get_state(comp=True))
+    for x, y in zip(*got):
+        assert x.tobytes() == y.tobytes()
